@@ -1,0 +1,508 @@
+"""Timed cases of the library's public entry points.
+
+Every case is one call (or one forward-and-inverse pair of calls) that a
+program using the library makes in its loop, with the plan, the workspaces
+and the output arrays that such a program keeps between calls.  `listed()`
+gives the fixed cases, `draw()` further ones of the same ranges, `prepare()`
+the state before the call, `run()` the call, `work()` the bytes and floating
+point operations the result cannot do without, and `exact()` the same outputs
+computed in 64 bits with plain torch.
+
+The inputs are synthetic and seeded, with the shapes of the bunches in
+`paper_1509_07685_amd/workloads.py` (drawn with torch on the device, because
+up to 1e8 particles are drawn for every state).
+"""
+
+import math
+
+import numpy as np
+import torch
+
+from paper_1509_07685_amd import dks
+from paper_1509_07685_amd import workloads as wl
+
+EPS0 = 8.8541878128e-12       # F/m
+DEV = "cuda"
+TORCH = {"f32": torch.float32, "f64": torch.float64}
+NP = {"f32": np.float32, "f64": np.float64}
+
+
+# --------------------------------------------------------------------------
+# the cases
+# --------------------------------------------------------------------------
+
+def _step(name, n, np_, dtype, bunch, h=None, scheme="cic", kind="step"):
+    c = {"name": name, "kind": kind, "nx": n[0], "ny": n[1], "nz": n[2], "np": np_, "dtype": dtype, "bunch": bunch,
+         "scheme": scheme, "hx": 0.0, "hy": 0.0, "hz": 0.0}
+    if h is not None:
+        c.update(hx=h[0], hy=h[1], hz=h[2])
+    return c
+
+
+def listed():
+    return [
+        # The smallest step: a fixed mesh over a small bunch in double
+        # precision (the launches count), a third of it outside the mesh.
+        _step("step_32_f64", (32, 32, 32), 10_000, "f64", "gauss", (1e-4, 1e-4, 1e-4)),
+        # The ordinary single-precision step of a particle-fitted cubic mesh.
+        _step("step_64_f32", (64, 64, 64), 1_000_000, "f32", "ball"),
+        # A mixed-radix mesh fitted to a medium bunch in double precision:
+        # one of the shapes of the request stream.
+        _step("step_96x96x192_f64", (96, 96, 192), 316_229, "f64", "gauss"),
+        # The wider assignment scheme, odd particle count, mixed-radix mesh.
+        _step("step_tsc_144x128x96_f32", (144, 128, 96), 3_000_001, "f32", "gauss", scheme="tsc"),
+        # A long bunch on anisotropic cells, field back in the input order.
+        _step("step_elongated_f32", (128, 128, 256), 10_000_000, "f32", "long", (5e-5, 5e-5, 2e-4)),
+        # The largest step: the particles stay on the device in the order the
+        # previous step left them; the program follows marked particles.
+        _step("sorted_256_f32", (256, 256, 256), 100_000_000, "f32", "halo", kind="sorted"),
+        # Eight waiting requests of one shape in one launch sequence.
+        {"name": "batched_8x48_f32", "kind": "batched", "nx": 48, "ny": 48, "nz": 48, "np": 100_000, "dtype": "f32",
+         "batch": 8},
+        # Mesh-only solve: density in, potential and field out.
+        {"name": "rho_256_f32", "kind": "rho", "nx": 256, "ny": 256, "nz": 256, "dtype": "f32", "hx": 1e-5,
+         "hy": 1e-5, "hz": 1e-5},
+        # The raw transform at the paper's largest size.
+        {"name": "fft_512x512x256_f32", "kind": "c2c", "nx": 512, "ny": 512, "nz": 256, "batch": 1, "dtype": "f32"},
+        # A real field to its half spectrum and back, mixed radices, a stack
+        # of arrays, double precision.
+        {"name": "fft_r2c_216x144x96x4_f64", "kind": "r2c", "nx": 216, "ny": 144, "nz": 96, "batch": 4, "dtype": "f64"},
+        # One evaluation of the fit statistic: the largest data set of the
+        # paper's fitting table.
+        {"name": "musr_chisq_1", "kind": "musr", "n_det": 16, "n_bins": 206_250, "sets": 1, "stat": "chisq"},
+        # A central-difference gradient of the log-likelihood: 2 * 66 + 1 sets.
+        {"name": "musr_mle_133", "kind": "musr", "n_det": 16, "n_bins": 206_250, "sets": 133, "stat": "mle"},
+    ]
+
+
+def _extents(lo, hi):
+    """The 2^a 3^b in [lo, hi]."""
+    return sorted(v for a in range(13) for b in range(8) for v in [2 ** a * 3 ** b] if lo <= v <= hi)
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _mesh(rng, lo, hi, most):
+    """Three extents, spread over their logarithm, of at most `most` nodes."""
+    ext = _extents(lo, hi)
+    while True:
+        want = [rng.uniform(math.log(lo), math.log(hi)) for _ in range(3)]
+        n = [min(ext, key=lambda v, w=w: abs(math.log(v) - w)) for w in want]
+        if n[0] * n[1] * n[2] <= most:
+            return n
+
+
+def draw(rng):
+    kind = rng.choice(["step", "step", "step", "sorted", "batched", "rho", "c2c", "r2c", "musr", "musr"])
+    dtype = "f32" if rng.random() < 0.6 else "f64"
+    if kind in ("step", "sorted"):
+        n = _mesh(rng, 16, 256, 256 ** 3 // (1 if dtype == "f32" else 2))
+        c = {"kind": kind, "nx": n[0], "ny": n[1], "nz": n[2],
+             "np": _log(rng, 10_000, 30_000_000 if dtype == "f32" else 10_000_000), "dtype": dtype,
+             "bunch": rng.choice(["gauss", "ball", "halo", "long"]), "scheme": rng.choice(["cic", "cic", "ngp", "tsc"]),
+             "hx": 0.0, "hy": 0.0, "hz": 0.0}
+        if rng.random() < 0.4:      # an explicit mesh over about +-3 sigma of the bunch
+            s = _sigma(c["bunch"])
+            c.update({"h" + d: 6.4 * s[i] / n[i] for i, d in enumerate("xyz")})
+        return c
+    if kind == "batched":
+        n = _mesh(rng, 32, 128, 128 ** 3)
+        return {"kind": kind, "nx": n[0], "ny": n[1], "nz": n[2], "np": _log(rng, 10_000, 1_000_000), "dtype": dtype,
+                "batch": rng.randint(2, 8)}
+    if kind == "rho":
+        n = _mesh(rng, 16, 256, 256 ** 3 // (1 if dtype == "f32" else 2))
+        return {"kind": kind, "nx": n[0], "ny": n[1], "nz": n[2], "dtype": dtype, "hx": 1e-5,
+                "hy": 1e-5 * rng.choice([1, 2]), "hz": 1e-5 * rng.choice([1, 2, 4])}
+    if kind in ("c2c", "r2c"):
+        n = _mesh(rng, 16, 512, 2 ** 26 // (1 if dtype == "f32" else 2))
+        most = max(1, min(8, 2 ** 26 // (n[0] * n[1] * n[2] * (1 if dtype == "f32" else 2))))
+        return {"kind": kind, "nx": n[0], "ny": n[1], "nz": n[2], "batch": rng.randint(1, most), "dtype": dtype}
+    n_det = rng.randint(4, 32)
+    return {"kind": "musr", "n_det": n_det, "n_bins": _log(rng, 4096, 206_250),
+            "sets": rng.choice([1, 1, rng.randint(2, 2 * (2 + 4 * n_det) + 1)]), "stat": rng.choice(["chisq", "mle"])}
+
+
+# --------------------------------------------------------------------------
+# inputs
+# --------------------------------------------------------------------------
+
+def _rng(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(seed))
+    return g
+
+
+def _sigma(bunch):
+    return {"gauss": (1e-3, 1e-3, 1e-3), "ball": (1.25e-3, 1.25e-3, 1.25e-3), "halo": (1e-3, 1e-3, 1e-3),
+            "long": (1e-3, 1e-3, 1e-2)}[bunch]
+
+
+def _ball(g, num, radius):
+    v = torch.randn((3, num), generator=g, dtype=torch.float32, device=DEV)
+    v /= v.square().sum(0).sqrt().clamp_min(1e-20)
+    return v * (radius * torch.rand(num, generator=g, dtype=torch.float32, device=DEV).pow(1.0 / 3.0))
+
+
+def _bunch(bunch, num, seed, dtype):
+    """x, y, z of a bunch, metres (particles in no particular order)."""
+    g = _rng(seed)
+    if bunch == "ball":
+        p = _ball(g, num, 2.5e-3)
+    else:
+        p = torch.randn((3, num), generator=g, dtype=torch.float32 if num > 20_000_000 else torch.float64, device=DEV)
+        for d, s in enumerate(_sigma(bunch)):
+            p[d] *= s
+        if bunch == "halo":       # every tenth particle uniform in the 5 sigma ball
+            halo = p[:, 9::10]
+            halo.copy_(_ball(g, halo.shape[1], 5e-3))
+    return tuple(p[d].to(TORCH[dtype]).contiguous() for d in range(3))
+
+
+def _n(c):
+    return c["nx"], c["ny"], c["nz"]
+
+
+def _h(c):
+    return (c["hx"], c["hy"], c["hz"]) if c["hx"] else None
+
+
+def _q(c):
+    return wl.TOTAL_CHARGE / c["np"]
+
+
+def _request(c, seed, b):
+    """Element b of a batch: its own particle count and bunch widths."""
+    num = int(c["np"] * np.random.default_rng([c["np"], b]).uniform(0.3, 1.0))
+    sigma = np.random.default_rng([int(seed), b]).uniform(0.5e-3, 2e-3, 3)
+    p = torch.randn((3, num), generator=_rng(seed * 16 + b), dtype=torch.float64, device=DEV)
+    return tuple((p[d] * sigma[d]).to(TORCH[c["dtype"]]).contiguous() for d in range(3))
+
+
+def _rho(c, seed):
+    """Charge density of a 1 nC bunch with granular noise, C/m^3."""
+    n, h = _n(c), _h(c)
+    ax = [(torch.arange(n[d], dtype=torch.float64, device=DEV) - 0.5 * (n[d] - 1)) / (n[d] / 6.4) for d in range(3)]
+    w = torch.exp(-0.5 * (ax[2][:, None, None] ** 2 + ax[1][None, :, None] ** 2 + ax[0][None, None, :] ** 2))
+    w = w * (0.5 + torch.rand(w.shape, generator=_rng(seed), dtype=torch.float64, device=DEV))
+    return (w * (wl.TOTAL_CHARGE / (w.sum() * h[0] * h[1] * h[2]))).to(TORCH[c["dtype"]])
+
+
+def _field(c, seed):
+    shape = (c["batch"], c["nz"], c["ny"], c["nx"])
+    if c["kind"] == "c2c":
+        dt = torch.complex64 if c["dtype"] == "f32" else torch.complex128
+        return torch.randn(shape, generator=_rng(seed), dtype=dt, device=DEV)
+    return torch.randn(shape, generator=_rng(seed), dtype=TORCH[c["dtype"]], device=DEV)
+
+
+def _musr(c, seed):
+    """Histograms of counts [n_det][n_bins], bin width (us), parameter sets
+    [sets][2 + 4 n_det] around the start of a fit."""
+    nd, nb = c["n_det"], c["n_bins"]
+    dt = 10.0 / nb
+    j = np.arange(nd)
+    n0 = 0.5 * 3e6 / wl.MUON_LIFETIME_US * dt
+    truth = np.concatenate([[0.3, 100.0],
+                            np.stack([np.full(nd, n0), np.full(nd, 0.5), 0.25 + 0.01 * np.cos(j),
+                                      2.0 * np.pi * j / nd], 1).ravel()])
+    data = torch.poisson(_musr_model(torch.from_numpy(truth).to(DEV), nd, nb, dt), generator=_rng(seed))
+    r = np.random.default_rng(int(seed))
+    start = truth * (1.0 + 0.02 * r.uniform(-1.0, 1.0, truth.size))
+    return data.contiguous(), dt, start * (1.0 + 1e-4 * r.uniform(-1.0, 1.0, (c["sets"], truth.size)))
+
+
+def _musr_model(p, nd, nb, dt):
+    t = torch.arange(nb, dtype=torch.float64, device=DEV) * dt
+    det = p[2:].reshape(nd, 4)
+    w = 2.0 * math.pi * wl.MUON_GAMMA_MHZ_PER_G * p[1]
+    asym = det[:, 2, None] * torch.exp(-0.5 * (p[0] * t) ** 2) * torch.cos(w * t + det[:, 3, None])
+    return det[:, 0, None] * torch.exp(-t / wl.MUON_LIFETIME_US) * (1.0 + asym) + det[:, 1, None]
+
+
+# --------------------------------------------------------------------------
+# the state before a call, and the call
+# --------------------------------------------------------------------------
+
+def _field_out(num, dt):
+    return tuple(torch.empty(num, dtype=dt, device=DEV) for _ in range(3)) + (torch.zeros(1, dtype=torch.int64,
+                                                                                          device=DEV),)
+
+
+def prepare(case, seed):
+    c, dt = case, TORCH.get(case.get("dtype"))
+    s = {"case": c}
+    if c["kind"] in ("step", "sorted"):
+        pos = _bunch(c["bunch"], c["np"], seed, c["dtype"])
+        plan = dks.PoissonPlan(_n(c), _h(c), c["dtype"], scheme=c["scheme"])
+        plan.reserve_particles(c["np"])
+        s.update(plan=plan, pos=pos, out=_field_out(c["np"], dt))
+        if c["kind"] == "sorted":
+            # the previous step leaves the particles in its order; every 64th
+            # particle is marked
+            s["pos"], _, _, _, idx = plan.solve_particles_sorted(*pos, _q(c), want_index=True)
+            s["marked"] = idx[::64].long()
+            s["pos_out"] = tuple(torch.empty_like(p) for p in pos)
+    elif c["kind"] == "batched":
+        plan = dks.PoissonPlan(_n(c), None, c["dtype"])
+        sets = [_request(c, seed, b) for b in range(c["batch"])]
+        outs = [_field_out(p[0].numel(), dt) for p in sets]
+        table = dks.particle_set_table([
+            {"x": p[0].data_ptr(), "y": p[1].data_ptr(), "z": p[2].data_ptr(), "Ex": o[0].data_ptr(),
+             "Ey": o[1].data_ptr(), "Ez": o[2].data_ptr(), "n_outside": o[3].data_ptr(), "np": p[0].numel(),
+             "q": wl.TOTAL_CHARGE / p[0].numel()} for p, o in zip(sets, outs)])
+        s.update(plan=plan, sets=sets, outs=outs, scratch=plan.batch_scratch(c["batch"], c["np"]),
+                 table=torch.frombuffer(bytearray(table), dtype=torch.uint8).to(DEV))
+    elif c["kind"] == "rho":
+        s.update(plan=dks.PoissonPlan(_n(c), _h(c), c["dtype"]), rho=_rho(c, seed))
+    elif c["kind"] in ("c2c", "r2c"):
+        plan = dks.FFTPlan(_n(c), c["batch"], c["kind"], c["dtype"])
+        s.update(plan=plan, x=_field(c, seed), spectrum=torch.empty(plan.shape(spectrum=True), dtype=plan.cdtype,
+                                                                    device=DEV))
+        if c["kind"] == "r2c":
+            s["back"] = torch.empty_like(s["x"])
+    else:
+        data, dt_us, params = _musr(c, seed)
+        s.update(fit=dks.MusrFit(data, dt_us, max_sets=c["sets"]), params=params)
+        if c["sets"] > 1:
+            s.update(params=torch.from_numpy(params).to(DEV),
+                     out=torch.empty(c["sets"], dtype=torch.float64, device=DEV))
+    return s
+
+
+def run(state):
+    c = state["case"]
+    kind = c["kind"]
+    if kind == "step":
+        (ex, ey, ez), _, cnt = state["plan"].solve_particles(*state["pos"], _q(c), out=state["out"])
+        return {"E": (ex, ey, ez), "outside": cnt}
+    if kind == "sorted":
+        pos, E, phi, cnt, idx = state["plan"].solve_particles_sorted(
+            *state["pos"], _q(c), want_phi=True, want_index=True, pos_out=state["pos_out"], out=state["out"])
+        # the program reads off the potential and, through the permutation,
+        # its marked particles (the order inside a tile is any)
+        at = idx[state["marked"]]
+        return {"phi": phi, "outside": cnt, "marked": [a[at] for a in (*pos, *E)]}
+    if kind == "batched":
+        state["plan"].solve_particles_batched(state["table"], c["batch"], c["np"], state["scratch"])
+        return [{"E": o[:3], "outside": o[3]} for o in state["outs"]]
+    if kind == "rho":
+        phi, E = state["plan"].solve_rho(state["rho"])
+        return {"phi": phi, "E": E}
+    if kind == "c2c":
+        return state["plan"].forward(state["x"], out=state["spectrum"])
+    if kind == "r2c":
+        X = state["plan"].forward(state["x"], out=state["spectrum"])
+        return {"spectrum": X, "back": state["plan"].inverse(X, out=state["back"])}
+    if c["sets"] == 1:
+        return state["fit"].eval_async(c["stat"], state["params"][0])
+    return state["fit"].eval_batch(c["stat"], state["params"], out=state["out"])
+
+
+# --------------------------------------------------------------------------
+# what a call cannot do without
+# --------------------------------------------------------------------------
+
+def _conv_work(c):
+    """Green's spectrum octant read once; the transforms of the doubled grid
+    without those of rows that are zero or not kept, and the products."""
+    nx, ny, nz = _n(c)
+    s = NP[c["dtype"]]().itemsize
+
+    def fft(n):
+        return 5.0 * n * math.log2(n)
+
+    flops = 2 * (ny * nz * fft(2 * nx) / 2 + (nx + 1) * nz * fft(2 * ny) + (nx + 1) * 2 * ny * fft(2 * nz))
+    return s * (nx + 1) * (ny + 1) * (nz + 1), flops + 2 * (nx + 1) * 4 * ny * nz
+
+
+def work(case):
+    c = case
+    if c["kind"] in ("step", "sorted", "batched"):
+        s = NP[c["dtype"]]().itemsize
+        b, f = _conv_work(c)
+        batch = c.get("batch", 1)
+        num = c["np"] if batch == 1 else 0.65 * c["np"]       # a batch's elements hold 0.3 .. 1 of np
+        nodes = {"ngp": 1, "cic": 8, "tsc": 27}[c.get("scheme", "cic")]
+        per = 6 * s                                           # positions in, field out
+        if c["kind"] == "sorted":
+            per += 3 * s + 4                                  # positions and permutation out
+            b += s * c["nx"] * c["ny"] * c["nz"]              # potential out
+        return {"bytes": b + batch * per * num, "flops": batch * (f + num * (20 + 8 * nodes))}
+    if c["kind"] == "rho":
+        s = NP[c["dtype"]]().itemsize
+        b, f = _conv_work(c)
+        mesh = c["nx"] * c["ny"] * c["nz"]
+        return {"bytes": b + 5 * s * mesh, "flops": f + 6 * mesh}
+    if c["kind"] in ("c2c", "r2c"):
+        s = NP[c["dtype"]]().itemsize
+        N = c["batch"] * c["nx"] * c["ny"] * c["nz"]
+        flops = 5.0 * N * math.log2(c["nx"] * c["ny"] * c["nz"])
+        if c["kind"] == "c2c":
+            return {"bytes": 2 * 2 * s * N, "flops": flops}
+        H = N // c["nx"] * (c["nx"] // 2 + 1)
+        return {"bytes": 2 * (s * N + 2 * s * H), "flops": flops}      # there and back, half each
+    bins = c["n_det"] * c["n_bins"]
+    # per bin and detector: model 6, statistic 4 (and a logarithm, ~20); per
+    # bin and set two exponentials and a sine-cosine, ~60
+    per = 10 if c["stat"] == "chisq" else 30
+    return {"bytes": 8.0 * bins, "flops": float(c["sets"]) * (bins * per + c["n_bins"] * 60)}
+
+
+# --------------------------------------------------------------------------
+# the outputs in 64 bits, with plain torch
+# --------------------------------------------------------------------------
+
+def _antiderivative(x, y, z):
+    r = torch.sqrt(x * x + y * y + z * z)
+    return (y * z * torch.log(x + r) + x * z * torch.log(y + r) + x * y * torch.log(z + r)
+            - 0.5 * x * x * torch.atan(y * z / (x * r)) - 0.5 * y * y * torch.atan(x * z / (y * r))
+            - 0.5 * z * z * torch.atan(x * y / (z * r)))
+
+
+def _cell_integral(n, h):
+    """1/r integrated over the cell at each offset 0..n per axis, [z][y][x]:
+    the closed form near the origin (it loses 3 log10(D) digits at D cells),
+    a 6-point Gauss-Legendre product rule from 10 cells on."""
+    ax = [torch.arange(n[d] + 1, dtype=torch.float64, device=DEV) for d in range(3)]
+    t, w = np.polynomial.legendre.leggauss(6)
+    G = torch.zeros((n[2] + 1, n[1] + 1, n[0] + 1), dtype=torch.float64, device=DEV)
+    at = [ax[2][:, None, None], ax[1][None, :, None], ax[0][None, None, :]]
+    for i in range(6):
+        for j in range(6):
+            for k in range(6):
+                z, y, x = ((at[0] + 0.5 * t[i]) * h[2], (at[1] + 0.5 * t[j]) * h[1], (at[2] + 0.5 * t[k]) * h[0])
+                G += w[i] * w[j] * w[k] / torch.sqrt(x * x + y * y + z * z)
+    G *= h[0] * h[1] * h[2] / 8.0
+    hm = max(h)
+    m = [min(n[d], int(10 * hm / h[d])) + 1 for d in range(3)]
+    near = torch.zeros((m[2], m[1], m[0]), dtype=torch.float64, device=DEV)
+    for dz in (0, 1):
+        for dy in (0, 1):
+            for dx in (0, 1):
+                sign = -1.0 if (3 - dx - dy - dz) % 2 else 1.0
+                x, y, z = torch.broadcast_tensors((ax[0][:m[0]] - 0.5 + dx)[None, None, :] * h[0],
+                                                  (ax[1][:m[1]] - 0.5 + dy)[None, :, None] * h[1],
+                                                  (ax[2][:m[2]] - 0.5 + dz)[:, None, None] * h[2])
+                near += sign * _antiderivative(x, y, z)
+    D = torch.sqrt(sum((a * h[2 - i]) ** 2 for i, a in enumerate(at))) / hm
+    corner = G[:m[2], :m[1], :m[0]]
+    corner.copy_(torch.where(D[:m[2], :m[1], :m[0]] < 10.0, near, corner))
+    return G
+
+
+def _potential(rho, n, h):
+    """phi of rho on the mesh nodes and one ghost node per side, volts."""
+    G = _cell_integral(n, h)
+    fold = [torch.minimum(torch.arange(2 * n[d], device=DEV), 2 * n[d] - torch.arange(2 * n[d], device=DEV))
+            for d in range(3)]
+    spec = torch.fft.rfftn(G[fold[2]][:, fold[1]][:, :, fold[0]])
+    pad = torch.zeros((2 * n[2], 2 * n[1], 2 * n[0]), dtype=torch.float64, device=DEV)
+    pad[:n[2], :n[1], :n[0]] = rho
+    phi = torch.fft.irfftn(torch.fft.rfftn(pad) * spec, s=pad.shape) / (4.0 * math.pi * EPS0)
+    i = [torch.arange(-1, n[d] + 1, device=DEV) % (2 * n[d]) for d in range(3)]
+    return phi[i[2]][:, i[1]][:, :, i[0]]
+
+
+def _gradient(phi, h):
+    return [-(phi[1:-1, 1:-1, 2:] - phi[1:-1, 1:-1, :-2]) / (2 * h[0]),
+            -(phi[1:-1, 2:, 1:-1] - phi[1:-1, :-2, 1:-1]) / (2 * h[1]),
+            -(phi[2:, 1:-1, 1:-1] - phi[:-2, 1:-1, 1:-1]) / (2 * h[2])]
+
+
+def _fit(pos, n):
+    lo = [float(p.min()) for p in pos]
+    hi = [float(p.max()) for p in pos]
+    h = max((hi[d] - lo[d]) / (n[d] - 3) for d in range(3))
+    h = h if h > 0.0 else 1.0
+    return (h, h, h), [0.5 * (lo[d] + hi[d]) - 0.5 * (n[d] - 1) * h for d in range(3)]
+
+
+def _stencil(p, x0, h, n, scheme, dtype):
+    """(inside, first node, weights) of one axis.  Whether a particle is
+    inside and which node it is filed under follow the cell coordinate in the
+    call's type; the weights are those of the 64-bit coordinate."""
+    s = (p - NP[dtype](x0)) * NP[dtype](1.0 / h)
+    e = (p.double() - x0) / h
+    ok = (s >= 0) & (s <= n - 1)
+    if scheme == "cic":
+        k = torch.clamp(torch.floor(s), 0, n - 2)
+        f = e - k
+        return ok, k.long(), [1.0 - f, f]
+    k = torch.floor(s + 0.5)
+    if scheme == "ngp":
+        return ok, torch.clamp(k, 0, n - 1).long(), [torch.ones_like(e)]
+    d = e - k
+    ok = ok & (k >= 1) & (k <= n - 2)
+    return ok, torch.clamp(k, 1, n - 2).long() - 1, [0.5 * (0.5 - d) ** 2, 0.75 - d * d, 0.5 * (0.5 + d) ** 2]
+
+
+def _particles(pos, q, n, h, scheme, dtype):
+    """(phi with ghosts, [Ex, Ey, Ez], number outside)."""
+    if h is None:
+        h, x0 = _fit(pos, n)
+    else:
+        x0 = [-0.5 * (n[d] - 1) * h[d] for d in range(3)]
+    W = torch.zeros(n[2] * n[1] * n[0], dtype=torch.float64, device=DEV)
+    num, part = pos[0].numel(), 10_000_000
+    outside = 0
+
+    def nodes(a, b):
+        ax = [_stencil(pos[d][a:b], x0[d], h[d], n[d], scheme, dtype) for d in range(3)]
+        ok = ax[0][0] & ax[1][0] & ax[2][0]
+        for kz, wz in enumerate(ax[2][2]):
+            for ky, wy in enumerate(ax[1][2]):
+                for kx, wx in enumerate(ax[0][2]):
+                    at = ((ax[2][1] + kz) * n[1] + ax[1][1] + ky) * n[0] + ax[0][1] + kx
+                    yield ok, at, wz * wy * wx * ok
+
+    for a in range(0, num, part):
+        for ok, at, w in nodes(a, min(a + part, num)):
+            W.index_add_(0, at, w)
+        outside += int((~ok).sum())
+    phi = _potential((W * (q / (h[0] * h[1] * h[2]))).reshape(n[2], n[1], n[0]), n, h)
+    mesh = [e.reshape(-1) for e in _gradient(phi, h)]
+    E = [torch.zeros(num, dtype=torch.float64, device=DEV) for _ in range(3)]
+    for a in range(0, num, part):
+        for _, at, w in nodes(a, min(a + part, num)):
+            for d in range(3):
+                E[d][a:a + part] += w * mesh[d][at]
+    return phi, E, outside
+
+
+def exact(case, seed):
+    c = case
+    if c["kind"] in ("step", "sorted"):
+        pos = _bunch(c["bunch"], c["np"], seed, c["dtype"])
+        phi, E, out = _particles(pos, _q(c), _n(c), _h(c), c["scheme"], c["dtype"])
+        out = torch.tensor([out])
+        if c["kind"] == "step":
+            return {"E": tuple(E), "outside": out}
+        return {"phi": phi[1:-1, 1:-1, 1:-1], "outside": out, "marked": [a[::64].double() for a in (*pos, *E)]}
+    if c["kind"] == "batched":
+        got = []
+        for b in range(c["batch"]):
+            pos = _request(c, seed, b)
+            _, E, out = _particles(pos, wl.TOTAL_CHARGE / pos[0].numel(), _n(c), None, "cic", c["dtype"])
+            got.append({"E": tuple(E), "outside": torch.tensor([out])})
+        return got
+    if c["kind"] == "rho":
+        phi = _potential(_rho(c, seed).double(), _n(c), _h(c))
+        return {"phi": phi[1:-1, 1:-1, 1:-1], "E": torch.stack(_gradient(phi, _h(c)))}
+    if c["kind"] == "c2c":
+        return torch.fft.fftn(_field(c, seed).to(torch.complex128), dim=(1, 2, 3))
+    if c["kind"] == "r2c":
+        x = _field(c, seed).double()
+        return {"spectrum": torch.fft.rfftn(x, dim=(1, 2, 3)), "back": x * float(c["nx"] * c["ny"] * c["nz"])}
+    data, dt, params = _musr(c, seed)
+    got = []
+    for p in params:
+        N = _musr_model(torch.from_numpy(p).to(DEV), c["n_det"], c["n_bins"], dt)
+        if c["stat"] == "chisq":
+            term = (data - N) ** 2 / torch.where(data > 0, data, torch.ones_like(data))
+        else:
+            term = 2.0 * (N - data + torch.where(data > 0, data * torch.log(data.clamp_min(1.0) / N),
+                                                 torch.zeros_like(data)))
+        got.append(term.sum())
+    return torch.stack(got)
