@@ -239,10 +239,10 @@ def prepare(case, seed):
         plan.reserve_particles(c["np"])
         s.update(plan=plan, pos=pos, out=_field_out(c["np"], dt))
         if c["kind"] == "sorted":
-            # the previous step leaves the particles in its order; every 64th
+            # the previous step leaves the particles in its order; every 256th
             # particle is marked
             s["pos"], _, _, _, idx = plan.solve_particles_sorted(*pos, _q(c), want_index=True)
-            s["marked"] = idx[::64].long()
+            s["marked"] = idx[::256].long()
             s["pos_out"] = tuple(torch.empty_like(p) for p in pos)
     elif c["kind"] == "batched":
         plan = dks.PoissonPlan(_n(c), None, c["dtype"])
@@ -479,7 +479,7 @@ def exact(case, seed):
         out = torch.tensor([out])
         if c["kind"] == "step":
             return {"E": tuple(E), "outside": out}
-        return {"phi": phi[1:-1, 1:-1, 1:-1], "outside": out, "marked": [a[::64].double() for a in (*pos, *E)]}
+        return {"phi": phi[1:-1, 1:-1, 1:-1], "outside": out, "marked": [a[::256].double() for a in (*pos, *E)]}
     if c["kind"] == "batched":
         got = []
         for b in range(c["batch"]):
