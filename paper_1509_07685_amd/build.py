@@ -17,7 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libdks_poisson.so")
-SOURCES = ["fft_kernels.hip", "fft_raw.hip", "particle_kernels.hip", "bin_kernels.hip", "greens_kernels.hip",
+SOURCES = ["fft_kernels_z64.hip", "fft_kernels_z32.hip", "fft_kernels_y.hip", "fft_kernels.hip", "fft_raw.hip", "particle_kernels.hip", "bin_kernels.hip", "greens_kernels.hip",
            "plan.hip", "musr_kernels.hip"]
 ARCH = "gfx950"
 
@@ -43,7 +43,7 @@ def hipcc():
 
 # Per-source extra flags.  The FFT passes do not depend on the sign of zero,
 # which lets the compiler drop additions of the zero padding.
-EXTRA = {"fft_kernels.hip": ["-fno-signed-zeros"]}
+EXTRA = {f"fft_kernels{s}.hip": ["-fno-signed-zeros"] for s in ("", "_y", "_z32", "_z64")}
 
 
 def _compile(src):

@@ -85,6 +85,12 @@ struct MeshDims {
   int ncols;          // nx + 1 complex columns
 };
 
+// Every element offset the y and z passes form inside one batch element's
+// intermediate arrays stays below (nz + 2) * Ny * cs (the size of C).
+static inline bool offsets_fit32(const MeshDims& m) {
+  return (double)(m.nz + 2) * (double)m.Ny * (double)m.cs < 2147483648.0;
+}
+
 constexpr int kMaxBatch = 16;
 static_assert(sizeof(dks_particle_set) == 80, "dks_particle_set layout is part of the ABI");
 

@@ -1,8 +1,8 @@
 // Mixed-radix Stockham FFT engine shared by the convolution passes and the
-// raw transform entry points: complex helpers, radix-2/3/4/8 butterflies, one
+// raw transform entry points: complex helpers, radix 2 to 16 butterflies, one
 // pass over an LDS tile of W pencils ([element][pencil], pencil fastest), the
-// pass loop with runtime plans, and compile-time plans for power-of-two
-// lengths.  A transform of P passes reads its first pass from any source and
+// pass loop with runtime plans (radices 2, 3, 4 and 8), and compile-time plans
+// for the lengths of common meshes.  A transform of P passes reads its first pass from any source and
 // hands its last pass to any sink, with P - 1 LDS round trips between.
 #ifndef DKS_FFT_ENGINE_H
 #define DKS_FFT_ENGINE_H
@@ -103,11 +103,112 @@ template <bool INV, typename C> __device__ __forceinline__ void dft3(C* v) {
   v[2] = csub(m, si);
 }
 
+// Radix 6 = 2 x 3 and 12 = 4 x 3 by the prime-factor map (coprime factors: no
+// twiddles between them): input n = (3 n1 + 2 n2) mod 6, output k = (3 k1 +
+// 4 k2) mod 6; n = (3 n1 + 4 n2) mod 12, k = (9 k1 + 4 k2) mod 12.
+template <bool INV, typename C> __device__ __forceinline__ void dft6(C* v) {
+  C a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
+  dft3<INV>(a);
+  dft3<INV>(b);
+#pragma unroll
+  for (int k2 = 0; k2 < 3; ++k2) {
+    v[(4 * k2) % 6] = cadd(a[k2], b[k2]);
+    v[(3 + 4 * k2) % 6] = csub(a[k2], b[k2]);
+  }
+}
+
+template <bool INV, typename C> __device__ __forceinline__ void dft12(C* v) {
+  C q[3][4];
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 4; ++n1) q[n2][n1] = v[(3 * n1 + 4 * n2) % 12];
+    dft4<INV>(q[n2]);
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) {
+    C t[3] = {q[0][k1], q[1][k1], q[2][k1]};
+    dft3<INV>(t);
+#pragma unroll
+    for (int k2 = 0; k2 < 3; ++k2) v[(9 * k1 + 4 * k2) % 12] = t[k2];
+  }
+}
+
+// Radix 9 = 3 x 3 and 16 = 4 x 4: input n = F n1 + n2, output k = k1 + F k2,
+// the twiddle w^(n2 k1) between the two stages (F = 3, 4).
+template <bool INV, typename C> __device__ __forceinline__ C tw_const(C a, double c, double s) {
+  using T = decltype(C::x);
+  return cmul(a, C{(T)c, (T)(INV ? -s : s)});
+}
+
+template <bool INV, typename C> __device__ __forceinline__ void dft9(C* v) {
+  // cos and sin of -2 pi m / 9, m = 1, 2, 4
+  constexpr double c1 = 0.76604444311897803520, s1 = -0.64278760968653932632;
+  constexpr double c2 = 0.17364817766693034885, s2 = -0.98480775301220805937;
+  constexpr double c4 = -0.93969262078590838405, s4 = -0.34202014332566873304;
+  C q[3][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 3; ++n1) q[n2][n1] = v[3 * n1 + n2];
+    dft3<INV>(q[n2]);
+  }
+  q[1][1] = tw_const<INV>(q[1][1], c1, s1);
+  q[1][2] = tw_const<INV>(q[1][2], c2, s2);
+  q[2][1] = tw_const<INV>(q[2][1], c2, s2);
+  q[2][2] = tw_const<INV>(q[2][2], c4, s4);
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    C t[3] = {q[0][k1], q[1][k1], q[2][k1]};
+    dft3<INV>(t);
+#pragma unroll
+    for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = t[k2];
+  }
+}
+
+template <bool INV, typename C> __device__ __forceinline__ void dft16(C* v) {
+  using T = decltype(C::x);
+  // cos and sin of -2 pi m / 16, m = 1, 3 (m = 2: +-1/sqrt 2; m = 9: minus m = 1)
+  constexpr double c1 = 0.92387953251128675613, s1 = -0.38268343236508977173;
+  constexpr double c3 = 0.38268343236508977173, s3 = -0.92387953251128675613;
+  const T h = (T)0.70710678118654752440;
+  C q[4][4];
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 4; ++n1) q[n2][n1] = v[4 * n1 + n2];
+    dft4<INV>(q[n2]);
+  }
+  // times w^2 = (1 - i) / sqrt 2 and w^6 = -(1 + i) / sqrt 2 (forward)
+  auto w2 = [&](C a) { return INV ? C{h * (a.x - a.y), h * (a.x + a.y)} : C{h * (a.x + a.y), h * (a.y - a.x)}; };
+  auto w6 = [&](C a) { return INV ? C{-h * (a.x + a.y), h * (a.x - a.y)} : C{h * (a.y - a.x), -h * (a.x + a.y)}; };
+  q[1][1] = tw_const<INV>(q[1][1], c1, s1);
+  q[1][2] = w2(q[1][2]);
+  q[1][3] = tw_const<INV>(q[1][3], c3, s3);
+  q[2][1] = w2(q[2][1]);
+  q[2][2] = mul_mi<INV>(q[2][2]);
+  q[2][3] = w6(q[2][3]);
+  q[3][1] = tw_const<INV>(q[3][1], c3, s3);
+  q[3][2] = w6(q[3][2]);
+  q[3][3] = tw_const<INV>(q[3][3], -c1, -s1);
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) {
+    C t[4] = {q[0][k1], q[1][k1], q[2][k1], q[3][k1]};
+    dft4<INV>(t);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = t[k2];
+  }
+}
+
 template <int R, bool INV, typename C> __device__ __forceinline__ void dft(C* v) {
   if constexpr (R == 2) dft2<INV>(v);
   else if constexpr (R == 3) dft3<INV>(v);
   else if constexpr (R == 4) dft4<INV>(v);
-  else dft8<INV>(v);
+  else if constexpr (R == 6) dft6<INV>(v);
+  else if constexpr (R == 8) dft8<INV>(v);
+  else if constexpr (R == 9) dft9<INV>(v);
+  else if constexpr (R == 12) dft12<INV>(v);
+  else dft16<INV>(v);
 }
 
 template <class F> __device__ __forceinline__ void radix_dispatch(int R, F&& f) {
@@ -214,34 +315,109 @@ __device__ __forceinline__ void run_fft(typename Cplx<T>::type* lds, const FFTPl
 }
 
 // ---------------------------------------------------------------------------
-// Compile-time plans.  For the power-of-two lengths of common meshes the
-// kernels are also instantiated with the whole plan known at compile time
-// (length, tile width, LDS stride, radix order), so butterfly indexing,
-// twiddle offsets and guards fold to constants; the runtime plan above
-// serves every other shape.  A launcher uses a compile-time plan only when
-// the host plan matches it exactly.
+// Compile-time plans.  For the lengths of static_radices (every 2^a 3^b from
+// 16 to 512) the kernels are instantiated with the whole plan known at
+// compile time (length, tile width, LDS stride, radix order, lanes), so
+// butterfly indexing, twiddle offsets and guards fold to constants; the
+// runtime plan above serves every other shape.  A launcher uses a
+// compile-time plan only when the host plan matches it exactly.
 // ---------------------------------------------------------------------------
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
+constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
 struct DynPlan {
   static constexpr bool is_static = false;
 };
 
-// Power-of-two length N: radix-8 passes, then one radix-4 or radix-2 pass
-// (the host's order); REV reverses the order (the inverse z transform).
-template <int N_, int W_, int LD_, bool REV_>
+// Radix order of a length with a compile-time plan (n = 0: none, the length
+// runs on the runtime plan).  At most three passes, the two or three radices
+// near equal so that every pass keeps about the same lanes busy; the first
+// radix of an even length is even (a zero-padded forward transform then skips
+// its whole upper half), the last one too where the factors allow it.
+// Against the runtime plan, whose time went to index arithmetic, guards and
+// passes of radix 3 (the five passes of a solve): 96 x 96 x 192
+// FP64 180 -> 91 us, 8 x 48^3 FP32 in one batch 115 -> 36 us, 144 x 128 x 96
+// FP32 106 -> 56 us; raw 216 x 144 x 96 x 4 FP64, there and back, 410 -> 288 us.
+struct RadixList {
+  int n;
+  int r[3];
+};
+constexpr RadixList static_radices(int N) {
+  switch (N) {
+    case 16: return {2, {4, 4, 1}};
+    case 18: return {2, {6, 3, 1}};
+    case 24: return {2, {6, 4, 1}};
+    case 27: return {2, {9, 3, 1}};
+    case 32: return {2, {8, 4, 1}};
+    case 36: return {2, {6, 6, 1}};
+    case 48: return {2, {8, 6, 1}};
+    case 54: return {2, {6, 9, 1}};
+    case 64: return {2, {8, 8, 1}};
+    case 72: return {2, {12, 6, 1}};
+    case 81: return {2, {9, 9, 1}};
+    case 96: return {2, {8, 12, 1}};
+    case 108: return {2, {12, 9, 1}};
+    case 128: return {2, {16, 8, 1}};
+    case 144: return {2, {12, 12, 1}};
+    case 162: return {3, {6, 3, 9}};
+    case 192: return {2, {16, 12, 1}};
+    case 216: return {3, {6, 6, 6}};
+    case 243: return {3, {9, 9, 3}};
+    case 256: return {3, {8, 8, 4}};
+    case 288: return {3, {8, 6, 6}};
+    case 324: return {3, {6, 9, 6}};
+    case 384: return {3, {8, 6, 8}};
+    case 432: return {3, {6, 9, 8}};
+    case 486: return {3, {6, 9, 9}};
+    case 512: return {3, {8, 8, 8}};
+    default: return {0, {1, 1, 1}};
+  }
+}
+
+// Lengths with compile-time kernels in the convolution: x rows (pairs of
+// reals: even lengths) up to 256, y and z pencils (doubled extents) from 32,
+// where the intermediates' element offsets fit 32 bits.
+constexpr bool static_row(int N) { return N % 2 == 0 && N <= 256 && static_radices(N).n > 0; }
+constexpr bool static_pencil(int N) { return N % 2 == 0 && N >= 32 && static_radices(N).n > 0; }
+
+// The lengths above, for switches over them.
+#define DKS_STATIC_LENGTHS(F) \
+  F(16) F(18) F(24) F(27) F(32) F(36) F(48) F(54) F(64) F(72) F(81) F(96) F(108) F(128) F(144) F(162) F(192) F(216) \
+  F(243) F(256) F(288) F(324) F(384) F(432) F(486) F(512)
+
+// Compile-time plan of length N (radix order static_radices, REV reversed:
+// the inverse z transform), W pencils per tile with LDS stride LD, at most
+// CAP lanes per workgroup.  TH lanes run the tile: the widest pass's
+// butterflies in the fewest rounds that CAP allows, so a short transform does
+// not carry idle wavefronts through its barriers.
+template <int N_, int W_, int LD_, bool REV_, int CAP_>
 struct SPlan {
   static constexpr bool is_static = true;
   static constexpr int N = N_, W = W_, LD = LD_, logW = ilog2(W_);
-  static constexpr int n8 = ilog2(N_) / 3, rem = ilog2(N_) % 3;
-  static constexpr int npass = n8 + (rem ? 1 : 0);
-  static constexpr int Rf(int p) { return p < n8 ? 8 : (rem == 2 ? 4 : 2); }
-  static constexpr int R(int p) { return REV_ ? Rf(npass - 1 - p) : Rf(p); }
+  static constexpr RadixList list = static_radices(N_);
+  static_assert(list.n > 0 && list.r[0] * list.r[1] * list.r[2] == N_, "radices of a compile-time plan");
+  static constexpr int npass = list.n;
+  static constexpr int R(int p) { return REV_ ? list.r[npass - 1 - p] : list.r[p]; }
   static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * R(p - 1); }
   static constexpr int tw_off(int p) { return p <= 1 ? 0 : tw_off(p - 1) + Ns(p - 1) * (R(p - 1) - 1); }
-  using Reversed = SPlan<N_, W_, LD_, !REV_>;
+  static constexpr int widest() {
+    int m = 0;
+    for (int p = 0; p < npass; ++p) m = N / R(p) > m ? N / R(p) : m;
+    return m * W;
+  }
+  static constexpr int rounds = (widest() + CAP_ - 1) / CAP_;
+  static constexpr int TH = ((widest() + rounds - 1) / rounds + 63) / 64 * 64;
+  // the first radix is even, so the first pass's upper half inputs are r >= R/2
+  static constexpr bool even_first = R(0) % 2 == 0;
+  using Reversed = SPlan<N_, W_, LD_, !REV_, CAP_>;
 };
+
+// Lanes per workgroup of a pass kernel.
+template <typename T, class SP> constexpr int block_threads() {
+  if constexpr (SP::is_static) return SP::TH;
+  else return RegCfg<T>::THREADS;
+}
 
 // The inverse z plan of a forward plan: radices reversed.
 template <class SP> struct InvPlan { using type = typename SP::Reversed; };
@@ -280,9 +456,10 @@ template <typename T, bool INV, class SP, int p, bool SYNC, bool ZU, class TwP, 
 __device__ __forceinline__ void fft_pass_s(TwP twb, In in, Out out, Pre pre) {
   using C = typename Cplx<T>::type;
   constexpr int R = SP::R(p), Ns = SP::Ns(p), NR = SP::N / R, W = SP::W, logW = SP::logW;
-  constexpr int TH = RegCfg<T>::THREADS, nbf = W * NR;
-  constexpr int K = cmin((RegCfg<T>::EMAX + R - 1) / R, (nbf + TH - 1) / TH);
+  constexpr int TH = SP::TH, nbf = W * NR;
+  constexpr int K = (nbf + TH - 1) / TH;
   constexpr bool guard = K * TH > nbf;
+  static_assert(!ZU || R % 2 == 0, "a zero-padded transform starts with an even radix");
   const TwP tw = twb + SP::tw_off(p);
   C v[K * R];
   C w[K * (R - 1)];
@@ -296,7 +473,7 @@ __device__ __forceinline__ void fft_pass_s(TwP twb, In in, Out out, Pre pre) {
         v[k * R + r] = (ZU && 2 * r >= R) ? C{0, 0} : in(c, j + r * NR, ZU ? k * (R / 2) + r : k * R + r);
       pre(std::integral_constant<int, R>{}, k, c, j);
       if constexpr (Ns > 1) {
-        const TwP wt = tw + (j & (Ns - 1)) * (R - 1);
+        const TwP wt = tw + (int)((unsigned)j % (unsigned)Ns) * (R - 1);
 #pragma unroll
         for (int r = 1; r < R; ++r) w[k * (R - 1) + r - 1] = C{wt[r - 1].x, wt[r - 1].y};
       }
@@ -310,7 +487,7 @@ __device__ __forceinline__ void fft_pass_s(TwP twb, In in, Out out, Pre pre) {
       const int c = b & (W - 1), j = b >> logW;
       int base;
       if constexpr (Ns > 1) {
-        const int t = j & (Ns - 1);
+        const int t = (int)((unsigned)j % (unsigned)Ns);
 #pragma unroll
         for (int r = 1; r < R; ++r) {
           C wr = w[k * (R - 1) + r - 1];

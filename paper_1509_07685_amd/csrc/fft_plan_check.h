@@ -5,7 +5,7 @@
 //
 //   V1  structure: 1 <= N <= max_length; npass <= max_pass, and npass = 0
 //       only for N = 1 (a copy through the tile); every radix
-//       is 2, 3, 4 or 8 and their product is N; Ns[0] = 1 and
+//       is 2, 3, 4, 6, 8, 9, 12 or 16 and their product is N; Ns[0] = 1 and
 //       Ns[p + 1] = Ns[p] R[p]; twiddle offsets tw_off[0] = tw_off[1] = 0 and
 //       tw_off[p + 1] = tw_off[p] + Ns[p] (R[p] - 1)
 //   V2  tile shape: W is a power of two, logW = log2 W, LD is W or W + 1
@@ -65,7 +65,7 @@ inline int fft_plan_violation(const Plan& P, const EngineLimits& L, size_t csize
   int tw = 0;
   for (int p = 0; p < P.npass; ++p) {
     const int R = P.R[p];
-    if (R != 2 && R != 3 && R != 4 && R != 8) return kPlanStructure;
+    if (R != 2 && R != 3 && R != 4 && R != 6 && R != 8 && R != 9 && R != 12 && R != 16) return kPlanStructure;
     if (P.Ns[p] != prod) return kPlanStructure;
     if (P.tw_off[p] != tw) return kPlanStructure;
     if (p > 0) tw += P.Ns[p] * (R - 1);

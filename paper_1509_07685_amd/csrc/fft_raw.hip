@@ -39,20 +39,37 @@ enum RowKind { kRowC2C = 0, kRowR2C = 1, kRowC2R = 2 };
 // complex in, completed to the full Hermitian row X[N - k] = conj X[k], the
 // real parts of the inverse transform out.
 // ---------------------------------------------------------------------------
+// Values of its tile a lane stages; the length of a compile-time plan.
+template <typename T, class SP> constexpr int row_regs() {
+  if constexpr (SP::is_static) return (SP::N * SP::W + SP::TH - 1) / SP::TH;
+  else return RegCfg<T>::EMAX;
+}
+template <class SP> constexpr int static_n() {
+  if constexpr (SP::is_static) return SP::N;
+  else return 1;
+}
 template <typename T, class SP, bool INV, int KIND>
-__global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __restrict__ in,
+__global__ __launch_bounds__((block_threads<T, SP>())) void k_fftr_rows(const void* __restrict__ in,
                                                                  void* __restrict__ out, long long nrows,
                                                                  const FFTPlan* __restrict__ P, int in_len,
                                                                  int out_len, unsigned magic_in,
                                                                  unsigned magic_out) {
   using C = typename Cplx<T>::type;
-  constexpr int TH = RegCfg<T>::THREADS;
-  constexpr int KL = RegCfg<T>::EMAX;
+  constexpr int TH = block_threads<T, SP>();
+  constexpr int KL = row_regs<T, SP>();
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   const int W = plan_W<SP>(P), LD = plan_LD<SP>(P), N = plan_N<SP>(P);
   const long long row0 = (long long)blockIdx.x * W;
   const int nvalid = (int)min((long long)W, nrows - row0);
+  // element e of the tile's rows of `len` values -> its row
+  auto row_of = [](int e, int len, unsigned magic, auto clen) {
+    if constexpr (SP::is_static) return (int)((unsigned)e / (unsigned)decltype(clen)::value);
+    else return len == 1 ? e : (int)__umulhi((unsigned)e, magic);
+  };
+  constexpr int NS = static_n<SP>();
+  using InLen = std::integral_constant<int, KIND == kRowC2R ? NS / 2 + 1 : NS>;
+  using OutLen = std::integral_constant<int, KIND == kRowR2C ? NS / 2 + 1 : NS>;
   {
     const int total = nvalid * in_len;
     if constexpr (KIND == kRowR2C) {
@@ -67,7 +84,7 @@ __global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __
       for (int k = 0; k < KL; ++k) {
         const int e = (int)threadIdx.x + k * TH;
         if (e < total) {
-          const int p = in_len == 1 ? e : (int)__umulhi((unsigned)e, magic_in);
+          const int p = row_of(e, in_len, magic_in, InLen{});
           const int x = e - p * in_len;
           lds[x * LD + p] = C{v[k], (T)0};
         }
@@ -84,7 +101,7 @@ __global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __
       for (int k = 0; k < KL; ++k) {
         const int e = (int)threadIdx.x + k * TH;
         if (e < total) {
-          const int p = in_len == 1 ? e : (int)__umulhi((unsigned)e, magic_in);
+          const int p = row_of(e, in_len, magic_in, InLen{});
           const int x = e - p * in_len;
           lds[x * LD + p] = v[k];
           if constexpr (KIND == kRowC2R) {
@@ -109,7 +126,7 @@ __global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __
     T* dst = static_cast<T*>(out) + row0 * out_len;
 #pragma unroll 4
     for (int e = (int)threadIdx.x; e < total; e += TH) {
-      const int p = out_len == 1 ? e : (int)__umulhi((unsigned)e, magic_out);
+      const int p = row_of(e, out_len, magic_out, OutLen{});
       const int x = e - p * out_len;
       dst[e] = lds[x * LD + p].x;
     }
@@ -117,7 +134,7 @@ __global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __
     C* dst = static_cast<C*>(out) + row0 * out_len;
 #pragma unroll 4
     for (int e = (int)threadIdx.x; e < total; e += TH) {
-      const int p = out_len == 1 ? e : (int)__umulhi((unsigned)e, magic_out);
+      const int p = row_of(e, out_len, magic_out, OutLen{});
       const int x = e - p * out_len;
       dst[e] = lds[x * LD + p];
     }
@@ -130,7 +147,7 @@ __global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_rows(const void* __
 // element is (o / d1) s1 + (o mod d1) s2.
 // ---------------------------------------------------------------------------
 template <typename T, class SP, bool INV>
-__global__ __launch_bounds__(RegCfg<T>::THREADS) void k_fftr_cols(const typename Cplx<T>::type* in,
+__global__ __launch_bounds__((block_threads<T, SP>())) void k_fftr_cols(const typename Cplx<T>::type* in,
                                                                  typename Cplx<T>::type* out, int ncols,
                                                                  int ntile, size_t S, int d1, size_t s1,
                                                                  size_t s2, const FFTPlan* __restrict__ P) {
@@ -164,24 +181,39 @@ constexpr int row_width(int N, int c, int w) { return (w > 1 && N * (w + 1) * c 
 
 template <typename T, int N> using RowPlan =
     SPlan<N, row_width(N, 2 * (int)sizeof(T), 128 / (2 * (int)sizeof(T))),
-          row_width(N, 2 * (int)sizeof(T), 128 / (2 * (int)sizeof(T))) + 1, false>;
-template <typename T, int N> using ColPlan = SPlan<N, 128 / (2 * (int)sizeof(T)), 128 / (2 * (int)sizeof(T)), false>;
+          row_width(N, 2 * (int)sizeof(T), 128 / (2 * (int)sizeof(T))) + 1, false, RegCfg<T>::THREADS>;
+template <typename T, int N> using ColPlan =
+    SPlan<N, 128 / (2 * (int)sizeof(T)), 128 / (2 * (int)sizeof(T)), false, RegCfg<T>::THREADS>;
 
+// Calls f with the compile-time plan equal to host plan h, or with DynPlan.
+// Plan creation gives a length the radices of static_radices exactly where
+// the compile-time kernels run it: every row, and columns whose array is
+// addressable with 32-bit element offsets.
+template <class SP, class F> static bool try_plan(const FFTPlan& h, F&& f) {
+  if (!plan_matches<SP>(h)) return false;
+  f(SP{});
+  return true;
+}
 template <typename T, class F> static void with_row_plan(const FFTPlan& h, F&& f) {
-  if (plan_matches<RowPlan<T, 512>>(h)) f(RowPlan<T, 512>{});
-  else if (plan_matches<RowPlan<T, 256>>(h)) f(RowPlan<T, 256>{});
-  else if (plan_matches<RowPlan<T, 128>>(h)) f(RowPlan<T, 128>{});
-  else if (plan_matches<RowPlan<T, 64>>(h)) f(RowPlan<T, 64>{});
-  else f(DynPlan{});
+  bool done = false;
+  switch (h.N) {
+#define DKS_TRY(N) case N: done = try_plan<RowPlan<T, N>>(h, f); break;
+    DKS_STATIC_LENGTHS(DKS_TRY)
+#undef DKS_TRY
+    default: break;
+  }
+  if (!done) f(DynPlan{});
 }
 
 template <typename T, class F> static void with_col_plan(const FFTPlan& h, F&& f, bool off32) {
-  if (!off32) f(DynPlan{});
-  else if (plan_matches<ColPlan<T, 512>>(h)) f(ColPlan<T, 512>{});
-  else if (plan_matches<ColPlan<T, 256>>(h)) f(ColPlan<T, 256>{});
-  else if (plan_matches<ColPlan<T, 128>>(h)) f(ColPlan<T, 128>{});
-  else if (plan_matches<ColPlan<T, 64>>(h)) f(ColPlan<T, 64>{});
-  else f(DynPlan{});
+  bool done = false;
+  if (off32) switch (h.N) {
+#define DKS_TRY(N) case N: done = try_plan<ColPlan<T, N>>(h, f); break;
+    DKS_STATIC_LENGTHS(DKS_TRY)
+#undef DKS_TRY
+    default: break;
+  }
+  if (!done) f(DynPlan{});
 }
 
 template <typename T, bool INV, int KIND>
@@ -190,12 +222,14 @@ static hipError_t launch_rows(const void* in, void* out, long long nrows, const 
   const long long nblk = (nrows + P.host.W - 1) / P.host.W;
   if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
   with_row_plan<T>(P.host, [&](auto sp) {
-    hipLaunchKernelGGL((k_fftr_rows<T, decltype(sp), INV, KIND>), dim3((unsigned)nblk), dim3(RegCfg<T>::THREADS),
-                       lds_bytes<T>(P.host), s, in, out, nrows, P.dev, in_len, out_len, magic_of(in_len),
+    hipLaunchKernelGGL((k_fftr_rows<T, decltype(sp), INV, KIND>), dim3((unsigned)nblk),
+                       dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s, in, out, nrows, P.dev, in_len, out_len, magic_of(in_len),
                        magic_of(out_len));
   });
   return hipGetLastError();
 }
+
+static inline bool cols_fit32(size_t elems) { return elems < 0x7fffffffULL; }
 
 template <typename T, bool INV>
 static hipError_t launch_cols(const void* in, void* out, int ncols, size_t S, int nouter, int d1, size_t s1,
@@ -205,10 +239,10 @@ static hipError_t launch_cols(const void* in, void* out, int ncols, size_t S, in
   const long long nblk = (long long)ntile * nouter;
   if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
   // 32-bit offsets inside a pencil tile when the whole array is addressable with them
-  const bool off32 = elems < 0x7fffffffULL;
+  const bool off32 = cols_fit32(elems);
   with_col_plan<T>(P.host, [&](auto sp) {
-    hipLaunchKernelGGL((k_fftr_cols<T, decltype(sp), INV>), dim3((unsigned)nblk), dim3(RegCfg<T>::THREADS),
-                       lds_bytes<T>(P.host), s, (const C*)in, (C*)out, ncols, ntile, S, d1, s1, s2, P.dev);
+    hipLaunchKernelGGL((k_fftr_cols<T, decltype(sp), INV>), dim3((unsigned)nblk),
+                       dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s, (const C*)in, (C*)out, ncols, ntile, S, d1, s1, s2, P.dev);
   }, off32);
   return hipGetLastError();
 }
@@ -244,7 +278,9 @@ bool is_23(int N) {
   return N == 1;
 }
 
-std::vector<int> radix_order(int N) {
+std::vector<int> radix_order(int N, bool fixed) {
+  const RadixList l = static_radices(N);
+  if (fixed && l.n > 0) return std::vector<int>(l.r, l.r + l.n);
   int a = 0, b = 0;
   while (N % 2 == 0) { N /= 2; ++a; }
   while (N % 3 == 0) { N /= 3; ++b; }
@@ -256,9 +292,10 @@ std::vector<int> radix_order(int N) {
   return r;
 }
 
-void make_axis(FFTPlanHost& P, int N, int W, int LD) {
+// fixed: the compile-time kernels run this axis where they know its length.
+void make_axis(FFTPlanHost& P, int N, int W, int LD, bool fixed) {
   std::memset(&P, 0, sizeof(P));
-  const std::vector<int> R = radix_order(N);
+  const std::vector<int> R = radix_order(N, fixed);
   P.dev.N = N;
   P.dev.npass = (int)R.size();
   P.dev.W = W;
@@ -374,11 +411,12 @@ dks_status dks_fft_plan(int nx, int ny, int nz, int batch, dks_fft_kind kind, dk
   // x: padded row tiles (unpadded single rows when even one padded row does not fit)
   const int Wx = row_width(nx, c, wmax);
   const bool padded = (size_t)nx * (Wx + 1) * c <= (size_t)kLdsBytes;
-  make_axis(p->pl[0], nx, Wx, padded ? Wx + 1 : Wx);
+  make_axis(p->pl[0], nx, Wx, padded ? Wx + 1 : Wx, true);
+  const bool fit = cols_fit32(row_len_complex(p) * (size_t)ny * nz * batch);
   for (int a = 1; a < 3; ++a) {
     int W = wmax;
     while (W > 1 && (size_t)ns[a] * W * c > (size_t)kLdsBytes) W >>= 1;
-    make_axis(p->pl[a], ns[a], W, W);
+    make_axis(p->pl[a], ns[a], W, W, fit);
   }
   size_t off = 0;
   p->off_plans = off;

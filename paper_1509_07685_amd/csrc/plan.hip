@@ -76,9 +76,14 @@ static bool factor23(int N) {
   return N == 1;
 }
 
-// Radix-8 passes first, then one radix-4 or radix-2 pass for the remaining
-// powers of two, then radix-3 passes; pass 0 is even whenever N is.
-static std::vector<int> radices_for(int N) {
+// Radix order of a length: the compile-time kernels' where `fixed` says they
+// run it, else radix-8 passes first, then one radix-4 or radix-2 pass for the
+// remaining powers of two, then radix-3 passes; pass 0 is even whenever N is.
+static std::vector<int> radices_for(int N, bool fixed) {
+  if (fixed) {
+    const RadixList l = static_radices(N);
+    return std::vector<int>(l.r, l.r + l.n);
+  }
   int a = 0, b = 0;
   while (N % 2 == 0) { N /= 2; ++a; }
   while (N % 3 == 0) { N /= 3; ++b; }
@@ -339,9 +344,10 @@ void layout(dks_poisson_plan_s* p) {
   const int Wx = pick_width(nx, c, true, wmax);
   const int Wy = pick_width(m.Ny, c, false, wmax);
   const int Wz = pick_width(m.Nz, c, false, wmax);
-  build_fft(p->px, nx, radices_for(nx), Wx, true);
-  build_fft(p->py, m.Ny, radices_for(m.Ny), Wy, false);
-  std::vector<int> rz = radices_for(m.Nz);
+  const bool fit = offsets_fit32(m);
+  build_fft(p->px, nx, radices_for(nx, static_row(nx)), Wx, true);
+  build_fft(p->py, m.Ny, radices_for(m.Ny, fit && static_pencil(m.Ny)), Wy, false);
+  std::vector<int> rz = radices_for(m.Nz, fit && static_pencil(m.Nz));
   build_fft(p->pz, m.Nz, rz, Wz, false);
   std::reverse(rz.begin(), rz.end());
   build_fft(p->pzi, m.Nz, rz, Wz, false);
