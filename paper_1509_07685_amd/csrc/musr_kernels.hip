@@ -5,15 +5,14 @@
 // a call brings only the parameter vector and produces one FP64 number.
 //
 // One fused kernel per call: every workgroup takes 256 consecutive time
-// bins of a group of detectors, evaluates the model (the time-only factors
-// once per bin, shared by the group's detectors), accumulates the statistic
-// in FP64, reduces it across the workgroup in a fixed order and stores a
-// partial; a one-workgroup-per-set kernel then adds the partials in index
-// order, so a result is bitwise reproducible.  (A last-workgroup-done
-// counter in the first kernel would need an agent-scope release and
-// acquire per workgroup, i.e. an L2 write-back and invalidate each, which
-// measured slower than the second launch.)  Batched calls put the
-// parameter set in the grid's z index.
+// bins of a group of up to 16 detectors and a run of parameter sets,
+// evaluates the model, accumulates the statistic in FP64, reduces it across
+// the workgroup in a fixed order and stores a partial per set; a
+// one-workgroup-per-set kernel then adds the partials in index order, so a
+// result is bitwise reproducible.  (A last-workgroup-done counter in the
+// first kernel would need an agent-scope release and acquire per workgroup,
+// i.e. an L2 write-back and invalidate each, which measured slower than the
+// second launch.)
 
 #include <algorithm>
 #include <cmath>
@@ -30,21 +29,29 @@ namespace musr {
 constexpr int kMaxDet = 32;
 constexpr int kMaxSets = 1024;
 constexpr int kThreads = 256;
-constexpr int kChunk = 16;      // detector loads issued together
+constexpr int kGroup = 16;      // most detectors per workgroup: their counts stay in registers
+constexpr int kRun = 8;         // most parameter sets per workgroup: 36 KB of LDS, four workgroups per CU
 constexpr double kTauMu = 2.1969811;                         // muon lifetime, us
 constexpr double kGammaMu = 6.283185307179586 * 0.01355388094;   // rad / (us G)
 
-// Parameters of one evaluation, passed by value (kernel argument).
+// Parameters of one evaluation, passed by value (kernel argument): sigma, B
+// and per detector N0, Nbkg, A0 N0 cos(phi), A0 N0 sin(phi).
 struct Params {
   double sigma, B;
-  double det[kMaxDet][4];   // N0, Nbkg, A0, phi
+  double det[4 * kMaxDet];
 };
+
+// Sum over the wavefront in a fixed order (xor shuffles).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
 
 // Sum over the workgroup in a fixed order: within each wavefront by xor
 // shuffles, then the four wavefront sums in order.
 __device__ __forceinline__ double block_sum(double v, double* lds) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  v = wave_sum(v);
   const int w = (int)threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) lds[w] = v;
   __syncthreads();
@@ -55,6 +62,7 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
   return s;
 }
 
+// The statistic's term as it is defined.
 template <int STAT>
 __device__ __forceinline__ double term(double d, double N) {
   if constexpr (STAT == DKS_MUSR_CHISQ) {
@@ -65,84 +73,175 @@ __device__ __forceinline__ double term(double d, double N) {
   }
 }
 
-// grid: (time-bin blocks, detector groups, sets); partial: [sets][gx * gy].
-// A thread owns one time bin t = n dt and every detector of its group: the
-// decay exp(-t/tau), the damped decay exp(-t/tau - (sigma t)^2 / 2) and
-// cos/sin of the precession angle gamma B t depend on t alone, so they are
-// computed once per bin and the detectors' counts follow by
-// cos(w t + phi_j) = cos(w t) cos(phi_j) - sin(w t) sin(phi_j).
+// Counts and ratios N / d between these bounds take the fast terms below;
+// anything else (zero, negative, not finite, out of range) takes term().
+constexpr double kLow = 0x1p-960, kHigh = 0x1p960;
+
+// 1 / d of a normal d in (kLow, kHigh): the hardware estimate and two Newton
+// steps.
+__device__ __forceinline__ double recip(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  return fma(fma(-d, y, 1.0), y, y);
+}
+
+// a b + c with a constant c kept in scalar registers (the compiler's two-address
+// form copies a constant into the destination before every step of a
+// polynomial: a sixth of the batch's instructions).
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+  return r;
+}
+
+// log(q) of a normal q > 0: q = 2^k m with m in [sqrt(1/2), sqrt(2)), s =
+// (m - 1) / (m + 1), log m = 2 atanh(s) = 2 s (1 + z P(z)), z = s^2 <=
+// 0.02945.  P interpolates 1/3 + z/5 + z^2/7 + ... at the seven Chebyshev
+// nodes of that interval (z P off by at most 4.7e-18).
+__device__ __forceinline__ double log_normal(double q) {
+  const int hi = __double2hiint(q);
+  const int k = (hi - 0x3fe6a09e) >> 20;                  // sqrt(1/2) = 0x3fe6a09e...
+  const double m = __hiloint2double(hi - (k << 20), __double2loint(q));
+  const double s = (m - 1.0) * recip(m + 1.0);
+  const double z = s * s;
+  double p = 0.0730856419990365;
+  p = fma_const(p, z, 0.07665833338298587);
+  p = fma_const(p, z, 0.09091445389013066);
+  p = fma_const(p, z, 0.11111105556052474);
+  p = fma_const(p, z, 0.1428571431305726);
+  p = fma_const(p, z, 0.199999999999496);
+  p = fma_const(p, z, 0.3333333333333335);
+  const double s2 = s + s;
+  return fma((double)k, 0.6931471805599453, fma(s2 * z, p, s2));
+}
+
+// grid: (time-bin blocks, detector groups, runs of `run` sets); partial:
+// [sets][gx * gy].  A thread owns one time bin t = n dt and every detector of
+// its group for each set of its run: the counts d and their reciprocals are
+// formed once for all sets, and per set exp(-t/tau - (sigma t)^2 / 2) and
+// cos/sin of the precession angle gamma B t once for all detectors, whose
+// counts follow by cos(w t + phi_j) = cos(w t) cos(phi_j) - sin(w t)
+// sin(phi_j) in three multiply-adds.  With the division by d turned into a
+// product, log(d / N) = -log(N (1/d)) needs no division by N either.
+// Bound by FP64 vector issue: about 840 instructions per wavefront of bins and
+// set, 42 of them per detector's logarithm and term; 133 sets of 16 x 206250
+// bins took 1.59 ms (log-likelihood) when every term divided twice and ran
+// the library logarithm, 0.62 ms now.  A single evaluation is bound by the
+// latency of its one chain per lane and by the two launches (13.4 -> 12.6 us).
 template <int STAT, bool DEV>
-__global__ __launch_bounds__(kThreads) void k_musr_eval(const double* __restrict__ data, long long n_bins,
-                                                        double dt, Params prm, const double* __restrict__ dprm,
-                                                        int nparam, int n_det, int dg,
-                                                        double* __restrict__ partial) {
-  __shared__ double red[kThreads / 64];
-  __shared__ double sN0[kMaxDet], sNb[kMaxDet], sAN[kMaxDet], sC[kMaxDet], sS[kMaxDet];
-  const int set = blockIdx.z;
+__global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void k_musr_eval(const double* __restrict__ data, long long n_bins,
+                                                           double dt, Params prm, const double* __restrict__ dprm,
+                                                           int nparam, int n_det, int dg, int nsets, int run,
+                                                           double* __restrict__ partial) {
+  // per set of the run and detector of the group: N0, Nbkg, A0 N0 cos(phi), A0 N0 sin(phi)
+  __shared__ double cst[DEV ? kRun * kGroup * 4 : kGroup * 4];
+  __shared__ double sums[DEV ? kRun : 1][kThreads / 64];
+  __shared__ double2 uv[DEV ? kRun : 1][DEV ? kThreads : 1];   // a lane's own entries: cos and sin parts per set
+  const int tid = (int)threadIdx.x;
+  const int set0 = blockIdx.z * run;
+  const int ns = DEV ? min(run, nsets - set0) : 1;
   const int j0 = blockIdx.y * dg;
   const int nj = min(dg, n_det - j0);
-  const double* dp = DEV ? dprm + (size_t)set * nparam : nullptr;
-  // the group's detector constants: lane t < nj takes detector j0 + t
-  {
-    const int t = (int)threadIdx.x;
-    double N0 = 0.0, Nb = 0.0, A0 = 0.0, ph = 0.0;
-    if constexpr (DEV) {
-      if (t < nj) {
-        const double* q = dp + 2 + 4 * (j0 + t);
-        N0 = q[0];
-        Nb = q[1];
-        A0 = q[2];
-        ph = q[3];
-      }
-    } else {
-      for (int j = 0; j < nj; ++j)
-        if (t == j) {
-          N0 = prm.det[j0 + j][0];
-          Nb = prm.det[j0 + j][1];
-          A0 = prm.det[j0 + j][2];
-          ph = prm.det[j0 + j][3];
-        }
-    }
-    if (t < nj) {
-      double sp, cp;
-      sincos(ph, &sp, &cp);
-      sN0[t] = N0;
-      sNb[t] = Nb;
-      sAN[t] = A0 * N0;
-      sC[t] = cp;
-      sS[t] = sp;
-    }
-  }
-  __syncthreads();
-  const double sigma = DEV ? dp[0] : prm.sigma;
-  const double B = DEV ? dp[1] : prm.B;
-  const long long n = (long long)blockIdx.x * kThreads + threadIdx.x;
-  double acc = 0.0;
-  if (n < n_bins) {
-    const double t = (double)n * dt;
-    const double a = -t / kTauMu;
-    const double E = exp(a);
+  const long long n = (long long)blockIdx.x * kThreads + tid;
+  const bool live = n < n_bins;
+  const double* col = data + (size_t)j0 * n_bins + (live ? n : n_bins - 1);
+  const double t = (double)n * dt;
+  const double a = -t / kTauMu;
+  auto damped = [&](double sigma, double B) {
     const double EG = exp(a - 0.5 * (sigma * t) * (sigma * t));
     double sw, cw;
     sincos(kGammaMu * B * t, &sw, &cw);
-    const double* col = data + (size_t)j0 * n_bins + n;
-    // the detectors' counts of this bin in chunks of kChunk loads in flight
-    for (int jb = 0; jb < nj; jb += kChunk) {
-      double d[kChunk];
+    return make_double2(EG * cw, -EG * sw);
+  };
+  double d[kGroup], rd[kGroup];
+  double2 own;
+  if constexpr (DEV) {
+    // before the counts are loaded: their registers would be held through
+    // the sine's argument reduction, which needs many
+    for (int i = tid; i < ns * kGroup; i += kThreads) {
+      const int s = i / kGroup, j = i % kGroup;
+      double* c = cst + i * 4;
+      if (j < nj) {
+        const double* q = dprm + (size_t)(set0 + s) * nparam + 2 + 4 * (j0 + j);
+        double sp, cp;
+        sincos(q[3], &sp, &cp);
+        c[0] = q[0];
+        c[1] = q[1];
+        c[2] = q[2] * q[0] * cp;
+        c[3] = q[2] * q[0] * sp;
+      } else {
+        c[0] = c[2] = c[3] = 0.0;
+        c[1] = 1.0;
+      }
+    }
+#pragma unroll 1
+    for (int s = 0; s < ns; ++s) {
+      const double* q = dprm + (size_t)(set0 + s) * nparam;
+      uv[s][tid] = damped(q[0], q[1]);
+    }
+  }
 #pragma unroll
-      for (int k = 0; k < kChunk; ++k) d[k] = jb + k < nj ? col[(size_t)(jb + k) * n_bins] : 0.0;
+  for (int j = 0; j < kGroup; ++j) d[j] = j < nj ? col[(size_t)j * n_bins] : 1.0;
+  if constexpr (!DEV) {
+    if (tid < 4 * kGroup) cst[tid] = tid < 4 * nj ? prm.det[4 * j0 + tid] : (tid & 3) == 1 ? 1.0 : 0.0;
+    own = damped(prm.sigma, prm.B);
+  }
+  const double E = exp(a);
+  // A reciprocal's rounding error e (1/d = rd + e/d) is the same for every bin
+  // with that count, so the errors of N rd would not average out over the
+  // bins: -d e, the first order of d log(1 - e), takes them out again.
+  bool odd = false;          // some positive count out of the fast terms' range
+  double fix = 0.0;
 #pragma unroll
-      for (int k = 0; k < kChunk; ++k) {
-        const int j = jb + k;
-        if (j < nj) {
-          const double N = sN0[j] * E + sAN[j] * EG * (cw * sC[j] - sw * sS[j]) + sNb[j];
-          acc += term<STAT>(d[k], N);
+  for (int j = 0; j < kGroup; ++j) {
+    odd = odd || (d[j] > 0.0 && !(d[j] > kLow && d[j] < kHigh));
+    rd[j] = d[j] > 0.0 ? recip(d[j]) : 1.0;
+    if (STAT == DKS_MUSR_MLE && d[j] > 0.0) fix = fma(-d[j], fma(-d[j], rd[j], 1.0), fix);
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int s = 0; s < ns; ++s) {
+    if constexpr (DEV) own = uv[s][tid];
+    const double u = own.x, v = own.y;
+    const double* c = cst + s * (kGroup * 4);
+    double acc = fix;
+    unsigned far = 0;          // largest distance of a ratio's high word from kLow's
+    // four detectors at a time, their chains interleaved; a group's missing
+    // ones have a count and a model of 1 and add nothing
+#pragma unroll
+    for (int jb = 0; jb < kGroup; jb += 4) {
+      if (jb >= nj) break;
+#pragma unroll
+      for (int j = jb; j < jb + 4; ++j) {
+        const double N = fma(c[4 * j], E, fma(c[4 * j + 2], u, fma(c[4 * j + 3], v, c[4 * j + 1])));
+        if constexpr (STAT == DKS_MUSR_CHISQ) {
+          const double r = d[j] - N;
+          acc += r * r * rd[j];
+        } else {
+          // d <= 0 has rd = 1 and weighs its logarithm with 0
+          const double q = N * rd[j];
+          far = max(far, (unsigned)__double2hiint(q) - (unsigned)__double2hiint(kLow));
+          acc += fma(-fmax(d[j], 0.0), log_normal(q), N - d[j]);
         }
       }
     }
+    if (odd || far > (unsigned)__double2hiint(kHigh) - (unsigned)__double2hiint(kLow)) {
+      acc = 0.0;
+#pragma unroll 1
+      for (int j = 0; j < nj; ++j) {
+        const double N = fma(c[4 * j], E, fma(c[4 * j + 2], u, fma(c[4 * j + 3], v, c[4 * j + 1])));
+        acc += term<STAT>(col[(size_t)j * n_bins], N);
+      }
+    }
+    const double w = wave_sum(live ? acc : 0.0);
+    if ((tid & 63) == 0) sums[s][tid >> 6] = w;
   }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[(size_t)set * gridDim.x * gridDim.y + blockIdx.y * gridDim.x + blockIdx.x] = s;
+  __syncthreads();
+  if (tid < ns) {
+    double w = 0.0;
+    for (int i = 0; i < kThreads / 64; ++i) w += sums[tid][i];
+    partial[(size_t)(set0 + tid) * gridDim.x * gridDim.y + blockIdx.y * gridDim.x + blockIdx.x] = w;
+  }
 }
 
 // One workgroup per set: the set's partials added in index order.
@@ -183,8 +282,17 @@ template <int STAT, bool DEV>
 hipError_t launch(const dks_musr_plan_s* p, const Params& prm, const double* dprm, int nsets, double* result,
                   hipStream_t st) {
   double* partial = reinterpret_cast<double*>(p->ws);
-  hipLaunchKernelGGL((k_musr_eval<STAT, DEV>), dim3(p->bx, p->gy, nsets), dim3(kThreads), 0, st, p->data,
-                     p->n_bins, p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, p->dg, partial);
+  // sets per workgroup: the counts' reciprocals are shared by a run, but at
+  // least about four rounds of workgroups (four per CU) should remain
+  const long long groups = (long long)p->bx * p->gy;
+  int run = 1;
+  if (DEV) {
+    const int want = (int)std::min<long long>(kRun, std::max<long long>(1, groups * nsets / 4096));
+    const int runs = (nsets + want - 1) / want;
+    run = (nsets + runs - 1) / runs;
+  }
+  hipLaunchKernelGGL((k_musr_eval<STAT, DEV>), dim3(p->bx, p->gy, (nsets + run - 1) / run), dim3(kThreads), 0, st,
+                     p->data, p->n_bins, p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, p->dg, nsets, run, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_musr_final<STAT>), dim3(nsets), dim3(kThreads), 0, st, partial, p->bx * p->gy, result);
@@ -226,9 +334,10 @@ dks_status dks_musr_plan(int n_det, int64_t n_bins, double dt, int max_sets, dks
   p->dt = dt;
   p->max_sets = max_sets;
   p->bx = (int)((n_bins + kThreads - 1) / kThreads);
-  // share the per-bin transcendentals across as many detectors as possible
-  // while keeping at least ~512 workgroups per set in flight
-  const int groups = (int)std::min<long long>(n_det, std::max<long long>(1, (512 + p->bx - 1) / p->bx));
+  // share the per-bin transcendentals across as many detectors as a group
+  // holds while keeping at least ~512 workgroups per set in flight
+  const long long least = std::max<long long>((n_det + kGroup - 1) / kGroup, (512 + p->bx - 1) / p->bx);
+  const int groups = (int)std::min<long long>(n_det, least);
   p->dg = (n_det + groups - 1) / groups;
   p->gy = (n_det + p->dg - 1) / p->dg;
   p->ws_total = al256((size_t)max_sets * p->bx * p->gy * sizeof(double));
@@ -273,8 +382,13 @@ dks_status dks_musr_eval(dks_musr_plan_t p, dks_musr_stat stat, const double* pa
   std::memset(&prm, 0, sizeof(prm));
   prm.sigma = params[0];
   prm.B = params[1];
-  for (int j = 0; j < p->n_det; ++j)
-    for (int q = 0; q < 4; ++q) prm.det[j][q] = params[2 + 4 * j + q];
+  for (int j = 0; j < p->n_det; ++j) {
+    const double* q = params + 2 + 4 * j;
+    prm.det[4 * j] = q[0];
+    prm.det[4 * j + 1] = q[1];
+    prm.det[4 * j + 2] = q[2] * q[0] * std::cos(q[3]);
+    prm.det[4 * j + 3] = q[2] * q[0] * std::sin(q[3]);
+  }
   return run(p, stat, prm, nullptr, 1, result, static_cast<hipStream_t>(stream));
 }
 
