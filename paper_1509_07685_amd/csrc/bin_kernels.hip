@@ -145,7 +145,8 @@ __device__ __forceinline__ BinState bin_state(char* slot_base, size_t stride, si
   s.offset = s.count + L;
   s.xcursor = s.offset + L + 1;
   s.item_off = s.xcursor + kXcd * L;
-  s.misc = s.item_off + L + 1;
+  s.gitem_off = s.item_off + L + 1;
+  s.misc = s.gitem_off + L + 1;
   return s;
 }
 
@@ -236,8 +237,14 @@ __device__ __forceinline__ void count_add(unsigned* ctr, int key) {
 // c = w, w + G, ... (G = gridDim.x, a multiple of kXcd), which all fall in
 // group (b * nchunk + w) mod kXcd.
 // ---------------------------------------------------------------------------
+// 1024 lanes: a chunk is one round of vector loads, all in flight at once
+// (with 256 lanes the four rounds of a chunk waited for each other: 10 us
+// against 6 for 1e6 FP32 particles).  Solves of more chunks than two per CU keep
+// 256, whose seven wavefronts per SIMD hide the loads better (185 against 220
+// us at 1e8).
+constexpr int kCountThreads = 1024;
 template <typename T, bool LDSHIST, int SCH>
-__global__ __launch_bounds__(256) void k_bin_count(ElemBatch eb, const Geometry* geo, size_t stride, char* slot_base,
+__global__ __launch_bounds__(kCountThreads) void k_bin_count(ElemBatch eb, const Geometry* geo, size_t stride, char* slot_base,
                                                    size_t bins_off, MeshDims m, BinGeom bg, int nchunk) {
   extern __shared__ unsigned hist[];
   constexpr int64_t CH = scatter_chunk<T>();
@@ -274,40 +281,39 @@ __global__ __launch_bounds__(256) void k_bin_count(ElemBatch eb, const Geometry*
 // block of 1024 threads per batch element.  Also publishes the out-of-mesh
 // count.
 // ---------------------------------------------------------------------------
-// Exclusive prefix sums of (a, b) over the 1024 lanes of the workgroup in
-// lane order: inclusive scans within each wavefront by shuffles, then the
-// wavefront totals; returns the exclusive sums, totals in *ta, *tb.
-__device__ __forceinline__ void scan1024(unsigned a, unsigned b, unsigned* wa, unsigned* wb, unsigned* ea,
-                                         unsigned* eb_, unsigned* ta, unsigned* tb) {
+// Exclusive prefix sums of the N values v over the 1024 lanes of the workgroup
+// in lane order: inclusive scans within each wavefront by shuffles, then the
+// wavefront totals; leaves the exclusive sums in v, the totals in tot.
+template <int N>
+__device__ __forceinline__ void scan1024(unsigned (&v)[N], unsigned (*ws)[16], unsigned (&tot)[N]) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  unsigned x = a, y = b;
+  unsigned x[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) x[q] = v[q];
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const unsigned xo = __shfl_up(x, o, 64), yo = __shfl_up(y, o, 64);
-    if (lane >= o) {
-      x += xo;
-      y += yo;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const unsigned xo = __shfl_up(x[q], o, 64);
+      if (lane >= o) x[q] += xo;
     }
   }
   if (lane == 63) {
-    wa[w] = x;
-    wb[w] = y;
+#pragma unroll
+    for (int q = 0; q < N; ++q) ws[q][w] = x[q];
   }
   __syncthreads();
-  unsigned pa = 0, pb = 0, sa = 0, sb = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (i < w) {
-      pa += wa[i];
-      pb += wb[i];
+  for (int q = 0; q < N; ++q) {
+    unsigned p = 0, s = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i < w) p += ws[q][i];
+      s += ws[q][i];
     }
-    sa += wa[i];
-    sb += wb[i];
+    v[q] = p + x[q] - v[q];
+    tot[q] = s;
   }
-  *ea = pa + x - a;
-  *eb_ = pb + y - b;
-  *ta = sa;
-  *tb = sb;
 }
 
 // Tile counts of one element: per-XCD-group counts summed, exclusive offsets,
@@ -318,13 +324,31 @@ __device__ __forceinline__ void scan1024(unsigned a, unsigned b, unsigned* wa, u
 constexpr int kScanRun = 8;
 __global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t stride, char* slot_base,
                                                    size_t bins_off, BinGeom bg, ElemBatch eb) {
-  __shared__ unsigned wa[16], wb[16];
+  __shared__ unsigned ws[3][16];
   const int b = blockIdx.x;
   BinState st = bin_state(slot_base, stride, bins_off, b, bg.K);
   const int L = bg.K + 1;
   const int per = (L + 1023) / 1024;
   const int lo = min((int)threadIdx.x * per, L), hi = min(lo + per, L);
-  unsigned sc = 0, si = 0, oc, oi, tc, ti;
+  // running sums: particles, deposit items, gather items
+  unsigned run[3] = {0, 0, 0}, tot[3];
+  auto items = [](unsigned c, int item) { return (c + (unsigned)item - 1) / (unsigned)item; };
+  auto add = [&](unsigned c) {
+    run[0] += c;
+    run[1] += items(c, bg.item);
+    run[2] += items(c, bg.gitem);
+  };
+  auto store = [&](int k) {
+    st.offset[k] = run[0];
+    unsigned cur = run[0];
+#pragma unroll
+    for (int x = 0; x < kXcd; ++x) {
+      st.xcursor[x * L + k] = cur;
+      cur += st.xcount[x * L + k];
+    }
+    st.item_off[k] = run[1];
+    st.gitem_off[k] = run[2];
+  };
   if (per <= kScanRun) {
     unsigned c[kScanRun];
 #pragma unroll
@@ -339,25 +363,15 @@ __global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t s
     for (int j = 0; j < kScanRun; ++j) {
       if (lo + j < hi) {
         st.count[lo + j] = c[j];
-        sc += c[j];
-        si += (c[j] + bg.item - 1) / bg.item;
+        add(c[j]);
       }
     }
-    scan1024(sc, si, wa, wb, &oc, &oi, &tc, &ti);
+    scan1024(run, ws, tot);
 #pragma unroll
     for (int j = 0; j < kScanRun; ++j) {
-      const int k = lo + j;
-      if (k < hi) {
-        st.offset[k] = oc;
-        unsigned run = oc;
-#pragma unroll
-        for (int x = 0; x < kXcd; ++x) {
-          st.xcursor[x * L + k] = run;
-          run += st.xcount[x * L + k];
-        }
-        st.item_off[k] = oi;
-        oc += c[j];
-        oi += (c[j] + bg.item - 1) / bg.item;
+      if (lo + j < hi) {
+        store(lo + j);
+        add(c[j]);
       }
     }
   } else {
@@ -366,28 +380,20 @@ __global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t s
 #pragma unroll
       for (int x = 0; x < kXcd; ++x) c += st.xcount[x * L + k];
       st.count[k] = c;
-      sc += c;
-      si += (c + bg.item - 1) / bg.item;
+      add(c);
     }
-    scan1024(sc, si, wa, wb, &oc, &oi, &tc, &ti);
+    scan1024(run, ws, tot);
     for (int k = lo; k < hi; ++k) {
-      const unsigned c = st.count[k];
-      st.offset[k] = oc;
-      unsigned run = oc;
-#pragma unroll
-      for (int x = 0; x < kXcd; ++x) {
-        st.xcursor[x * L + k] = run;
-        run += st.xcount[x * L + k];
-      }
-      st.item_off[k] = oi;
-      oc += c;
-      oi += (c + bg.item - 1) / bg.item;
+      store(k);
+      add(st.count[k]);
     }
   }
   if (threadIdx.x == 1023) {
-    st.offset[L] = tc;
-    st.item_off[L] = ti;
-    st.misc[0] = ti;
+    st.offset[L] = tot[0];
+    st.item_off[L] = tot[1];
+    st.gitem_off[L] = tot[2];
+    st.misc[0] = tot[1];
+    st.misc[1] = tot[2];
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -452,7 +458,7 @@ struct NoMid {
 };
 template <typename T, bool FULL, class RecOut, class Mid = NoMid, int PER = chunk_per<T, kScatterThreads>()>
 __device__ __forceinline__ void scatter_stage_chunk(unsigned* lcnt, unsigned* lbase, Rec<T>* srec,
-                                                    unsigned short* skey, unsigned* wa, unsigned* wb,
+                                                    unsigned short* skey, unsigned (*ws)[16],
                                                     unsigned* cursor, const BinGeom& bg, const int (&key)[PER],
                                                     const unsigned (&rank)[PER], const T (&xs)[PER],
                                                     const T (&ys)[PER], const T (&zs)[PER], int64_t c0, int64_t n,
@@ -473,8 +479,9 @@ __device__ __forceinline__ void scatter_stage_chunk(unsigned* lcnt, unsigned* lb
   }
 #pragma unroll
   for (int q = 0; q < kStageRun; ++q) rv[q] = cv[q] ? atomicAdd(&cursor[lo + q], cv[q]) : 0u;
-  unsigned off, unused0, unused1, unused2;
-  scan1024(sum, 0u, wa, wb, &off, &unused0, &unused1, &unused2);
+  unsigned scan[1] = {sum}, total[1];
+  scan1024(scan, ws, total);
+  unsigned off = scan[0];
 #pragma unroll
   for (int q = 0; q < kStageRun; ++q) {
     if (lo + q < hi) {
@@ -559,7 +566,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
                                                                  size_t inv_off, MeshDims m, BinGeom bg,
                                                                  int chunk0, int nchunk, SortedOut<T> so) {
   extern __shared__ unsigned lds[];
-  __shared__ unsigned wa[16], wb[16];
+  __shared__ unsigned ws[1][16];
   constexpr int PER = chunk_per<T, kScatterThreads>();
   constexpr int NV = Vec16<T>::n;
   constexpr int64_t CH = scatter_chunk<T>();
@@ -638,7 +645,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
     else rank[j] = key[j] >= 0 ? rank_add(cursor, key[j]) : 0u;
   }
   if constexpr (STAGE) {
-    scatter_stage_chunk<T, false>(lcnt, lbase, srec, skey, wa, wb, cursor, bg, key, rank, xs, ys, zs, c0, n, vec, out,
+    scatter_stage_chunk<T, false>(lcnt, lbase, srec, skey, ws, cursor, bg, key, rank, xs, ys, zs, c0, n, vec, out,
                                   inv);
     return;
   }
@@ -701,7 +708,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
                                                                       size_t inv_off, MeshDims m, BinGeom bg,
                                                                       int nchunk, int nfull, SortedOut<T> so) {
   extern __shared__ unsigned lds[];
-  __shared__ unsigned wa[16], wb[16];
+  __shared__ unsigned ws[1][16];
   constexpr int PER = chunk_per<T, kScatterThreads>();
   constexpr int NV = Vec16<T>::n;
   constexpr int64_t CH = scatter_chunk<T>();
@@ -755,7 +762,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
     const int cn = c + (int)gridDim.x;
     const bool more = cn < nfull;
     T nxs[PER], nys[PER], nzs[PER];
-    scatter_stage_chunk<T, true>(lcnt, lbase, srec, skey, wa, wb, cursor, bg, key, rank, xs, ys, zs,
+    scatter_stage_chunk<T, true>(lcnt, lbase, srec, skey, ws, cursor, bg, key, rank, xs, ys, zs,
                                  (int64_t)c * CH, n, true, out, inv,
                                  [&]() { load(more ? cn : c, nxs, nys, nzs); });
     if (!more) break;
@@ -771,19 +778,27 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
 
 // Work item t -> (tile, first particle, one past the last).
 // The range is clamped to the binned-particle buffer (max_np records).
-__device__ __forceinline__ void decode_item(const BinState& st, const BinGeom& bg, unsigned t, int* tile,
-                                            unsigned* start, unsigned* end) {
+// The tile is the last one with item_off <= t: every wavefront narrows the
+// range 64-fold per step with one load per lane (one step up to 63 tiles, two
+// up to 4095; a binary search's dependent loads took 6 and 12 round trips to
+// the L2 before the workgroup could start).  All lanes of the wavefront call.
+__device__ __forceinline__ void decode_item(const unsigned* item_off, int item, const BinState& st,
+                                            const BinGeom& bg, unsigned t, int* tile, unsigned* start,
+                                            unsigned* end) {
+  const int lane = (int)threadIdx.x & 63;
   int lo = 0, hi = bg.K + 1;   // item_off[lo] <= t < item_off[hi]
   while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (st.item_off[mid] <= t) lo = mid;
-    else hi = mid;
+    const int step = (hi - lo + 63) >> 6;
+    const int k = lo + lane * step;
+    const unsigned long long at = __ballot(k < hi && item_off[min(k, hi)] <= t);
+    lo += (__popcll(at) - 1) * step;                     // item_off is non-decreasing: at is a run from lane 0
+    hi = min(lo + step, hi);
   }
+  lo = __builtin_amdgcn_readfirstlane(lo);
   *tile = lo;
-  const unsigned e = min(min(st.offset[lo] + (t - st.item_off[lo]) * (unsigned)bg.item + (unsigned)bg.item,
-                             st.offset[lo + 1]),
-                         bg.max_np);
-  *start = min(st.offset[lo] + (t - st.item_off[lo]) * (unsigned)bg.item, e);
+  const unsigned first = st.offset[lo] + (t - item_off[lo]) * (unsigned)item;
+  const unsigned e = min(min(first + (unsigned)item, st.offset[lo + 1]), bg.max_np);
+  *start = min(first, e);
   *end = e;
 }
 
@@ -826,16 +841,14 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_binned(const Geomet
   for (unsigned t = blockIdx.x; t < nitems; t += gridDim.x) {
     int tile;
     unsigned s0, s1;
-    decode_item(st, bg, t, &tile, &s0, &s1);
+    decode_item(st.item_off, bg.item, st, bg, t, &tile, &s0, &s1);
     if (tile == bg.K) continue;                      // outside particles deposit nothing
     const int tx = tile % bg.tx, ty = (tile / bg.tx) % bg.ty, tz = tile / (bg.tx * bg.ty);
     // first node of the accumulator (the tile's first stencil node)
     const int bx = tx * kTile + Scheme<SCH>::lo, by = ty * kTile + Scheme<SCH>::lo, bz = tz * kTile + Scheme<SCH>::lo;
-    for (int e = threadIdx.x; e < NN; e += blockDim.x) acc[e] = 0ull;
-    __syncthreads();
     // The next group of records is loaded while this one is deposited (the
     // loop issues no other vector-memory operation, so waiting for them is
-    // exact).
+    // exact), the first one while the accumulator is cleared.
     // Loads past the item's end re-read its last record (s1 > s0 here), so
     // that no load is conditional: a conditional one makes the compiler wait
     // for every load in flight before the next use.
@@ -844,6 +857,8 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_binned(const Geomet
 #pragma unroll
       for (int u = 0; u < kUnrollDeposit; ++u) pr[u] = part.ld(min(s0 + threadIdx.x + u * blockDim.x, s1 - 1));
     }
+    for (int e = threadIdx.x; e < NN; e += blockDim.x) acc[e] = 0ull;
+    __syncthreads();
     for (unsigned i0 = s0 + threadIdx.x; i0 < s1; i0 += kUnrollDeposit * blockDim.x) {
 #pragma unroll
       for (int u = 0; u < kUnrollDeposit; ++u) nx[u] = part.ld(min(i0 + (kUnrollDeposit + u) * blockDim.x, s1 - 1));
@@ -928,11 +943,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_binned(const Geometry
   const T* phi = phi_ext + (size_t)b * phi_stride;
   const T cx = Geo<T>::grad(g, 0), cy = Geo<T>::grad(g, 1), cz = Geo<T>::grad(g, 2);
   const int nx2 = m.nx + 2, ny2 = m.ny + 2, nz2 = m.nz + 2;
-  const unsigned nitems = min(st.misc[0], bg.max_items);
+  const unsigned nitems = min(st.misc[1], bg.max_gitems);
   for (unsigned t = blockIdx.x; t < nitems; t += gridDim.x) {
     int tile;
     unsigned s0, s1;
-    decode_item(st, bg, t, &tile, &s0, &s1);
+    decode_item(st.gitem_off, bg.gitem, st, bg, t, &tile, &s0, &s1);
     if (tile == bg.K) {
       for (unsigned i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
         if constexpr (SOA) {
@@ -949,12 +964,22 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_binned(const Geometry
     // first stencil node of the tile; staged value e holds node b? - 1 + e,
     // which is phi_ext index b? + e (phi_ext index = node + 1)
     const int bx = tx * kTile + Scheme<SCH>::lo, by = ty * kTile + Scheme<SCH>::lo, bz = tz * kTile + Scheme<SCH>::lo;
-    for (int e = threadIdx.x; e < NA; e += blockDim.x) {
-      const int ex = e % A, ey = (e / A) % A, ez = e / (A * A);
-      const int x = bx + ex, y = by + ey, z = bz + ez;
-      const bool in_yz = y >= 0 && z >= 0 && y < ny2 && z < nz2;
-      const T* row = phi + ((size_t)z * ny2 + y) * nx2;
-      ph[e] = (in_yz && x >= 0 && x < nx2) ? row[x] : (T)0;
+    // All of a lane's loads of a batch are issued before the first LDS store.
+    // A node off the mesh is read as the nearest one on it: no particle's
+    // stencil reaches it.
+    constexpr int SB = 8;
+    for (int e0 = threadIdx.x; e0 < NA; e0 += SB * kGatherThreads) {
+      T v[SB];
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const int e = min(e0 + u * kGatherThreads, NA - 1);
+        const int x = min(max(bx + e % A, 0), nx2 - 1), y = min(max(by + (e / A) % A, 0), ny2 - 1),
+                  z = min(max(bz + e / (A * A), 0), nz2 - 1);
+        v[u] = phi[((size_t)z * ny2 + y) * nx2 + x];
+      }
+#pragma unroll
+      for (int u = 0; u < SB; ++u)
+        if (e0 + u * kGatherThreads < NA) ph[e0 + u * kGatherThreads] = v[u];
     }
     __syncthreads();
     // Unconditional loads (past the item's end they re-read its last record;
@@ -1072,6 +1097,7 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
                                                               size_t phi_stride, MeshDims m, BinGeom bg,
                                                               SortedOut<float> so) {
   constexpr int E = field_edge<SCH>(), WD = Scheme<SCH>::width;
+  static_assert(Scheme<SCH>::lo == 0, "a tile's first stencil node is on the mesh");
   __shared__ float4 ef[E * E * E];
   using P4 = Rec<float>;
   const int b = blockIdx.y;
@@ -1082,11 +1108,11 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
   const float* phi = phi_ext + (size_t)b * phi_stride;
   const float cx = Geo<float>::grad(g, 0), cy = Geo<float>::grad(g, 1), cz = Geo<float>::grad(g, 2);
   const int nx2 = m.nx + 2, ny2 = m.ny + 2, nz2 = m.nz + 2;
-  const unsigned nitems = min(st.misc[0], bg.max_items);
+  const unsigned nitems = min(st.misc[1], bg.max_gitems);
   for (unsigned t = blockIdx.x; t < nitems; t += gridDim.x) {
     int tile;
     unsigned s0, s1;
-    decode_item(st, bg, t, &tile, &s0, &s1);
+    decode_item(st.gitem_off, bg.gitem, st, bg, t, &tile, &s0, &s1);
     if (tile == bg.K) {
       for (unsigned i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
         if constexpr (SOA) {
@@ -1102,17 +1128,30 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
     const int tx = tile % bg.tx, ty = (tile / bg.tx) % bg.ty, tz = tile / (bg.tx * bg.ty);
     // entry e holds node (bx, by, bz) + (e % E, e / E % E, e / E^2), the
     // tile's first stencil node onwards; its phi_ext index is node + 1 per
-    // axis, and phi outside phi_ext reads as 0
+    // axis.  Entries of nodes off the mesh are formed from the nearest values
+    // on it (no particle's stencil reaches them); SB entries' loads are issued
+    // before the first is used.
     const int bx = tx * kTile + Scheme<SCH>::lo, by = ty * kTile + Scheme<SCH>::lo, bz = tz * kTile + Scheme<SCH>::lo;
-    for (int e = threadIdx.x; e < E * E * E; e += blockDim.x) {
-      const int x = bx + e % E + 1, y = by + (e / E) % E + 1, z = bz + e / (E * E) + 1;
-      auto at = [&](int xx, int yy, int zz) {
-        return (xx >= 0 && yy >= 0 && zz >= 0 && xx < nx2 && yy < ny2 && zz < nz2)
-                   ? phi[((size_t)zz * ny2 + yy) * nx2 + xx]
-                   : 0.f;
-      };
-      ef[e] = make_float4(at(x + 1, y, z) - at(x - 1, y, z), at(x, y + 1, z) - at(x, y - 1, z),
-                          at(x, y, z + 1) - at(x, y, z - 1), 0.f);
+    constexpr int NE = E * E * E, SB = 5;
+    const int sy = nx2, sz = nx2 * ny2;
+    for (int e0 = threadIdx.x; e0 < NE; e0 += SB * 1024) {
+      float v[SB][6];
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const int e = min(e0 + u * 1024, NE - 1);
+        const int x = min(bx + e % E + 1, nx2 - 2), y = min(by + (e / E) % E + 1, ny2 - 2),
+                  z = min(bz + e / (E * E) + 1, nz2 - 2);
+        const float* c = phi + (size_t)z * sz + (y * sy + x);
+        v[u][0] = c[1];
+        v[u][1] = c[-1];
+        v[u][2] = c[sy];
+        v[u][3] = c[-sy];
+        v[u][4] = c[sz];
+        v[u][5] = c[-sz];
+      }
+#pragma unroll
+      for (int u = 0; u < SB; ++u)
+        if (e0 + u * 1024 < NE) ef[e0 + u * 1024] = make_float4(v[u][0] - v[u][1], v[u][2] - v[u][3], v[u][4] - v[u][5], 0.f);
     }
     __syncthreads();
     // Unconditional loads (past the item's end they re-read its last record;
@@ -1283,34 +1322,6 @@ template <class F> static void with_scheme_soa(int scheme, bool soa, F&& f) {
   });
 }
 
-template <typename T>
-hipError_t launch_bin_count(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, char* slot_base, size_t bins_off,
-                            const MeshDims& m, const BinGeom& bg, int nblk, hipStream_t s) {
-  (void)nblk;
-  if (eb.max_np == 0) return hipSuccess;
-  const int64_t nchunk = (eb.max_np + scatter_chunk<T>() - 1) / scatter_chunk<T>();
-  // a multiple of kXcd, so every chunk a workgroup walks is in one XCD group
-  const unsigned grid = (unsigned)std::min<int64_t>(1024, (nchunk + kXcd - 1) / kXcd * kXcd);
-  const bool lh = bg.lds_hist != 0;
-  const size_t lds = lh ? (size_t)(bg.K + 1) * sizeof(unsigned) : 0;
-  with_scheme(bg.scheme, [&](auto sc) {
-    constexpr int SCH = decltype(sc)::value;
-    if (lh)
-      hipLaunchKernelGGL((k_bin_count<T, true, SCH>), dim3(grid, batch), dim3(256), lds, s, eb, geo, stride,
-                         slot_base, bins_off, m, bg, (int)nchunk);
-    else
-      hipLaunchKernelGGL((k_bin_count<T, false, SCH>), dim3(grid, batch), dim3(256), 0, s, eb, geo, stride,
-                         slot_base, bins_off, m, bg, (int)nchunk);
-  });
-  return hipGetLastError();
-}
-
-hipError_t launch_bin_scan(const Geometry* geo, size_t stride, char* slot_base, size_t bins_off, const BinGeom& bg,
-                           const ElemBatch& eb, int batch, hipStream_t s) {
-  hipLaunchKernelGGL(k_bin_scan, dim3(batch), dim3(1024), 0, s, geo, stride, slot_base, bins_off, bg, eb);
-  return hipGetLastError();
-}
-
 // Compute units of the current device (cached per device).
 static int compute_units() {
   static int cache[64] = {0};
@@ -1322,6 +1333,35 @@ static int compute_units() {
     cache[dev] = v;
   }
   return cache[dev];
+}
+
+template <typename T>
+hipError_t launch_bin_count(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, char* slot_base, size_t bins_off,
+                            const MeshDims& m, const BinGeom& bg, int nblk, hipStream_t s) {
+  (void)nblk;
+  if (eb.max_np == 0) return hipSuccess;
+  const int64_t nchunk = (eb.max_np + scatter_chunk<T>() - 1) / scatter_chunk<T>();
+  // a multiple of kXcd, so every chunk a workgroup walks is in one XCD group
+  const unsigned grid = (unsigned)std::min<int64_t>(1024, (nchunk + kXcd - 1) / kXcd * kXcd);
+  const bool lh = bg.lds_hist != 0;
+  const size_t lds = lh ? (size_t)(bg.K + 1) * sizeof(unsigned) : 0;
+  const unsigned threads = nchunk * batch <= 2 * compute_units() ? kCountThreads : 256;
+  with_scheme(bg.scheme, [&](auto sc) {
+    constexpr int SCH = decltype(sc)::value;
+    if (lh)
+      hipLaunchKernelGGL((k_bin_count<T, true, SCH>), dim3(grid, batch), dim3(threads), lds, s, eb, geo, stride,
+                         slot_base, bins_off, m, bg, (int)nchunk);
+    else
+      hipLaunchKernelGGL((k_bin_count<T, false, SCH>), dim3(grid, batch), dim3(threads), 0, s, eb, geo, stride,
+                         slot_base, bins_off, m, bg, (int)nchunk);
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_bin_scan(const Geometry* geo, size_t stride, char* slot_base, size_t bins_off, const BinGeom& bg,
+                           const ElemBatch& eb, int batch, hipStream_t s) {
+  hipLaunchKernelGGL(k_bin_scan, dim3(batch), dim3(1024), 0, s, geo, stride, slot_base, bins_off, bg, eb);
+  return hipGetLastError();
 }
 
 template <typename T>

@@ -254,9 +254,11 @@ struct GeoArgs {
 struct BinGeom {
   int tx, ty, tz;      // tiles per axis
   int K;               // tx * ty * tz
-  int item;            // particles per deposit/gather work item
+  int item;            // particles per deposit work item
+  int gitem;           // particles per gather work item
   int lds_hist;        // 1: per-block tile histograms fit in LDS
-  unsigned max_items;  // bound on the work-item count of one solve
+  unsigned max_items;  // bounds on the work-item counts of one solve
+  unsigned max_gitems;
   unsigned max_np;     // bound on binned particles per element (buffer size)
   int scheme;          // kSchemeCIC / kSchemeNGP / kSchemeTSC
 };
@@ -273,17 +275,19 @@ constexpr int kXcd = 8;
 
 // Per-slot bin bookkeeping (uint32), L = K + 1 tiles (tile K: outside):
 // xcount[kXcd][L] (cleared by the geometry kernel), count[L], offset[L+1],
-// xcursor[kXcd][L], item_off[L+1], misc[4] (misc[0] = number of work items).
+// xcursor[kXcd][L], item_off[L+1] and gitem_off[L+1] (deposit and gather work
+// items), misc[4] (misc[0], misc[1]: their numbers).
 struct BinState {
   unsigned* xcount;
   unsigned* count;
   unsigned* offset;
   unsigned* xcursor;
   unsigned* item_off;
+  unsigned* gitem_off;
   unsigned* misc;
 };
-// Total entries of that layout: 2 kXcd L + 3 L + 2 (the two L + 1 arrays) + 4.
-__host__ __device__ constexpr int bins_entries(int K) { return (2 * kXcd + 3) * (K + 1) + 6; }
+// Total entries of that layout: 2 kXcd L + 4 L + 3 (the three L + 1 arrays) + 4.
+__host__ __device__ constexpr int bins_entries(int K) { return (2 * kXcd + 4) * (K + 1) + 7; }
 
 // Gauss-Legendre product rules of the Green's function bands: band i covers
 // D in [lo[i], lo[i+1]), D = |cell centre| / largest cell side.

@@ -458,7 +458,8 @@ GeoArgs geo_args(const dks_poisson_plan_s* p, int mode, int nblocks) {
 struct PartWork {
   BinGeom bg;
   int count_blocks;   // blocks of the count and scatter kernels (same chunking)
-  int item_blocks;    // blocks of the deposit and gather kernels (loop over work items)
+  int item_blocks;    // blocks of the deposit kernel (loops over work items)
+  int gitem_blocks;   // blocks of the gather kernel (likewise)
 };
 
 PartWork part_work(const dks_poisson_plan_s* p, int64_t maxn) {
@@ -470,11 +471,24 @@ PartWork part_work(const dks_poisson_plan_s* p, int64_t maxn) {
   // items (measured: gather 703 -> 658 us, deposit 394 -> 379 us at 1e8).
   const int64_t item_cap = p->dtype == DKS_F32 ? 32768 : 16384;
   w.bg.item = (int)std::min<int64_t>(item_cap, std::max<int64_t>(8192, maxn / 512));
+  // The gather's items: the deposit's, except that the kernels that stage phi
+  // itself (FP64, TSC) take shorter ones in small solves, where a few long
+  // items in the bunch's core would be the whole time (96 x 96 x 192 FP64
+  // with 3e5 particles: 8192 per item 32 us, 4096 21 us, 2048 16 us; TSC at
+  // 144 x 128 x 96 with 3e6: 77, 79, 62 us).  Forming node differences costs
+  // a workgroup more, and a deposit item is merged into the mesh node by
+  // node: both lose by shorter items (64^3 FP32 with 1e6: 20 -> 25 -> 28 us,
+  // deposit 16 -> 23 -> 29).
+  const bool staged_phi = w.bg.scheme == kSchemeTSC || p->dtype == DKS_F64;
+  w.bg.gitem = staged_phi ? (int)std::min<int64_t>(w.bg.item, std::max<int64_t>(2048, maxn / 2048)) : w.bg.item;
   w.count_blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (maxn + 8191) / 8192));
   const int64_t items = (maxn + w.bg.item - 1) / w.bg.item + w.bg.K + 1;
   w.item_blocks = (int)std::min<int64_t>(16384, std::max<int64_t>(1, items));
+  const int64_t gitems = (maxn + w.bg.gitem - 1) / w.bg.gitem + w.bg.K + 1;
+  w.gitem_blocks = (int)std::min<int64_t>(16384, std::max<int64_t>(1, gitems));
   // kernels never trust more items or particles than the buffers were sized for
   w.bg.max_items = (unsigned)items;
+  w.bg.max_gitems = (unsigned)gitems;
   w.bg.max_np = (unsigned)maxn;
   return w;
 }
@@ -530,7 +544,7 @@ dks_status solve_particles_t(const dks_poisson_plan_s* p, int batch, const Slots
   r = convolve<T>(p, sl.base + p->s_r3, sl.stride / sizeof(T), batch, sl, eb, st);
   if (r != DKS_OK) return r;
   DKS_TK("gather", launch_gather_binned<T>(sl.geo(), sl.stride, sl.base, p->s_bins, sorted, sorted_stride,
-                                           sl.base + p->s_r3, sl.stride / sizeof(T), p->md, w.bg, w.item_blocks,
+                                           sl.base + p->s_r3, sl.stride / sizeof(T), p->md, w.bg, w.gitem_blocks,
                                            batch, sorted_out, st));
   if (!sorted_out) DKS_TK("unsort", launch_unsort<T>(eb, batch, sorted, sorted_stride, inv_off, st));
   return DKS_OK;
