@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
                                                            int nparam, int n_det, int dg, int nsets, int run,
                                                            double* __restrict__ partial) {
   // per set of the run and detector of the group: N0, Nbkg, A0 N0 cos(phi), A0 N0 sin(phi)
-  __shared__ double cst[DEV ? kRun * kGroup * 4 : kGroup * 4];
+  __shared__ double cst[DEV ? kRun * kGroup * 4 : 1];
   __shared__ double sums[DEV ? kRun : 1][kThreads / 64];
   __shared__ double2 uv[DEV ? kRun : 1][DEV ? kThreads : 1];   // a lane's own entries: cos and sin parts per set
   const int tid = (int)threadIdx.x;
@@ -160,18 +160,15 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
     // the sine's argument reduction, which needs many
     for (int i = tid; i < ns * kGroup; i += kThreads) {
       const int s = i / kGroup, j = i % kGroup;
-      double* c = cst + i * 4;
       if (j < nj) {
         const double* q = dprm + (size_t)(set0 + s) * nparam + 2 + 4 * (j0 + j);
         double sp, cp;
         sincos(q[3], &sp, &cp);
+        double* c = cst + i * 4;
         c[0] = q[0];
         c[1] = q[1];
         c[2] = q[2] * q[0] * cp;
         c[3] = q[2] * q[0] * sp;
-      } else {
-        c[0] = c[2] = c[3] = 0.0;
-        c[1] = 1.0;
       }
     }
 #pragma unroll 1
@@ -182,10 +179,7 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
   }
 #pragma unroll
   for (int j = 0; j < kGroup; ++j) d[j] = j < nj ? col[(size_t)j * n_bins] : 1.0;
-  if constexpr (!DEV) {
-    if (tid < 4 * kGroup) cst[tid] = tid < 4 * nj ? prm.det[4 * j0 + tid] : (tid & 3) == 1 ? 1.0 : 0.0;
-    own = damped(prm.sigma, prm.B);
-  }
+  if constexpr (!DEV) own = damped(prm.sigma, prm.B);
   const double E = exp(a);
   // A reciprocal's rounding error e (1/d = rd + e/d) is the same for every bin
   // with that count, so the errors of N rd would not average out over the
@@ -198,39 +192,52 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
     rd[j] = d[j] > 0.0 ? recip(d[j]) : 1.0;
     if (STAT == DKS_MUSR_MLE && d[j] > 0.0) fix = fma(-d[j], fma(-d[j], rd[j], 1.0), fix);
   }
-  __syncthreads();
+  if constexpr (DEV) __syncthreads();
 #pragma unroll 1
   for (int s = 0; s < ns; ++s) {
     if constexpr (DEV) own = uv[s][tid];
     const double u = own.x, v = own.y;
-    const double* c = cst + s * (kGroup * 4);
+    // constants of detector j of the group: LDS, or scalar loads of the kernel argument
+    auto model = [&](int j) {
+      if constexpr (DEV) {
+        const double* c = cst + (s * kGroup + j) * 4;
+        return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
+      } else {
+        const double* c = prm.det + 4 * (j0 + j);
+        return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
+      }
+    };
     double acc = fix;
     unsigned far = 0;          // largest distance of a ratio's high word from kLow's
-    // four detectors at a time, their chains interleaved; a group's missing
-    // ones have a count and a model of 1 and add nothing
+    auto one = [&](int j) {
+      const double N = model(j);
+      if constexpr (STAT == DKS_MUSR_CHISQ) {
+        const double r = d[j] - N;
+        acc += r * r * rd[j];
+      } else {
+        // d <= 0 has rd = 1 and weighs its logarithm with 0
+        const double q = N * rd[j];
+        far = max(far, (unsigned)__double2hiint(q) - (unsigned)__double2hiint(kLow));
+        acc += fma(-fmax(d[j], 0.0), log_normal(q), N - d[j]);
+      }
+    };
+    // four detectors at a time, their chains interleaved, then the rest
 #pragma unroll
     for (int jb = 0; jb < kGroup; jb += 4) {
-      if (jb >= nj) break;
+      if (jb + 4 <= nj) {
 #pragma unroll
-      for (int j = jb; j < jb + 4; ++j) {
-        const double N = fma(c[4 * j], E, fma(c[4 * j + 2], u, fma(c[4 * j + 3], v, c[4 * j + 1])));
-        if constexpr (STAT == DKS_MUSR_CHISQ) {
-          const double r = d[j] - N;
-          acc += r * r * rd[j];
-        } else {
-          // d <= 0 has rd = 1 and weighs its logarithm with 0
-          const double q = N * rd[j];
-          far = max(far, (unsigned)__double2hiint(q) - (unsigned)__double2hiint(kLow));
-          acc += fma(-fmax(d[j], 0.0), log_normal(q), N - d[j]);
-        }
+        for (int j = jb; j < jb + 4; ++j) one(j);
+      } else {
+#pragma unroll
+        for (int j = jb; j < jb + 3; ++j)
+          if (j < nj) one(j);
       }
     }
     if (odd || far > (unsigned)__double2hiint(kHigh) - (unsigned)__double2hiint(kLow)) {
       acc = 0.0;
 #pragma unroll 1
       for (int j = 0; j < nj; ++j) {
-        const double N = fma(c[4 * j], E, fma(c[4 * j + 2], u, fma(c[4 * j + 3], v, c[4 * j + 1])));
-        acc += term<STAT>(col[(size_t)j * n_bins], N);
+        acc += term<STAT>(col[(size_t)j * n_bins], model(j));
       }
     }
     const double w = wave_sum(live ? acc : 0.0);
@@ -282,20 +289,24 @@ template <int STAT, bool DEV>
 hipError_t launch(const dks_musr_plan_s* p, const Params& prm, const double* dprm, int nsets, double* result,
                   hipStream_t st) {
   double* partial = reinterpret_cast<double*>(p->ws);
-  // sets per workgroup: the counts' reciprocals are shared by a run, but at
-  // least about four rounds of workgroups (four per CU) should remain
-  const long long groups = (long long)p->bx * p->gy;
-  int run = 1;
+  // Batches: as many detectors per group as leave about four workgroups per
+  // CU (the plan's groups are those of one set), and runs of sets, which
+  // share the counts' reciprocals, as long as leave twice that.
+  int dg = p->dg, gy = p->gy, run = 1;
   if (DEV) {
-    const int want = (int)std::min<long long>(kRun, std::max<long long>(1, groups * nsets / 4096));
+    const long long per_group = (long long)p->bx * nsets;
+    gy = (int)std::min<long long>(gy, std::max<long long>((p->n_det + kGroup - 1) / kGroup, (1024 + per_group - 1) / per_group));
+    dg = (p->n_det + gy - 1) / gy;
+    gy = (p->n_det + dg - 1) / dg;
+    const int want = (int)std::min<long long>(kRun, std::max<long long>(1, per_group * gy / 2048));
     const int runs = (nsets + want - 1) / want;
     run = (nsets + runs - 1) / runs;
   }
-  hipLaunchKernelGGL((k_musr_eval<STAT, DEV>), dim3(p->bx, p->gy, (nsets + run - 1) / run), dim3(kThreads), 0, st,
-                     p->data, p->n_bins, p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, p->dg, nsets, run, partial);
+  hipLaunchKernelGGL((k_musr_eval<STAT, DEV>), dim3(p->bx, gy, (nsets + run - 1) / run), dim3(kThreads), 0, st,
+                     p->data, p->n_bins, p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, dg, nsets, run, partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_musr_final<STAT>), dim3(nsets), dim3(kThreads), 0, st, partial, p->bx * p->gy, result);
+  hipLaunchKernelGGL((k_musr_final<STAT>), dim3(nsets), dim3(kThreads), 0, st, partial, p->bx * gy, result);
   return hipGetLastError();
 }
 
@@ -386,8 +397,10 @@ dks_status dks_musr_eval(dks_musr_plan_t p, dks_musr_stat stat, const double* pa
     const double* q = params + 2 + 4 * j;
     prm.det[4 * j] = q[0];
     prm.det[4 * j + 1] = q[1];
-    prm.det[4 * j + 2] = q[2] * q[0] * std::cos(q[3]);
-    prm.det[4 * j + 3] = q[2] * q[0] * std::sin(q[3]);
+    double sp, cp;
+    sincos(q[3], &sp, &cp);
+    prm.det[4 * j + 2] = q[2] * q[0] * cp;
+    prm.det[4 * j + 3] = q[2] * q[0] * sp;
   }
   return run(p, stat, prm, nullptr, 1, result, static_cast<hipStream_t>(stream));
 }
