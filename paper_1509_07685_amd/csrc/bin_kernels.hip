@@ -110,25 +110,6 @@ __device__ __forceinline__ Recs<T, SOA> recs_of(char* sorted_base, size_t sorted
   }
 }
 
-// Fixed-point scale of the deposit accumulators: a weight is at most 1 and a
-// work item holds at most 2^16 (FP32) or 2^14 (FP64) particles, so a node sum
-// stays below 2^47 resp. 2^63 in 64 bits; the scale keeps 2^-31 resp. 2^-49
-// resolution, finer than the dtype's rounding of the weight products.  The
-// scale is a power of two, folded exactly into one factor of each product;
-// to() takes the scaled weight (an FP32 one fits 32 bits: one rounding
-// conversion instead of a 64-bit one).
-template <typename T> struct Fixed;
-template <> struct Fixed<float> {
-  static constexpr float scale = 2147483648.0f;   // 2^31
-  static __device__ __forceinline__ unsigned long long to(float ws) { return (unsigned long long)__float2uint_rn(ws); }
-  static __device__ __forceinline__ float from(unsigned long long v) { return (float)v * 4.656612873077393e-10f; }
-};
-template <> struct Fixed<double> {
-  static constexpr double scale = 562949953421312.0;   // 2^49
-  static __device__ __forceinline__ unsigned long long to(double ws) { return __double2ull_rn(ws); }
-  static __device__ __forceinline__ double from(unsigned long long v) { return (double)v * 1.7763568394002505e-15; }
-};
-
 __device__ __forceinline__ float cc(float x, float x0, float ih) { return __fmul_rn(__fsub_rn(x, x0), ih); }
 __device__ __forceinline__ double cc(double x, double x0, double ih) { return __dmul_rn(__dsub_rn(x, x0), ih); }
 
@@ -596,7 +577,9 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
   // the chunk's XCD group, as the count kernel assigned it
   unsigned* cursor = st.xcursor + (int)(((int64_t)b * nchunk + chunk) % kXcd) * (bg.K + 1);
   const Recs<T, SOA> out = recs_of<T, SOA>(sorted_base, sorted_stride, b, so);
-  unsigned* inv = SOA ? so.inv : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
+  unsigned* inv = SOA ? so.inv
+                  : inv_off == kNoInverse ? nullptr
+                      : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
   if (LDSHIST) {
     for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
   }
@@ -730,7 +713,9 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
   const Geometry* g = &gcopy;
   BinState st = bin_state(slot_base, stride, bins_off, b, bg.K);
   const Recs<T, SOA> out = recs_of<T, SOA>(sorted_base, sorted_stride, b, so);
-  unsigned* inv = SOA ? so.inv : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
+  unsigned* inv = SOA ? so.inv
+                  : inv_off == kNoInverse ? nullptr
+                      : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
   auto load = [&](int ch, T (&x)[PER], T (&y)[PER], T (&z)[PER]) {
 #pragma unroll
     for (int q = 0; q < PER / NV; ++q) {
@@ -903,20 +888,114 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit_binned(const Geomet
 // The order-independent deposit's totals -> W: one conversion of each exact
 // integer total (FP64: high word times 2^64 plus the low word, in units of
 // the fixed-point scale).
-template <typename T>
+// WIDE: two words per node (FP64), else one.
+template <typename T, bool WIDE>
 __global__ __launch_bounds__(256) void k_fixed_to_weights(const unsigned long long* __restrict__ iacc,
                                                           size_t ia_stride, T* __restrict__ W, size_t w_stride,
                                                           size_t nmesh) {
   const unsigned long long* ia = iacc + (size_t)blockIdx.y * ia_stride;
   T* w = W + (size_t)blockIdx.y * w_stride;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nmesh; i += (size_t)gridDim.x * blockDim.x) {
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (!WIDE) {
       w[i] = Fixed<T>::from(ia[i]);
     } else {
       const unsigned long long lo = ia[2 * i], hi = ia[2 * i + 1];
       w[i] = (double)hi * 32768.0 + Fixed<T>::from(lo);     // 2^64 * 2^-49 = 2^15
     }
   }
+}
+
+// Central-difference field at a particle from phi, without the coefficients:
+// o points at phi on the stencil's first node, sy and sz are the strides of
+// phi's rows and planes.
+template <typename T, int SCH>
+__device__ __forceinline__ void interp_phi(const T* o, int sy, int sz, const Cell<T, SCH>& c, T& ax, T& ay, T& az) {
+  constexpr int WD = Scheme<SCH>::width;
+  if constexpr (SCH == kSchemeCIC) {
+    const T* wx = c.wx;
+    const T* wy = c.wy;
+    const T* wz = c.wz;
+    // The 32 distinct nodes the eight central differences use: four x
+    // values per (y, z) corner row, and the y and z neighbours beyond the
+    // corner cube.
+    T r[2][2][4], ym[2][2], yp[2][2], zm[2][2], zp[2][2];
+#pragma unroll
+    for (int kz = 0; kz < 2; ++kz)
+#pragma unroll
+      for (int ky = 0; ky < 2; ++ky)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[kz][ky][k] = o[kz * sz + ky * sy + k - 1];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int kx = 0; kx < 2; ++kx) {
+        ym[a][kx] = o[a * sz - sy + kx];         // (x + kx, y - 1, z + a)
+        yp[a][kx] = o[a * sz + 2 * sy + kx];         // (x + kx, y + 2, z + a)
+        zm[a][kx] = o[-sz + a * sy + kx];            // (x + kx, y + a, z - 1)
+        zp[a][kx] = o[2 * sz + a * sy + kx];         // (x + kx, y + a, z + 2)
+      }
+    // E_d = c_d * sum over the eight corners of weight * (phi(+1) - phi(-1)),
+    // the coefficient applied once at the end.
+#pragma unroll
+    for (int kz = 0; kz < 2; ++kz)
+#pragma unroll
+      for (int ky = 0; ky < 2; ++ky) {
+        const T d0 = r[kz][ky][2] - r[kz][ky][0], d1 = r[kz][ky][3] - r[kz][ky][1];
+        ax += wz[kz] * wy[ky] * (wx[0] * d0 + wx[1] * d1);
+      }
+#pragma unroll
+    for (int kz = 0; kz < 2; ++kz)
+#pragma unroll
+      for (int kx = 0; kx < 2; ++kx) {
+        const T d0 = r[kz][1][kx + 1] - ym[kz][kx], d1 = yp[kz][kx] - r[kz][0][kx + 1];
+        ay += wz[kz] * wx[kx] * (wy[0] * d0 + wy[1] * d1);
+      }
+#pragma unroll
+    for (int ky = 0; ky < 2; ++ky)
+#pragma unroll
+      for (int kx = 0; kx < 2; ++kx) {
+        const T d0 = r[1][ky][kx + 1] - zm[ky][kx], d1 = zp[ky][kx] - r[0][ky][kx + 1];
+        az += wy[ky] * wx[kx] * (wz[0] * d0 + wz[1] * d1);
+      }
+  } else {
+    // every stencil node: weight * (phi(+1) - phi(-1)) per axis
+#pragma unroll
+    for (int kz = 0; kz < WD; ++kz)
+#pragma unroll
+      for (int ky = 0; ky < WD; ++ky)
+#pragma unroll
+        for (int kx = 0; kx < WD; ++kx) {
+          const T* q = o + kz * sz + ky * sy + kx;
+          const T wgt = c.wz[kz] * c.wy[ky] * c.wx[kx];
+          ax += wgt * (q[1] - q[-1]);
+          ay += wgt * (q[sy] - q[-sy]);
+          az += wgt * (q[sz] - q[-sz]);
+        }
+  }
+}
+
+// The same from the node differences node(kz, ky, kx) -> (x, y, z) of the
+// stencil's nodes.
+template <int SCH, class Node>
+__device__ __forceinline__ void interp_field(Node&& node, const Cell<float, SCH>& c, float& ax, float& ay, float& az) {
+  constexpr int WD = Scheme<SCH>::width;
+#pragma unroll
+  for (int kz = 0; kz < WD; ++kz)
+#pragma unroll
+    for (int ky = 0; ky < WD; ++ky) {
+      const float w = c.wz[kz] * c.wy[ky];
+      float rx = 0.f, ry = 0.f, rz = 0.f;
+#pragma unroll
+      for (int kx = 0; kx < WD; ++kx) {
+        const float4 d = node(kz, ky, kx);
+        rx += c.wx[kx] * d.x;
+        ry += c.wx[kx] * d.y;
+        rz += c.wx[kx] * d.z;
+      }
+      ax += w * rx;
+      ay += w * ry;
+      az += w * rz;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -932,7 +1011,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_binned(const Geometry
                                                        size_t bins_off, char* sorted_base, size_t sorted_stride,
                                                        const T* __restrict__ phi_ext, size_t phi_stride,
                                                        MeshDims m, BinGeom bg, SortedOut<T> so) {
-  constexpr int A = apron_edge<SCH>(), NA = A * A * A, WD = Scheme<SCH>::width;
+  constexpr int A = apron_edge<SCH>(), NA = A * A * A;
   __shared__ T ph[NA];
   using P4 = Rec<T>;
   const int b = blockIdx.y;
@@ -998,69 +1077,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_binned(const Geometry
         // staged index of the first stencil node: (node - tile's first node) + 1 per axis
         const int o_idx = ((c.bz - bz + 1) * A + (c.by - by + 1)) * A + (c.bx - bx + 1);
         T ax = 0, ay = 0, az = 0;
-        if constexpr (SCH == kSchemeCIC) {
-          const T* o = ph + o_idx;
-          const T* wx = c.wx;
-          const T* wy = c.wy;
-          const T* wz = c.wz;
-          // The 32 distinct nodes the eight central differences use: four x
-          // values per (y, z) corner row, and the y and z neighbours beyond the
-          // corner cube.
-          T r[2][2][4], ym[2][2], yp[2][2], zm[2][2], zp[2][2];
-#pragma unroll
-          for (int kz = 0; kz < 2; ++kz)
-#pragma unroll
-            for (int ky = 0; ky < 2; ++ky)
-#pragma unroll
-              for (int k = 0; k < 4; ++k) r[kz][ky][k] = o[(kz * A + ky) * A + k - 1];
-#pragma unroll
-          for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int kx = 0; kx < 2; ++kx) {
-              ym[a][kx] = o[(a * A - 1) * A + kx];         // (x + kx, y - 1, z + a)
-              yp[a][kx] = o[(a * A + 2) * A + kx];         // (x + kx, y + 2, z + a)
-              zm[a][kx] = o[(-A + a) * A + kx];            // (x + kx, y + a, z - 1)
-              zp[a][kx] = o[(2 * A + a) * A + kx];         // (x + kx, y + a, z + 2)
-            }
-          // E_d = c_d * sum over the eight corners of weight * (phi(+1) - phi(-1)),
-          // the coefficient applied once at the end.
-#pragma unroll
-          for (int kz = 0; kz < 2; ++kz)
-#pragma unroll
-            for (int ky = 0; ky < 2; ++ky) {
-              const T d0 = r[kz][ky][2] - r[kz][ky][0], d1 = r[kz][ky][3] - r[kz][ky][1];
-              ax += wz[kz] * wy[ky] * (wx[0] * d0 + wx[1] * d1);
-            }
-#pragma unroll
-          for (int kz = 0; kz < 2; ++kz)
-#pragma unroll
-            for (int kx = 0; kx < 2; ++kx) {
-              const T d0 = r[kz][1][kx + 1] - ym[kz][kx], d1 = yp[kz][kx] - r[kz][0][kx + 1];
-              ay += wz[kz] * wx[kx] * (wy[0] * d0 + wy[1] * d1);
-            }
-#pragma unroll
-          for (int ky = 0; ky < 2; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 2; ++kx) {
-              const T d0 = r[1][ky][kx + 1] - zm[ky][kx], d1 = zp[ky][kx] - r[0][ky][kx + 1];
-              az += wy[ky] * wx[kx] * (wz[0] * d0 + wz[1] * d1);
-            }
-        } else {
-          const T* o = ph + o_idx;
-          // every stencil node: weight * (phi(+1) - phi(-1)) per axis
-#pragma unroll
-          for (int kz = 0; kz < WD; ++kz)
-#pragma unroll
-            for (int ky = 0; ky < WD; ++ky)
-#pragma unroll
-              for (int kx = 0; kx < WD; ++kx) {
-                const T* q = o + (kz * A + ky) * A + kx;
-                const T wgt = c.wz[kz] * c.wy[ky] * c.wx[kx];
-                ax += wgt * (q[1] - q[-1]);
-                ay += wgt * (q[A] - q[-A]);
-                az += wgt * (q[A * A] - q[-A * A]);
-              }
-        }
+        interp_phi<T, SCH>(ph + o_idx, A, A * A, c, ax, ay, az);
         if constexpr (SOA) {
           so.ex[i] = ax * cx;
           so.ey[i] = ay * cy;
@@ -1096,7 +1113,7 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
                                                               size_t sorted_stride, const float* __restrict__ phi_ext,
                                                               size_t phi_stride, MeshDims m, BinGeom bg,
                                                               SortedOut<float> so) {
-  constexpr int E = field_edge<SCH>(), WD = Scheme<SCH>::width;
+  constexpr int E = field_edge<SCH>();
   static_assert(Scheme<SCH>::lo == 0, "a tile's first stencil node is on the mesh");
   __shared__ float4 ef[E * E * E];
   using P4 = Rec<float>;
@@ -1168,23 +1185,7 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
         const Cell<float, SCH> c = locate<float, SCH>(p.x, p.y, p.z, g, m, bg);
         const float4* o = ef + ((c.bz - bz) * E + (c.by - by)) * E + (c.bx - bx);
         float ax = 0.f, ay = 0.f, az = 0.f;
-#pragma unroll
-        for (int kz = 0; kz < WD; ++kz)
-#pragma unroll
-          for (int ky = 0; ky < WD; ++ky) {
-            const float w = c.wz[kz] * c.wy[ky];
-            float rx = 0.f, ry = 0.f, rz = 0.f;
-#pragma unroll
-            for (int kx = 0; kx < WD; ++kx) {
-              const float4 d = o[(kz * E + ky) * E + kx];
-              rx += c.wx[kx] * d.x;
-              ry += c.wx[kx] * d.y;
-              rz += c.wx[kx] * d.z;
-            }
-            ax += w * rx;
-            ay += w * ry;
-            az += w * rz;
-          }
+        interp_field<SCH>([&](int kz, int ky, int kx) { return o[(kz * E + ky) * E + kx]; }, c, ax, ay, az);
         if constexpr (SOA) {
           so.ex[i] = ax * cx;
           so.ey[i] = ay * cy;
@@ -1304,6 +1305,82 @@ __global__ __launch_bounds__(kUnsortThreads) void k_unsort(ElemBatch eb, const c
       }
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Small solves without binning.  Below about half a million node updates the
+// binned path is a chain of launches with little to do in each; here every
+// particle adds its weights straight into the mesh with device atomics and
+// reads its field straight from phi.  The weights are added as the binned
+// deposit's fixed-point integers to one 64-bit total per node (exact, like a
+// work item's sums; the x pass converts them as it reads).  One particle per
+// lane, one wavefront per workgroup, so that 1e4 particles reach most CUs.
+// ---------------------------------------------------------------------------
+constexpr int kDirectThreads = 64;
+template <typename T, int SCH>
+__global__ __launch_bounds__(kDirectThreads) void k_deposit_direct(ElemBatch eb, const Geometry* geo, size_t stride,
+                                                                   unsigned long long* mesh, size_t mesh_stride,
+                                                                   MeshDims m,
+                                                                   BinGeom bg) {
+  constexpr int WD = Scheme<SCH>::width;
+  const int b = blockIdx.y;
+  const dks_particle_set e = eb.at(b);
+  const int64_t n = eb.n(e);
+  const int64_t i = (int64_t)blockIdx.x * kDirectThreads + threadIdx.x;
+  const Geometry* g = geo_of(geo, stride, b);
+  if (i >= n) return;
+  const Cell<T, SCH> c = locate<T, SCH>(((const T*)e.x)[i], ((const T*)e.y)[i], ((const T*)e.z)[i], g, m, bg);
+  const bool out = c.key == bg.K;
+  const unsigned long long outs = __ballot(out);
+  if (outs && (int)__lane_id() == __ffsll((long long)__ballot(1)) - 1) {
+    atomicAdd(&const_cast<Geometry*>(g)->n_outside, (unsigned long long)__popcll(outs));
+    if (e.n_outside) atomicAdd((unsigned long long*)e.n_outside, (unsigned long long)__popcll(outs));
+  }
+  if (out) return;
+  unsigned long long* total = mesh + (size_t)b * mesh_stride;
+#pragma unroll
+  for (int kz = 0; kz < WD; ++kz)
+#pragma unroll
+    for (int ky = 0; ky < WD; ++ky) {
+      const T zy = c.wz[kz] * c.wy[ky];
+      const size_t row = ((size_t)(c.bz + kz) * m.ny + (c.by + ky)) * m.nx + c.bx;
+#pragma unroll
+      for (int kx = 0; kx < WD; ++kx)
+        atomicAdd(total + row + kx, Fixed<T>::to(zy * (c.wx[kx] * Fixed<T>::scale)));
+    }
+}
+
+template <typename T, int SCH>
+__global__ __launch_bounds__(kDirectThreads) void k_gather_direct(ElemBatch eb, const Geometry* geo, size_t stride,
+                                                                  const T* __restrict__ phi_ext, size_t phi_stride,
+                                                                  MeshDims m, BinGeom bg) {
+  const int b = blockIdx.y;
+  const dks_particle_set e = eb.at(b);
+  const int64_t n = eb.n(e);
+  const int64_t i = (int64_t)blockIdx.x * kDirectThreads + threadIdx.x;
+  if (i >= n) return;
+  const Geometry* g = geo_of(geo, stride, b);
+  const Cell<T, SCH> c = locate<T, SCH>(((const T*)e.x)[i], ((const T*)e.y)[i], ((const T*)e.z)[i], g, m, bg);
+  T ax = 0, ay = 0, az = 0;
+  if (c.key != bg.K) {
+    const int sy = m.nx + 2, sz = (m.nx + 2) * (m.ny + 2);
+    // phi_ext index = node + 1 per axis
+    const T* o = phi_ext + (size_t)b * phi_stride + (size_t)(c.bz + 1) * sz + ((c.by + 1) * sy + c.bx + 1);
+    // the arithmetic of the binned gather of this dtype and scheme
+    if constexpr (sizeof(T) == 4 && SCH != kSchemeTSC) {
+      interp_field<SCH>(
+          [&](int kz, int ky, int kx) {
+            const T* q = o + kz * sz + ky * sy + kx;
+            return make_float4(q[1] - q[-1], q[sy] - q[-sy], q[sz] - q[-sz], 0.f);
+          },
+          c, ax, ay, az);
+    } else {
+      interp_phi<T, SCH>(o, sy, sz, c, ax, ay, az);
+    }
+  }
+  ((T*)e.Ex)[i] = ax * Geo<T>::grad(g, 0);
+  ((T*)e.Ey)[i] = ay * Geo<T>::grad(g, 1);
+  ((T*)e.Ez)[i] = az * Geo<T>::grad(g, 2);
 }
 
 // ---------------------------------------------------------------------------
@@ -1439,11 +1516,15 @@ hipError_t launch_deposit_binned(const Geometry* geo, size_t stride, char* slot_
 
 template <typename T>
 hipError_t launch_fixed_to_weights(const void* iacc, size_t ia_stride, void* W, size_t w_stride, size_t nmesh,
-                                   int batch, hipStream_t s) {
+                                   int batch, bool wide, hipStream_t s) {
   if (nmesh == 0) return hipSuccess;
   const unsigned blocks = (unsigned)std::min<size_t>((nmesh + 255) / 256, 8192);
-  hipLaunchKernelGGL(k_fixed_to_weights<T>, dim3(blocks, batch), dim3(256), 0, s,
-                     (const unsigned long long*)iacc, ia_stride, (T*)W, w_stride, nmesh);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks, batch), dim3(256), 0, s, (const unsigned long long*)iacc, ia_stride, (T*)W,
+                       w_stride, nmesh);
+  };
+  if (wide) go(k_fixed_to_weights<T, true>);
+  else go(k_fixed_to_weights<T, false>);
   return hipGetLastError();
 }
 
@@ -1504,6 +1585,52 @@ hipError_t launch_unsort(const ElemBatch& eb, int batch, const char* sorted_base
   return hipGetLastError();
 }
 
+// Where a solve deposits and gathers without binning.
+//
+// Deposit: scattered device atomics come to about 7e9 a second where many
+// particles share a node (32^3 halo bunch) and 2e10 on sparse meshes, the
+// count, scan, scatter and binned deposit to 25 us and more.  Measured, direct
+// against binned (whole step, FP32 CIC): 1e4 particles 42 against 65 us on
+// 32^3, 48 / 75 on 64^3, 91 / 130 on 128^3; 3.2e4 67 / 74, 62 / 83, 102 / 133;
+// 6.6e4 105 / 78 on 32^3.  FP64 totals hold 2^15 weights of at most 1 on their
+// scale of 2^49.
+//
+// Gather: its reads of phi by random particles cost 1.4 (32^3) to 5.3 us
+// (128^3) per 2^16 particles, the binned gather with its unsort about 20 us up
+// to a few 1e5 particles.
+bool direct_deposit_fits(const ElemBatch& eb, int batch, bool f64, const MeshDims& m, const BinGeom& bg) {
+  const int64_t w = bg.scheme == kSchemeNGP ? 1 : bg.scheme == kSchemeTSC ? 27 : 8;
+  const int64_t n = eb.max_np;
+  return n < (f64 ? 1 << 15 : 1 << 18) && n * w <= (1 << 18) && n * batch * w <= (1 << 19) &&
+         n <= 2 * (int64_t)m.nx * m.ny * m.nz;
+}
+bool direct_gather_fits(const ElemBatch& eb, int batch) { return eb.max_np <= (1 << 18) / batch; }
+
+template <typename T>
+hipError_t launch_deposit_direct(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, void* mesh,
+                                 size_t mesh_stride, const MeshDims& m, const BinGeom& bg, hipStream_t s) {
+  if (eb.max_np == 0) return hipSuccess;
+  const dim3 grid((unsigned)((eb.max_np + kDirectThreads - 1) / kDirectThreads), batch);
+  with_scheme(bg.scheme, [&](auto sc) {
+    hipLaunchKernelGGL((k_deposit_direct<T, decltype(sc)::value>), grid, dim3(kDirectThreads), 0, s, eb, geo, stride,
+                       (unsigned long long*)mesh, mesh_stride / sizeof(unsigned long long), m, bg);
+  });
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_gather_direct(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride,
+                                const void* phi_ext, size_t phi_stride, const MeshDims& m, const BinGeom& bg,
+                                hipStream_t s) {
+  if (eb.max_np == 0) return hipSuccess;
+  const dim3 grid((unsigned)((eb.max_np + kDirectThreads - 1) / kDirectThreads), batch);
+  with_scheme(bg.scheme, [&](auto sc) {
+    hipLaunchKernelGGL((k_gather_direct<T, decltype(sc)::value>), grid, dim3(kDirectThreads), 0, s, eb, geo, stride,
+                       (const T*)phi_ext, phi_stride, m, bg);
+  });
+  return hipGetLastError();
+}
+
 #define DKS_INSTANTIATE(T)                                                                                         \
   template hipError_t launch_bin_count<T>(const ElemBatch&, int, const Geometry*, size_t, char*, size_t, const MeshDims&,            \
                                           const BinGeom&, int, hipStream_t);                                       \
@@ -1513,11 +1640,15 @@ hipError_t launch_unsort(const ElemBatch& eb, int batch, const char* sorted_base
   template hipError_t launch_deposit_binned<T>(const Geometry*, size_t, char*, size_t, const char*, size_t, void*, \
                                                size_t, const MeshDims&, const BinGeom&, int, int, void* const*,    \
                                                void*, size_t, hipStream_t);                                        \
-  template hipError_t launch_fixed_to_weights<T>(const void*, size_t, void*, size_t, size_t, int, hipStream_t);   \
+  template hipError_t launch_fixed_to_weights<T>(const void*, size_t, void*, size_t, size_t, int, bool, hipStream_t); \
   template hipError_t launch_gather_binned<T>(const Geometry*, size_t, char*, size_t, char*, size_t,               \
                                               const void*, size_t, const MeshDims&, const BinGeom&, int, int,      \
                                               void* const*, hipStream_t);                                          \
-  template hipError_t launch_unsort<T>(const ElemBatch&, int, const char*, size_t, size_t, hipStream_t);
+  template hipError_t launch_unsort<T>(const ElemBatch&, int, const char*, size_t, size_t, hipStream_t);           \
+  template hipError_t launch_deposit_direct<T>(const ElemBatch&, int, const Geometry*, size_t, void*, size_t,      \
+                                               const MeshDims&, const BinGeom&, hipStream_t);                      \
+  template hipError_t launch_gather_direct<T>(const ElemBatch&, int, const Geometry*, size_t, const void*, size_t, \
+                                              const MeshDims&, const BinGeom&, hipStream_t);
 DKS_INSTANTIATE(float)
 DKS_INSTANTIATE(double)
 #undef DKS_INSTANTIATE

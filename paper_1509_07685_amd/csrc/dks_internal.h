@@ -238,6 +238,25 @@ __device__ __forceinline__ bool axis_stencil(T s, int n, int& node, T* w) {
   }
 }
 
+// Fixed-point scale of the deposit accumulators: a weight is at most 1 and a
+// work item holds at most 2^16 (FP32) or 2^14 (FP64) particles, so a node sum
+// stays below 2^47 resp. 2^63 in 64 bits; the scale keeps 2^-31 resp. 2^-49
+// resolution, finer than the dtype's rounding of the weight products.  The
+// scale is a power of two, folded exactly into one factor of each product;
+// to() takes the scaled weight (an FP32 one fits 32 bits: one rounding
+// conversion instead of a 64-bit one).
+template <typename T> struct Fixed;
+template <> struct Fixed<float> {
+  static constexpr float scale = 2147483648.0f;   // 2^31
+  static __device__ __forceinline__ unsigned long long to(float ws) { return (unsigned long long)__float2uint_rn(ws); }
+  static __device__ __forceinline__ float from(unsigned long long v) { return (float)v * 4.656612873077393e-10f; }
+};
+template <> struct Fixed<double> {
+  static constexpr double scale = 562949953421312.0;   // 2^49
+  static __device__ __forceinline__ unsigned long long to(double ws) { return __double2ull_rn(ws); }
+  static __device__ __forceinline__ double from(unsigned long long v) { return (double)v * 1.7763568394002505e-15; }
+};
+
 // Arguments of the per-solve geometry kernel.
 struct GeoArgs {
   int n[3];
@@ -272,6 +291,9 @@ struct BinGeom {
 // pure function of the chunk index; results do not depend on the hardware's
 // actual placement.)
 constexpr int kXcd = 8;
+
+// Offset of the inverse permutation in the particle scratch when none is wanted.
+constexpr size_t kNoInverse = ~(size_t)0;
 
 // Per-slot bin bookkeeping (uint32), L = K + 1 tiles (tile K: outside):
 // xcount[kXcd][L] (cleared by the geometry kernel), count[L], offset[L+1],

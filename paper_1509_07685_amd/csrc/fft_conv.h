@@ -62,12 +62,15 @@ template <typename T> constexpr int kBlockCols = 128 / (2 * (int)sizeof(T));
 // z[m] = x[2m] + i x[2m+1], then X[k] = (Z[k] + conj Z[nx-k]) / 2
 // - i w^k (Z[k] - conj Z[nx-k]) / 2 with w = exp(-2 pi i / 2nx).
 // ---------------------------------------------------------------------------
+// form: rows of reals, read one by one or as pairs, or rows of the small-solve
+// deposit's 64-bit fixed-point node totals.
+enum : int { kRowReals = 0, kRowPairs = 1, kRowFixed = 2 };
 template <typename T, class SP>
 __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_x_fwd(const T* __restrict__ in, size_t in_stride,
                                                         typename Cplx<T>::type* __restrict__ out,
                                                         size_t out_stride, MeshDims m, const FFTPlan* __restrict__ P,
                                                         const typename Cplx<T>::type* __restrict__ post,
-                                                        int nrows, unsigned magic_out, unsigned magic_nx, int pairs) {
+                                                        int nrows, unsigned magic_out, unsigned magic_nx, int form) {
   using C = typename Cplx<T>::type;
   constexpr int TH = block_threads<T, SP>();
   extern __shared__ __align__(16) unsigned char smem[];
@@ -91,7 +94,13 @@ __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_x_fwd(const T*
     if (p < nvalid) {
       C v[KI];
       const T* srow = src + (size_t)(row0 + p) * N;
-      if (pairs) {
+      if (form == kRowFixed) {
+        const unsigned long long* frow = reinterpret_cast<const unsigned long long*>(src) + (size_t)(row0 + p) * N;
+#pragma unroll
+        for (int i = 0; i < KI; ++i)
+          if (NP % LPR == 0 || l + LPR * i < NP)
+            v[i] = C{(T)Fixed<T>::from(frow[2 * (l + LPR * i)]), (T)Fixed<T>::from(frow[2 * (l + LPR * i) + 1])};
+      } else if (form == kRowPairs) {
 #pragma unroll
         for (int i = 0; i < KI; ++i)
           if (NP % LPR == 0 || l + LPR * i < NP) v[i] = reinterpret_cast<const C*>(srow)[l + LPR * i];
@@ -140,7 +149,10 @@ __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_x_fwd(const T*
 #pragma unroll
       for (int k = 0; k < KL; ++k) {
         const int e = (int)threadIdx.x + k * TH;
-        v[k] = e < total ? tsrc[e] : (T)0;
+        v[k] = e >= total ? (T)0
+               : form == kRowFixed
+                   ? (T)Fixed<T>::from(reinterpret_cast<const unsigned long long*>(src)[(size_t)row0 * nx + e])
+                   : tsrc[e];
       }
 #pragma unroll
       for (int k = 0; k < KL; ++k) {
@@ -975,20 +987,21 @@ __global__ __launch_bounds__(256) void k_fft_x_inv_wave(const typename Cplx<T>::
 }
 
 template <typename T>
-hipError_t launch_fft_x_fwd(const void* in, size_t in_stride, void* out, size_t out_stride, const MeshDims& m,
-                            const PlanRef& P, const void* post, int batch, hipStream_t s) {
+hipError_t launch_fft_x_fwd(const void* in, size_t in_stride, bool fixed, void* out, size_t out_stride,
+                            const MeshDims& m, const PlanRef& P, const void* post, int batch, hipStream_t s) {
   using C = typename Cplx<T>::type;
   const int nrows = m.ny * m.nz;
   if ((size_t)P.host.W * m.nx > (size_t)kTileReals * RegCfg<T>::THREADS) return hipErrorInvalidValue;
   dim3 grid((nrows + P.host.W - 1) / P.host.W, batch);
   // compile-time plans read pairs of reals as one complex value where they can
-  const int pairs = (reinterpret_cast<uintptr_t>(in) % (2 * sizeof(T))) == 0 &&
-                    (in_stride * sizeof(T)) % (2 * sizeof(T)) == 0;
+  const bool pairs = (reinterpret_cast<uintptr_t>(in) % (2 * sizeof(T))) == 0 &&
+                     (in_stride * sizeof(T)) % (2 * sizeof(T)) == 0;
+  const int form = fixed ? kRowFixed : pairs ? kRowPairs : kRowReals;
   with_plan<T, 1, true>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_x_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()),
                        lds_bytes<T>(P.host) + (size_t)(m.nx + 1) * sizeof(C), s,
                        (const T*)in, in_stride, (C*)out, out_stride, m, P.dev, (const C*)post, nrows, magic_of(m.nx + 1),
-                       magic_of(m.nx), pairs);
+                       magic_of(m.nx), form);
   });
   return hipGetLastError();
 }

@@ -20,8 +20,8 @@ hipError_t launch_store_plans(const FFTPlan* four, FFTPlan* dev, hipStream_t s) 
 }
 
 #define DKS_INSTANTIATE(T) \
-  template hipError_t launch_fft_x_fwd<T>(const void*, size_t, void*, size_t, const MeshDims&, const PlanRef&, \
-                                          const void*, int, hipStream_t);                                      \
+  template hipError_t launch_fft_x_fwd<T>(const void*, size_t, bool, void*, size_t, const MeshDims&,           \
+                                          const PlanRef&, const void*, int, hipStream_t);                      \
   template hipError_t launch_fft_x_inv<T>(const void*, size_t, void*, size_t, const ElemBatch&, const MeshDims&, \
                                           const PlanRef&, const void*, int, hipStream_t);
 DKS_INSTANTIATE(float)

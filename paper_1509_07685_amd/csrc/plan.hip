@@ -18,7 +18,7 @@
 namespace dks {
 
 // Launchers defined in the kernel translation units.
-template <typename T> hipError_t launch_fft_x_fwd(const void*, size_t, void*, size_t, const MeshDims&,
+template <typename T> hipError_t launch_fft_x_fwd(const void*, size_t, bool, void*, size_t, const MeshDims&,
                                                   const PlanRef&, const void*, int, hipStream_t);
 template <typename T> hipError_t launch_fft_y_fwd(const void*, void*, size_t, const MeshDims&, const PlanRef&, int, int,
                                                   int, hipStream_t);
@@ -51,11 +51,17 @@ template <typename T> hipError_t launch_bin_scatter(const ElemBatch&, int, const
 template <typename T> hipError_t launch_deposit_binned(const Geometry*, size_t, char*, size_t, const char*, size_t,
                                                        void*, size_t, const MeshDims&, const BinGeom&, int, int, void* const*,
                                                        void*, size_t, hipStream_t);
-template <typename T> hipError_t launch_fixed_to_weights(const void*, size_t, void*, size_t, size_t, int, hipStream_t);
+template <typename T> hipError_t launch_fixed_to_weights(const void*, size_t, void*, size_t, size_t, int, bool, hipStream_t);
 template <typename T> hipError_t launch_gather_binned(const Geometry*, size_t, char*, size_t, char*, size_t,
                                                       const void*, size_t, const MeshDims&, const BinGeom&, int, int,
                                                       void* const*, hipStream_t);
 template <typename T> hipError_t launch_unsort(const ElemBatch&, int, const char*, size_t, size_t, hipStream_t);
+bool direct_deposit_fits(const ElemBatch&, int, bool, const MeshDims&, const BinGeom&);
+bool direct_gather_fits(const ElemBatch&, int);
+template <typename T> hipError_t launch_deposit_direct(const ElemBatch&, int, const Geometry*, size_t, void*, size_t,
+                                                       const MeshDims&, const BinGeom&, hipStream_t);
+template <typename T> hipError_t launch_gather_direct(const ElemBatch&, int, const Geometry*, size_t, const void*,
+                                                      size_t, const MeshDims&, const BinGeom&, hipStream_t);
 template <typename T> hipError_t launch_twiddle_pass(void*, int, int, hipStream_t);
 template <typename T> hipError_t launch_twiddle_line(void*, int, int, hipStream_t);
 hipError_t launch_igf_octant(double*, const int*, const double*, const GLBands&, int, hipStream_t);
@@ -414,10 +420,11 @@ struct Slots {
   Geometry* geo() const { return reinterpret_cast<Geometry*>(base); }
 };
 
-// rho (in `src`, element stride in_stride) -> phi_ext in R3 (+ user phi) via the five passes.
+// rho (in `src`, element stride in_stride; fixed: the direct deposit's node
+// totals) -> phi_ext in R3 (+ user phi) via the five passes.
 template <typename T>
-dks_status convolve(const dks_poisson_plan_s* p, const void* src, size_t in_stride, int batch, const Slots& sl,
-                    const ElemBatch& phi_user, hipStream_t st) {
+dks_status convolve(const dks_poisson_plan_s* p, const void* src, size_t in_stride, bool fixed, int batch,
+                    const Slots& sl, const ElemBatch& phi_user, hipStream_t st) {
   const MeshDims& m = p->md;
   const size_t cstride = sl.stride / p->csize;
   const size_t rstride = sl.stride / p->rsize;
@@ -430,7 +437,7 @@ dks_status convolve(const dks_poisson_plan_s* p, const void* src, size_t in_stri
   const PlanRef fzi = planref(p, 3);
   const void* post = p->ws + p->tw_post;
   const void* G = p->ws + p->off_green;
-  DKS_TK("fft_x_fwd", launch_fft_x_fwd<T>(src, in_stride, R1, cstride, m, fx, post, batch, st));
+  DKS_TK("fft_x_fwd", launch_fft_x_fwd<T>(src, in_stride, fixed, R1, cstride, m, fx, post, batch, st));
   DKS_TK("fft_y_fwd", launch_fft_y_fwd<T>(R1, R2, cstride, m, fy, batch, 0, m.ncols, st));
   DKS_TK("fft_z_conv", launch_fft_z_conv<T>(R2, R1, cstride, G, sl.geo(), sl.stride, m, fz, fzi, batch, 0, m.ncols, st));
   DKS_TK("fft_y_inv", launch_fft_y_inv<T>(R1, R2, cstride, m, fy, batch, 0, m.ncols, st));
@@ -493,11 +500,18 @@ PartWork part_work(const dks_poisson_plan_s* p, int64_t maxn) {
   return w;
 }
 
+// Small solves deposit without binning (k_deposit_direct), except where the
+// binned order or the order-independent totals are asked for.
+bool deposit_direct(const dks_poisson_plan_s* p, int batch, const ElemBatch& eb, bool sorted) {
+  return !sorted && !p->deterministic && direct_deposit_fits(eb, batch, p->dtype == DKS_F64, p->md, p->bg);
+}
+
 // Mesh fit (fitted plans), geometry, particle binning and the binned deposit:
 // leaves the weights W in R3 and the binned particles in `sorted` (or, soa,
-// in the caller's output position arrays soa[0..2]).
+// in the caller's output position arrays soa[0..2]).  direct: no binning;
+// 64-bit fixed-point node totals are left in R2 instead of W.
 template <typename T>
-dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl, const ElemBatch& eb,
+dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl, const ElemBatch& eb, bool direct,
                          char* sorted, size_t sorted_stride, size_t inv_off, const PartWork& w,
                          hipStream_t st, void* const* soa = nullptr) {
   int nb = 0;
@@ -505,15 +519,19 @@ dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl
   if (p->fitted) DKS_TK("bbox", launch_bbox<T>(eb, batch, bbox, sl.stride / sizeof(double), &nb, st));
   GeoArgs ga = geo_args(p, 1, nb);
   ga.zero_off = p->s_bins;                  // the per-group tile counts
-  ga.zero_len = kXcd * (p->bg.K + 1);
+  ga.zero_len = direct ? 0 : kXcd * (p->bg.K + 1);
   // The order-independent deposit sums into integer node totals in R2
   // (free until the forward y pass) and forms W from them afterwards.
   const size_t nmesh = (size_t)p->n[0] * p->n[1] * p->n[2];
-  char* iacc = p->deterministic ? sl.base + p->s_r2 : nullptr;
-  const size_t iacc_bytes = nmesh * (sizeof(T) == 4 ? 8 : 16);
+  char* iacc = p->deterministic || direct ? sl.base + p->s_r2 : nullptr;
+  const size_t iacc_bytes = nmesh * (sizeof(T) == 4 || direct ? 8 : 16);
   DKS_TK("geometry", launch_geometry_zero(bbox, sl.stride / sizeof(double), sl.geo(), sl.stride, ga, eb, batch,
                                           iacc ? iacc : sl.base + p->s_r3, sl.stride, iacc ? iacc_bytes : p->bytes_W,
                                           st));
+  if (direct) {
+    DKS_TK("deposit", launch_deposit_direct<T>(eb, batch, sl.geo(), sl.stride, iacc, sl.stride, p->md, w.bg, st));
+    return DKS_OK;
+  }
   DKS_TK("bin_count", launch_bin_count<T>(eb, batch, sl.geo(), sl.stride, sl.base, p->s_bins, p->md, w.bg,
                                           w.count_blocks, st));
   DKS_TK("bin_scan", launch_bin_scan(sl.geo(), sl.stride, sl.base, p->s_bins, w.bg, eb, batch, st));
@@ -525,7 +543,7 @@ dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl
   if (iacc)
     DKS_TK("fixed_to_weights", launch_fixed_to_weights<T>(iacc, sl.stride / sizeof(unsigned long long),
                                                           sl.base + p->s_r3, sl.stride / sizeof(T), nmesh, batch,
-                                                          st));
+                                                          sizeof(T) == 8, st));
   return DKS_OK;
 }
 
@@ -538,11 +556,19 @@ template <typename T>
 dks_status solve_particles_t(const dks_poisson_plan_s* p, int batch, const Slots& sl, const ElemBatch& eb,
                              char* sorted, size_t sorted_stride, hipStream_t st, void* const* sorted_out = nullptr) {
   const PartWork w = part_work(p, eb.max_np);
-  const size_t inv_off = inv_offset(p, eb.max_np);
-  dks_status r = deposit_stage<T>(p, batch, sl, eb, sorted, sorted_stride, inv_off, w, st, sorted_out);
+  const bool direct = deposit_direct(p, batch, eb, sorted_out != nullptr);
+  // gathered in the input order: no permutation and no unsort
+  const bool in_order = !sorted_out && (direct || direct_gather_fits(eb, batch));
+  const size_t inv_off = in_order ? kNoInverse : inv_offset(p, eb.max_np);
+  dks_status r = deposit_stage<T>(p, batch, sl, eb, direct, sorted, sorted_stride, inv_off, w, st, sorted_out);
   if (r != DKS_OK) return r;
-  r = convolve<T>(p, sl.base + p->s_r3, sl.stride / sizeof(T), batch, sl, eb, st);
+  r = convolve<T>(p, sl.base + (direct ? p->s_r2 : p->s_r3), sl.stride / sizeof(T), direct, batch, sl, eb, st);
   if (r != DKS_OK) return r;
+  if (in_order) {
+    DKS_TK("gather", launch_gather_direct<T>(eb, batch, sl.geo(), sl.stride, sl.base + p->s_r3, sl.stride / sizeof(T),
+                                             p->md, w.bg, st));
+    return DKS_OK;
+  }
   DKS_TK("gather", launch_gather_binned<T>(sl.geo(), sl.stride, sl.base, p->s_bins, sorted, sorted_stride,
                                            sl.base + p->s_r3, sl.stride / sizeof(T), p->md, w.bg, w.gitem_blocks,
                                            batch, sorted_out, st));
@@ -626,14 +652,14 @@ dks_status solve_rho_dev(dks_poisson_plan_s* p, const void* rho, void* phi, void
   const ElemBatch out = single(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, phi, nullptr, 0, 0.0, false);
   dks_status r;
   if (p->dtype == DKS_F32) {
-    r = convolve<float>(p, rho, 0, 1, sl, out, st);
+    r = convolve<float>(p, rho, 0, false, 1, sl, out, st);
     if (r == DKS_OK && E_mesh) {
       Timed tm("gradient", st);
       r = hip_status(launch_gradient<float>(sl.base + p->s_r3, E_mesh, sl.geo(), p->md, st));
       tm.done();
     }
   } else {
-    r = convolve<double>(p, rho, 0, 1, sl, out, st);
+    r = convolve<double>(p, rho, 0, false, 1, sl, out, st);
     if (r == DKS_OK && E_mesh) {
       Timed tm("gradient", st);
       r = hip_status(launch_gradient<double>(sl.base + p->s_r3, E_mesh, sl.geo(), p->md, st));
@@ -1050,12 +1076,17 @@ dks_status dks_poisson_deposit(dks_poisson_plan_t p, const void* x, const void* 
   const ElemBatch eb = single(x, y, z, nullptr, nullptr, nullptr, nullptr, n_outside, np, q, false);
   const PartWork w = part_work(p, np);
   const size_t nmesh = (size_t)p->n[0] * p->n[1] * p->n[2];
+  const bool direct = deposit_direct(p, 1, eb, false);
   dks_status r;
   if (p->dtype == DKS_F32) {
-    r = deposit_stage<float>(p, 1, sl, eb, p->pscratch, 0, inv_offset(p, np), w, st);
+    r = deposit_stage<float>(p, 1, sl, eb, direct, p->pscratch, 0, kNoInverse, w, st);
+    if (r == DKS_OK && direct)
+      r = hip_status(launch_fixed_to_weights<float>(sl.base + p->s_r2, 0, sl.base + p->s_r3, 0, nmesh, 1, false, st));
     if (r == DKS_OK) r = hip_status(launch_weights_to_density<float>(sl.base + p->s_r3, rho, nmesh, sl.geo(), q, st));
   } else {
-    r = deposit_stage<double>(p, 1, sl, eb, p->pscratch, 0, inv_offset(p, np), w, st);
+    r = deposit_stage<double>(p, 1, sl, eb, direct, p->pscratch, 0, kNoInverse, w, st);
+    if (r == DKS_OK && direct)
+      r = hip_status(launch_fixed_to_weights<double>(sl.base + p->s_r2, 0, sl.base + p->s_r3, 0, nmesh, 1, false, st));
     if (r == DKS_OK) r = hip_status(launch_weights_to_density<double>(sl.base + p->s_r3, rho, nmesh, sl.geo(), q, st));
   }
   if (r == DKS_OK) p->has_geometry = true;
