@@ -17,7 +17,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libdks_poisson.so")
-SOURCES = ["fft_kernels_z64.hip", "fft_kernels_z32.hip", "fft_kernels_y.hip", "fft_kernels.hip", "fft_raw.hip", "particle_kernels.hip", "bin_kernels.hip", "greens_kernels.hip",
+SOURCES = ["fft_kernels_z64.hip", "fft_kernels_z32.hip", "fft_kernels_y.hip", "fft_kernels.hip",
+           "fft_raw_f32.hip", "fft_raw_f64.hip", "fft_raw.hip", "particle_kernels.hip", "bin_kernels.hip", "greens_kernels.hip",
            "plan.hip", "musr_kernels.hip"]
 ARCH = "gfx950"
 

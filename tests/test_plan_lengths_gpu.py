@@ -115,3 +115,40 @@ def test_raw_lengths(n, dt):
         torch.cuda.synchronize()
         assert rel_l2(H.cpu().numpy(), fo.rdft3(r.cpu().numpy())) <= FFT_TOL[dt], shape
         assert rel_l2(y.cpu().numpy() / (nx * ny * nz), r.cpu().numpy()) <= FFT_TOL[dt], shape
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("n,batch", [((256, 256, 128), 1), ((162, 243, 216), 1), ((48, 128, 128), 16)])
+def test_raw_wide_column_tiles(n, batch, dt):
+    """Arrays of 64 MiB and more run columns of up to 256 elements in wider
+    tiles; the last tile of a row or plane may be ragged."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n[0])
+    x = torch.randn((batch, n[2], n[1], n[0]), generator=g, dtype=CDT[dt], device="cuda")
+    plan = dks().FFTPlan(n, batch, "c2c", dt)
+    X = plan.forward(x)
+    ref = torch.fft.fftn(x.to(torch.complex128), dim=(1, 2, 3))
+    assert float((X - ref).abs().norm() / ref.norm()) <= FFT_TOL[dt]
+    y = plan.inverse(X) / (n[0] * n[1] * n[2])
+    assert float((y - x).norm() / x.norm()) <= FFT_TOL[dt]
+    r = x.real.contiguous()
+    plan = dks().FFTPlan(n, batch, "r2c", dt)
+    H = plan.forward(r)
+    ref = torch.fft.rfftn(r.double(), dim=(1, 2, 3))
+    assert float((H - ref).abs().norm() / ref.norm()) <= FFT_TOL[dt]
+    assert float((plan.inverse(H) / (n[0] * n[1] * n[2]) - r).norm() / r.norm()) <= FFT_TOL[dt]
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_raw_real_rows_at_an_odd_element_offset(dt):
+    """Real arrays whose address is not a multiple of a pair of reals."""
+    n = (48, 6, 4)
+    buf = torch.from_numpy(np.random.default_rng(4).standard_normal(2 * 48 * 24 + 1)).to(RDT[dt]).cuda()
+    x = buf[1:].view(2, 4, 6, 48)
+    out = torch.zeros_like(buf)[1:].view(2, 4, 6, 48)
+    plan = dks().FFTPlan(n, 2, "r2c", dt)
+    H = plan.forward(x)
+    plan.inverse(H, out=out)
+    torch.cuda.synchronize()
+    assert rel_l2(H.cpu().numpy(), fo.rdft3(x.cpu().numpy())) <= FFT_TOL[dt]
+    assert rel_l2(out.cpu().numpy() / (48 * 24), x.cpu().numpy()) <= FFT_TOL[dt]
