@@ -122,10 +122,10 @@ __device__ __forceinline__ BinState bin_state(char* slot_base, size_t stride, si
   const int L = K + 1;
   unsigned* p = reinterpret_cast<unsigned*>(slot_base + (size_t)b * stride + off);
   s.xcount = p;
-  s.count = p + kXcd * L;
+  s.xcursor = p + kXcd * L;
+  s.count = s.xcursor + kXcd * L;
   s.offset = s.count + L;
-  s.xcursor = s.offset + L + 1;
-  s.item_off = s.xcursor + kXcd * L;
+  s.item_off = s.offset + L + 1;
   s.gitem_off = s.item_off + L + 1;
   s.misc = s.gitem_off + L + 1;
   return s;
@@ -303,11 +303,11 @@ __device__ __forceinline__ void scan1024(unsigned (&v)[N], unsigned (*ws)[16], u
 // 8192 tiles, e.g. a 320^3 mesh) its counts stay in registers and all its
 // loads are issued together.
 constexpr int kScanRun = 8;
-__global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t stride, char* slot_base,
-                                                   size_t bins_off, BinGeom bg, ElemBatch eb) {
-  __shared__ unsigned ws[3][16];
-  const int b = blockIdx.x;
-  BinState st = bin_state(slot_base, stride, bins_off, b, bg.K);
+// CURSORS: store the cursors (else the scatter's workgroups form their own
+// group's bases and the cursors stay counts from 0).
+template <bool CURSORS>
+__device__ __forceinline__ void scan_tiles(const BinState& st, const BinGeom& bg, unsigned (*ws)[16], Geometry* geo,
+                                           int64_t* cnt) {
   const int L = bg.K + 1;
   const int per = (L + 1023) / 1024;
   const int lo = min((int)threadIdx.x * per, L), hi = min(lo + per, L);
@@ -321,11 +321,13 @@ __global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t s
   };
   auto store = [&](int k) {
     st.offset[k] = run[0];
-    unsigned cur = run[0];
+    if constexpr (CURSORS) {
+      unsigned cur = run[0];
 #pragma unroll
-    for (int x = 0; x < kXcd; ++x) {
-      st.xcursor[x * L + k] = cur;
-      cur += st.xcount[x * L + k];
+      for (int x = 0; x < kXcd; ++x) {
+        st.xcursor[x * L + k] = cur;
+        cur += st.xcount[x * L + k];
+      }
     }
     st.item_off[k] = run[1];
     st.gitem_off[k] = run[2];
@@ -379,11 +381,17 @@ __global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t s
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long outside = st.count[bg.K];
-    int64_t* cnt = eb.at(b).n_outside;
-    Geometry* gw = const_cast<Geometry*>(geo_of(geo, stride, b));
-    gw->n_outside = outside;
+    geo->n_outside = outside;
     if (cnt) *cnt = (int64_t)outside;
   }
+}
+
+__global__ __launch_bounds__(1024) void k_bin_scan(const Geometry* geo, size_t stride, char* slot_base,
+                                                   size_t bins_off, BinGeom bg, ElemBatch eb) {
+  __shared__ unsigned ws[3][16];
+  const int b = blockIdx.x;
+  scan_tiles<true>(bin_state(slot_base, stride, bins_off, b, bg.K), bg, ws,
+                   const_cast<Geometry*>(geo_of(geo, stride, b)), eb.at(b).n_outside);
 }
 
 // ---------------------------------------------------------------------------
@@ -437,10 +445,12 @@ constexpr int kStageRun = 8;
 struct NoMid {
   __device__ void operator()() const {}
 };
+// base: NULL when the cursors run from the tiles' reserved starts, else the
+// lane's own tiles' starts, to be added to cursors that run from 0.
 template <typename T, bool FULL, class RecOut, class Mid = NoMid, int PER = chunk_per<T, kScatterThreads>()>
 __device__ __forceinline__ void scatter_stage_chunk(unsigned* lcnt, unsigned* lbase, Rec<T>* srec,
                                                     unsigned short* skey, unsigned (*ws)[16],
-                                                    unsigned* cursor, const BinGeom& bg, const int (&key)[PER],
+                                                    unsigned* cursor, const unsigned* base, const BinGeom& bg, const int (&key)[PER],
                                                     const unsigned (&rank)[PER], const T (&xs)[PER],
                                                     const T (&ys)[PER], const T (&zs)[PER], int64_t c0, int64_t n,
                                                     bool vec, const RecOut& out, unsigned* inv, Mid mid = Mid{}) {
@@ -467,7 +477,7 @@ __device__ __forceinline__ void scatter_stage_chunk(unsigned* lcnt, unsigned* lb
   for (int q = 0; q < kStageRun; ++q) {
     if (lo + q < hi) {
       lcnt[lo + q] = off;
-      lbase[lo + q] = rv[q] - off;
+      lbase[lo + q] = rv[q] + (base ? base[q] : 0u) - off;
       off += cv[q];
     }
   }
@@ -540,51 +550,12 @@ __device__ __forceinline__ void scatter_stage_chunk(unsigned* lcnt, unsigned* lb
     if (FULL || threadIdx.x + (unsigned)j * kScatterThreads < nv) out.st(dd[j], P4{rx[j], ry[j], rz[j]});
 }
 
-template <typename T, bool LDSHIST, bool STAGE, int SCH, bool SOA>
-__global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, const Geometry* geo, size_t stride,
-                                                                 char* slot_base, size_t bins_off,
-                                                                 char* sorted_base, size_t sorted_stride,
-                                                                 size_t inv_off, MeshDims m, BinGeom bg,
-                                                                 int chunk0, int nchunk, SortedOut<T> so) {
-  extern __shared__ unsigned lds[];
-  __shared__ unsigned ws[1][16];
-  constexpr int PER = chunk_per<T, kScatterThreads>();
+// The positions of this lane's particles in the chunk at c0, 0 past the end.
+template <typename T, int PER = chunk_per<T, kScatterThreads>()>
+__device__ __forceinline__ void load_chunk(const T* px, const T* py, const T* pz, int64_t c0, int64_t n, bool vec,
+                                           T (&xs)[PER], T (&ys)[PER], T (&zs)[PER]) {
   constexpr int NV = Vec16<T>::n;
-  constexpr int64_t CH = scatter_chunk<T>();
-  static_assert(!STAGE || LDSHIST, "staging needs the LDS histogram");
-  using P4 = Rec<T>;
   using V = typename Vec16<T>::type;
-  const int b = blockIdx.y;
-  const dks_particle_set e = eb.at(b);
-  const int64_t n = eb.n(e);
-  const int chunk = chunk0 + (int)blockIdx.x;
-  const int64_t c0 = (int64_t)chunk * CH;
-  if (c0 >= n) return;                       // whole workgroup: no barrier is skipped by part of it
-  unsigned* lcnt = lds;
-  unsigned* lbase = lds + (bg.K + 1);
-  // 2 (K + 1) words precede the records: 8-byte aligned for FP64 records
-  P4* srec = reinterpret_cast<P4*>(lds + 2 * (bg.K + 1));
-  unsigned short* skey = reinterpret_cast<unsigned short*>(srec + CH);
-  const T* px = (const T*)e.x;
-  const T* py = (const T*)e.y;
-  const T* pz = (const T*)e.z;
-  // A private copy of the geometry: the LDS atomics between the particles'
-  // cell decisions would otherwise make the compiler reload its fields (and
-  // wait for them) once per particle.
-  const Geometry gcopy = *geo_of(geo, stride, b);
-  const Geometry* g = &gcopy;
-  BinState st = bin_state(slot_base, stride, bins_off, b, bg.K);
-  // the chunk's XCD group, as the count kernel assigned it
-  unsigned* cursor = st.xcursor + (int)(((int64_t)b * nchunk + chunk) % kXcd) * (bg.K + 1);
-  const Recs<T, SOA> out = recs_of<T, SOA>(sorted_base, sorted_stride, b, so);
-  unsigned* inv = SOA ? so.inv
-                  : inv_off == kNoInverse ? nullptr
-                      : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
-  if (LDSHIST) {
-    for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
-  }
-  const bool vec = aligned16(px + c0, py + c0, pz + c0);
-  T xs[PER], ys[PER], zs[PER];
   if (vec) {
 #pragma unroll
     for (int q = 0; q < PER / NV; ++q) {
@@ -617,9 +588,98 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
       zs[j] = ok ? pz[i] : (T)0;
     }
   }
+}
+
+// SCAN (staged scatters of the first launch after the count): every workgroup
+// scans the tile counts itself, while its positions are on their way, instead
+// of a scan kernel between the two; an element's first workgroup also stores
+// the offsets and work items for the kernels after it.  64^3 with 1e6 FP32
+// particles: scan and scatter 4.6 + 15.8 us, together now 16.3; batch of 8 x
+// 48^3 4.7 + 16.3, now 18.9.
+template <typename T, bool LDSHIST, bool STAGE, bool SCAN, int SCH, bool SOA>
+__global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, const Geometry* geo, size_t stride,
+                                                                 char* slot_base, size_t bins_off,
+                                                                 char* sorted_base, size_t sorted_stride,
+                                                                 size_t inv_off, MeshDims m, BinGeom bg,
+                                                                 int chunk0, int nchunk, SortedOut<T> so) {
+  extern __shared__ unsigned lds[];
+  __shared__ unsigned ws[SCAN ? 3 : 1][16];
+  constexpr int PER = chunk_per<T, kScatterThreads>();
+  constexpr int NV = Vec16<T>::n;
+  constexpr int64_t CH = scatter_chunk<T>();
+  static_assert(!STAGE || LDSHIST, "staging needs the LDS histogram");
+  static_assert(!SCAN || STAGE, "the scan shares the staging's tile ownership");
+  using P4 = Rec<T>;
+  using V = typename Vec16<T>::type;
+  const int b = blockIdx.y;
+  const dks_particle_set e = eb.at(b);
+  const int64_t n = eb.n(e);
+  const int chunk = chunk0 + (int)blockIdx.x;
+  const int64_t c0 = (int64_t)chunk * CH;
+  if constexpr (SCAN) {
+    if (chunk == 0) {
+      scan_tiles<false>(bin_state(slot_base, stride, bins_off, b, bg.K), bg, ws,
+                        const_cast<Geometry*>(geo_of(geo, stride, b)), e.n_outside);
+      __syncthreads();                       // ws is used again
+    }
+  }
+  if (c0 >= n) return;                       // whole workgroup: no barrier is skipped by part of it
+  unsigned* lcnt = lds;
+  unsigned* lbase = lds + (bg.K + 1);
+  // 2 (K + 1) words precede the records: 8-byte aligned for FP64 records
+  P4* srec = reinterpret_cast<P4*>(lds + 2 * (bg.K + 1));
+  unsigned short* skey = reinterpret_cast<unsigned short*>(srec + CH);
+  const T* px = (const T*)e.x;
+  const T* py = (const T*)e.y;
+  const T* pz = (const T*)e.z;
+  // A private copy of the geometry: the LDS atomics between the particles'
+  // cell decisions would otherwise make the compiler reload its fields (and
+  // wait for them) once per particle.
+  const Geometry gcopy = *geo_of(geo, stride, b);
+  const Geometry* g = &gcopy;
+  BinState st = bin_state(slot_base, stride, bins_off, b, bg.K);
+  // the chunk's XCD group, as the count kernel assigned it
+  unsigned* cursor = st.xcursor + (int)(((int64_t)b * nchunk + chunk) % kXcd) * (bg.K + 1);
+  const Recs<T, SOA> out = recs_of<T, SOA>(sorted_base, sorted_stride, b, so);
+  unsigned* inv = SOA ? so.inv
+                  : inv_off == kNoInverse ? nullptr
+                      : reinterpret_cast<unsigned*>(sorted_base + (size_t)b * sorted_stride + inv_off);
+  if (LDSHIST) {
+    for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
+  }
+  const bool vec = aligned16(px + c0, py + c0, pz + c0);
+  T xs[PER], ys[PER], zs[PER];
+  load_chunk<T>(px, py, pz, c0, n, vec, xs, ys, zs);
+  unsigned base[kStageRun];
+  if constexpr (SCAN) {
+    // starts of this group's part of the lane's tiles (the tiles it reserves)
+    const int L = bg.K + 1, per = (L + kScatterThreads - 1) / kScatterThreads;
+    const int lo = min((int)threadIdx.x * per, L), hi = min(lo + per, L);
+    const int group = (int)(((int64_t)b * nchunk + chunk) % kXcd);
+    unsigned before[kStageRun], all[kStageRun], sum[1] = {0}, tot[1];
+#pragma unroll
+    for (int q = 0; q < kStageRun; ++q) {
+      before[q] = all[q] = 0;
+      if (lo + q < hi) {
+#pragma unroll
+        for (int x = 0; x < kXcd; ++x) {
+          const unsigned c = st.xcount[x * L + lo + q];
+          all[q] += c;
+          before[q] += x < group ? c : 0u;
+        }
+      }
+      sum[0] += all[q];
+    }
+    scan1024(sum, ws, tot);
+#pragma unroll
+    for (int q = 0; q < kStageRun; ++q) {
+      base[q] = sum[0] + before[q];
+      sum[0] += all[q];
+    }
+  }
   int key[PER];
   unsigned rank[PER];
-  if (LDSHIST) __syncthreads();              // lcnt cleared
+  if (LDSHIST) __syncthreads();              // lcnt cleared, ws free
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int64_t i = chunk_index<T, kScatterThreads>(vec, c0, j);
@@ -628,7 +688,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
     else rank[j] = key[j] >= 0 ? rank_add(cursor, key[j]) : 0u;
   }
   if constexpr (STAGE) {
-    scatter_stage_chunk<T, false>(lcnt, lbase, srec, skey, ws, cursor, bg, key, rank, xs, ys, zs, c0, n, vec, out,
+    scatter_stage_chunk<T, false>(lcnt, lbase, srec, skey, ws, cursor, SCAN ? base : nullptr, bg, key, rank, xs, ys, zs, c0, n, vec, out,
                                   inv);
     return;
   }
@@ -683,7 +743,11 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
 // workgroup w takes chunks w, w + G, ... (G = gridDim.x, a multiple of kXcd,
 // one workgroup per CU), and loads chunk c + G while chunk c is ranked,
 // staged and stored.  One element whose positions are 16-byte aligned; the
-// chunks are the first nfull (whole) ones.
+// chunks are the first nfull (whole) ones.  The partial last one, if any, is
+// taken first by the workgroup next in turn (as a launch of its own it added
+// 11 us: 83 against 75 us for 1e7 particles); the tile-ordered step's kernel
+// has no registers left for that (it spilled 7, and 1e8 particles took 549
+// instead of 517 us) and leaves the partial chunk to the one-chunk kernel.
 template <typename T, int SCH, bool SOA>
 __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch eb, const Geometry* geo, size_t stride,
                                                                       char* slot_base, size_t bins_off,
@@ -730,6 +794,25 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
     }
   };
   for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
+  const int64_t cp = (int64_t)nfull * CH;
+  if (!SOA && cp < n && (int)blockIdx.x == nfull % (int)gridDim.x) {          // the partial chunk (whole workgroup)
+    T xs[PER], ys[PER], zs[PER];
+    load_chunk<T>(px, py, pz, cp, n, true, xs, ys, zs);
+    unsigned* cursor = st.xcursor + (int)(((int64_t)b * nchunk + nfull) % kXcd) * (bg.K + 1);
+    int key[PER];
+    unsigned rank[PER];
+    __syncthreads();                         // lcnt cleared
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int64_t i = chunk_index<T, kScatterThreads>(true, cp, j);
+      key[j] = i < n ? locate<T, SCH>(xs[j], ys[j], zs[j], g, m, bg).key : -1;
+      rank[j] = key[j] >= 0 ? rank_add(lcnt, key[j]) : 0u;
+    }
+    scatter_stage_chunk<T, false>(lcnt, lbase, srec, skey, ws, cursor, nullptr, bg, key, rank, xs, ys, zs, cp, n, true,
+                                  out, inv);
+    __syncthreads();                         // its records and offsets read
+    for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
+  }
   T xs[PER], ys[PER], zs[PER];
   load(c, xs, ys, zs);
   for (;;) {
@@ -747,7 +830,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
     const int cn = c + (int)gridDim.x;
     const bool more = cn < nfull;
     T nxs[PER], nys[PER], nzs[PER];
-    scatter_stage_chunk<T, true>(lcnt, lbase, srec, skey, ws, cursor, bg, key, rank, xs, ys, zs,
+    scatter_stage_chunk<T, true>(lcnt, lbase, srec, skey, ws, cursor, nullptr, bg, key, rank, xs, ys, zs,
                                  (int64_t)c * CH, n, true, out, inv,
                                  [&]() { load(more ? cn : c, nxs, nys, nzs); });
     if (!more) break;
@@ -1320,8 +1403,7 @@ constexpr int kDirectThreads = 64;
 template <typename T, int SCH>
 __global__ __launch_bounds__(kDirectThreads) void k_deposit_direct(ElemBatch eb, const Geometry* geo, size_t stride,
                                                                    unsigned long long* mesh, size_t mesh_stride,
-                                                                   MeshDims m,
-                                                                   BinGeom bg) {
+                                                                   MeshDims m, BinGeom bg) {
   constexpr int WD = Scheme<SCH>::width;
   const int b = blockIdx.y;
   const dks_particle_set e = eb.at(b);
@@ -1441,6 +1523,42 @@ hipError_t launch_bin_scan(const Geometry* geo, size_t stride, char* slot_base, 
   return hipGetLastError();
 }
 
+// How a solve's scatter runs: staged through LDS, a large single solve through
+// the persistent kernel (one element with aligned positions and at least two
+// chunks per CU), or (scan) with the tile scan in the scatter.
+struct ScatterForm {
+  bool stage, scan;
+  int nfull, G;
+};
+template <typename T>
+static ScatterForm scatter_form(const ElemBatch& eb, int batch, const BinGeom& bg) {
+  ScatterForm f{false, false, 0, 0};
+  if (eb.max_np == 0) return f;
+  const int64_t ch = scatter_chunk<T>();
+  // 512 bytes left for the static scan scratch
+  f.stage = bg.lds_hist != 0 && scatter_stage_lds<T>(bg.K) + 512 <= kLdsPerWorkgroup &&
+            bg.K + 1 <= kStageRun * kScatterThreads;
+  if (f.stage && batch == 1 && eb.dev == nullptr) {
+    const dks_particle_set& e = eb.local;
+    const bool have = e.x && e.y && e.z && (!eb.need_e || (e.Ex && e.Ey && e.Ez));
+    const int64_t n = have ? std::min<int64_t>(std::max<int64_t>(e.np, 0), eb.max_np) : 0;
+    const bool aligned = ((reinterpret_cast<uintptr_t>(e.x) | reinterpret_cast<uintptr_t>(e.y) |
+                           reinterpret_cast<uintptr_t>(e.z)) & 15u) == 0;
+    const int cus = compute_units();
+    if (aligned && cus > 0 && n / ch >= 2 * cus) {
+      f.nfull = (int)(n / ch);
+      f.G = std::max(kXcd, cus / kXcd * kXcd);
+    }
+  }
+  f.scan = f.stage && f.nfull == 0;
+  return f;
+}
+
+// Whether launch_bin_scatter scans the tile counts itself (no launch_bin_scan).
+template <typename T> bool scatter_scans(const ElemBatch& eb, int batch, const BinGeom& bg) {
+  return scatter_form<T>(eb, batch, bg).scan;
+}
+
 template <typename T>
 hipError_t launch_bin_scatter(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, char* slot_base, size_t bins_off,
                               char* sorted_base, size_t sorted_stride, size_t inv_off, const MeshDims& m,
@@ -1452,46 +1570,30 @@ hipError_t launch_bin_scatter(const ElemBatch& eb, int batch, const Geometry* ge
   const int64_t ch = scatter_chunk<T>();
   const unsigned nchunk = (unsigned)((eb.max_np + ch - 1) / ch);
   const bool lh = bg.lds_hist != 0;
-  // 256 bytes left for the static scan scratch
-  const bool stage = lh && scatter_stage_lds<T>(bg.K) + 256 <= kLdsPerWorkgroup &&
-                     bg.K + 1 <= kStageRun * kScatterThreads;
+  const ScatterForm form = scatter_form<T>(eb, batch, bg);
+  const bool stage = form.stage;
   const size_t lds = stage ? scatter_stage_lds<T>(bg.K) : lh ? 2 * (size_t)(bg.K + 1) * sizeof(unsigned) : 0;
-  // One element with aligned positions and at least one chunk per CU: the
-  // whole chunks go through the pipelined kernel, the partial last chunk (if
-  // any) through the one-chunk kernel.
-  int nfull = 0, G = 0;
-  if (stage && batch == 1 && eb.dev == nullptr) {
-    const dks_particle_set& e = eb.local;
-    const bool have = e.x && e.y && e.z && (!eb.need_e || (e.Ex && e.Ey && e.Ez));
-    const int64_t n = have ? std::min<int64_t>(std::max<int64_t>(e.np, 0), eb.max_np) : 0;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(e.x) | reinterpret_cast<uintptr_t>(e.y) |
-                           reinterpret_cast<uintptr_t>(e.z)) & 15u) == 0;
-    const int cus = compute_units();
-    if (aligned && cus > 0 && n / ch >= 2 * cus) {
-      nfull = (int)(n / ch);
-      G = std::max(kXcd, cus / kXcd * kXcd);
-    }
-  }
+  const int nfull = form.nfull, G = form.G;
   with_scheme_soa(bg.scheme, soa != nullptr, [&](auto sc, auto sa) {
     constexpr int SCH = decltype(sc)::value;
     constexpr bool SOA = decltype(sa)::value;
     if (nfull > 0) {
       hipLaunchKernelGGL((k_bin_scatter_pipe<T, SCH, SOA>), dim3(G, 1), dim3(kScatterThreads), lds, s, eb, geo, stride,
                          slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, (int)nchunk, nfull, so);
-      if ((unsigned)nfull < nchunk)
-        hipLaunchKernelGGL((k_bin_scatter<T, true, true, SCH, SOA>), dim3(nchunk - nfull, 1), dim3(kScatterThreads), lds,
-                           s, eb, geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg,
-                           nfull, (int)nchunk, so);
+      if (SOA && (unsigned)nfull < nchunk)
+        hipLaunchKernelGGL((k_bin_scatter<T, true, true, false, SCH, true>), dim3(1), dim3(kScatterThreads), lds, s, eb,
+                           geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, nfull,
+                           (int)nchunk, so);
     } else if (stage) {
-      hipLaunchKernelGGL((k_bin_scatter<T, true, true, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), lds, s, eb,
+      hipLaunchKernelGGL((k_bin_scatter<T, true, true, true, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), lds, s, eb,
                          geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, 0, (int)nchunk,
                          so);
     } else if (lh) {
-      hipLaunchKernelGGL((k_bin_scatter<T, true, false, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), lds, s,
+      hipLaunchKernelGGL((k_bin_scatter<T, true, false, false, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), lds, s,
                          eb, geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, 0,
                          (int)nchunk, so);
     } else {
-      hipLaunchKernelGGL((k_bin_scatter<T, false, false, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), 0, s,
+      hipLaunchKernelGGL((k_bin_scatter<T, false, false, false, SCH, SOA>), dim3(nchunk, batch), dim3(kScatterThreads), 0, s,
                          eb, geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, 0,
                          (int)nchunk, so);
     }
@@ -1634,6 +1736,7 @@ hipError_t launch_gather_direct(const ElemBatch& eb, int batch, const Geometry* 
 #define DKS_INSTANTIATE(T)                                                                                         \
   template hipError_t launch_bin_count<T>(const ElemBatch&, int, const Geometry*, size_t, char*, size_t, const MeshDims&,            \
                                           const BinGeom&, int, hipStream_t);                                       \
+  template bool scatter_scans<T>(const ElemBatch&, int, const BinGeom&);                                           \
   template hipError_t launch_bin_scatter<T>(const ElemBatch&, int, const Geometry*, size_t, char*, size_t,      \
                                             char*, size_t, size_t, const MeshDims&, const BinGeom&, int,           \
                                             void* const*, hipStream_t);                                            \

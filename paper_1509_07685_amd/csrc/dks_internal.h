@@ -296,9 +296,9 @@ constexpr int kXcd = 8;
 constexpr size_t kNoInverse = ~(size_t)0;
 
 // Per-slot bin bookkeeping (uint32), L = K + 1 tiles (tile K: outside):
-// xcount[kXcd][L] (cleared by the geometry kernel), count[L], offset[L+1],
-// xcursor[kXcd][L], item_off[L+1] and gitem_off[L+1] (deposit and gather work
-// items), misc[4] (misc[0], misc[1]: their numbers).
+// xcount[kXcd][L] and xcursor[kXcd][L] (both cleared before the count),
+// count[L], offset[L+1], item_off[L+1] and gitem_off[L+1] (deposit and gather
+// work items), misc[4] (misc[0], misc[1]: their numbers).
 struct BinState {
   unsigned* xcount;
   unsigned* count;

@@ -79,87 +79,73 @@ __global__ __launch_bounds__(256) void k_bbox(ElemBatch eb, double* partial, siz
 // ---------------------------------------------------------------------------
 // Geometry of each batch element (one block per element): reduce the bbox
 // partials, fit h and the origin, and derive every FP64 factor of the solve.
-// Thread 0 also clears the out-of-mesh counter.
+// The block also clears the out-of-mesh counter.  The whole is one chain of latencies in front of the step: the partials are
+// reduced by shuffles, and lane d derives the values of axis d, so that the
+// divisions of the three axes run side by side.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void geometry_of(int b, const double* partial, size_t partial_stride, Geometry* geo,
                                             size_t geo_stride, const GeoArgs& a, const ElemBatch& eb) {
 #pragma clang fp contract(off)
   const dks_particle_set e = eb.at(b);
   Geometry* g = reinterpret_cast<Geometry*>(reinterpret_cast<char*>(geo) + (size_t)b * geo_stride);
-  if (a.zero_len > 0) {
-    unsigned* z = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(g) + a.zero_off);
-    for (int i = threadIdx.x; i < a.zero_len; i += blockDim.x) z[i] = 0u;
-  }
-  __shared__ double red[6][256];
+  __shared__ double red[4][6];
+  double v[6];                              // minima, then negated maxima
+#pragma unroll
+  for (int d = 0; d < 6; ++d) v[d] = INFINITY;
   if (a.fitted) {
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     const double* pp = partial + (size_t)b * partial_stride;
     for (int i = threadIdx.x; i < a.nblocks; i += blockDim.x) {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        lo[d] = fmin(lo[d], pp[i * 6 + d]);
-        hi[d] = fmax(hi[d], pp[i * 6 + 3 + d]);
-      }
+      for (int d = 0; d < 6; ++d) v[d] = fmin(v[d], d < 3 ? pp[i * 6 + d] : -pp[i * 6 + d]);
     }
+  }
+  if (a.fitted) {
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      red[d][threadIdx.x] = lo[d];
-      red[3 + d][threadIdx.x] = hi[d];
+    for (int d = 0; d < 6; ++d) {
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) v[d] = fmin(v[d], __shfl_xor(v[d], o, 64));
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][d] = v[d];
     }
   }
   __syncthreads();
+  if (threadIdx.x >= 3) return;
+  const int d = (int)threadIdx.x;
+  auto axis = [&](const double (&x)[3]) { return d == 0 ? x[0] : d == 1 ? x[1] : x[2]; };
+  double h, origin;
   if (a.fitted) {
-    for (int s = 128; s > 0; s >>= 1) {
-      if ((int)threadIdx.x < s) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          red[d][threadIdx.x] = fmin(red[d][threadIdx.x], red[d][threadIdx.x + s]);
-          red[3 + d][threadIdx.x] = fmax(red[3 + d][threadIdx.x], red[3 + d][threadIdx.x + s]);
-        }
-      }
-      __syncthreads();
-    }
-  }
-  if (threadIdx.x != 0) return;
-  double h[3], origin[3];
-  if (a.fitted) {
-    double lo[3], hi[3];
+    const int n = d == 0 ? a.n[0] : d == 1 ? a.n[1] : a.n[2];
     const bool empty = eb.n(e) <= 0;
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = empty ? 0.0 : red[d][0];
-      hi[d] = empty ? 0.0 : red[3 + d][0];
-    }
-    double hc = 0.0;
-    for (int d = 0; d < 3; ++d) hc = fmax(hc, (hi[d] - lo[d]) / (double)(a.n[d] - 3));
-    if (!(hc > 0.0)) hc = 1.0;
-    for (int d = 0; d < 3; ++d) {
-      h[d] = hc;
-      origin[d] = 0.5 * (lo[d] + hi[d]) - 0.5 * (double)(a.n[d] - 1) * hc;
-    }
+    const double lo = empty ? 0.0 : fmin(fmin(red[0][d], red[1][d]), fmin(red[2][d], red[3][d]));
+    const double hi = empty ? 0.0 : -fmin(fmin(red[0][3 + d], red[1][3 + d]), fmin(red[2][3 + d], red[3][3 + d]));
+    const double w = (hi - lo) / (double)(n - 3);
+    h = fmax(fmax(fmax(0.0, __shfl(w, 0, 64)), __shfl(w, 1, 64)), __shfl(w, 2, 64));
+    if (!(h > 0.0)) h = 1.0;
+    origin = 0.5 * (lo + hi) - 0.5 * (double)(n - 1) * h;
   } else {
-    for (int d = 0; d < 3; ++d) {
-      h[d] = a.h[d];
-      origin[d] = a.origin[d];
-    }
+    h = axis(a.h);
+    origin = axis(a.origin);
   }
+  const double inv_h = 1.0 / h, grad = -1.0 / (2.0 * h);
+  g->h[d] = h;
+  g->origin[d] = origin;
+  g->inv_h[d] = inv_h;
+  g->grad_coef[d] = grad;
+  g->origin_f[d] = (float)origin;
+  g->inv_h_f[d] = (float)inv_h;
+  g->grad_coef_f[d] = (float)grad;
   const double coulomb = 1.0 / (4.0 * M_PI * kEps0);
-  double scale;
-  if (a.mode == 0) scale = coulomb;                                   // rho given in C/m^3
-  else if (a.fitted) scale = coulomb * e.q / h[0];                // spectrum built for h = 1 m
-  else scale = coulomb * e.q / (h[0] * h[1] * h[2]);             // rho = q W / V
-  for (int d = 0; d < 3; ++d) {
-    g->h[d] = h[d];
-    g->origin[d] = origin[d];
-    g->inv_h[d] = 1.0 / h[d];
-    g->grad_coef[d] = -1.0 / (2.0 * h[d]);
-    g->origin_f[d] = (float)origin[d];
-    g->inv_h_f[d] = (float)g->inv_h[d];
-    g->grad_coef_f[d] = (float)g->grad_coef[d];
+  if (d == 0) {
+    double scale;
+    if (a.mode == 0) scale = coulomb;                              // rho given in C/m^3
+    else if (a.fitted) scale = coulomb * e.q / h;                  // spectrum built for h = 1 m
+    else scale = coulomb * e.q / (a.h[0] * a.h[1] * a.h[2]);       // rho = q W / V
+    g->conv_scale = scale;
+    g->conv_scale_f = (float)scale;
+  } else if (d == 1) {
+    g->n_outside = 0;
+  } else if (e.n_outside) {
+    *e.n_outside = 0;
   }
-  g->conv_scale = scale;
-  g->conv_scale_f = (float)scale;
-  g->n_outside = 0;
-  if (e.n_outside) *e.n_outside = 0;
 }
 
 __global__ __launch_bounds__(256) void k_geometry(const double* partial, size_t partial_stride,
@@ -169,12 +155,15 @@ __global__ __launch_bounds__(256) void k_geometry(const double* partial, size_t 
 }
 
 // The geometry of element blockIdx.y (by workgroup 0 of the row) and the
-// zero fill of that element's deposit mesh (by every workgroup of the row):
-// one launch for two steps that do not depend on each other.
+// zero fills of that element's tile counters and deposit mesh (by every
+// workgroup of the row): one launch for steps that do not depend on each
+// other.
 __global__ __launch_bounds__(256) void k_geometry_zero(const double* partial, size_t partial_stride,
                                                        Geometry* geo, size_t geo_stride, GeoArgs a,
                                                        ElemBatch eb, void* zbase, size_t zstride, size_t zbytes) {
   if (blockIdx.x == 0) geometry_of(blockIdx.y, partial, partial_stride, geo, geo_stride, a, eb);
+  unsigned* z = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(geo) + (size_t)blockIdx.y * geo_stride + a.zero_off);
+  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x); i < a.zero_len; i += (int)(gridDim.x * blockDim.x)) z[i] = 0u;
   char* p = reinterpret_cast<char*>(zbase) + (size_t)blockIdx.y * zstride;
   const size_t n16 = zbytes / 16;
   uint4* q = reinterpret_cast<uint4*>(p);
@@ -271,7 +260,8 @@ static inline unsigned grid_for(int64_t n, unsigned cap) {
 template <typename T>
 hipError_t launch_bbox(const ElemBatch& eb, int batch, double* partial, size_t partial_stride, int* nblocks_out,
                        hipStream_t s) {
-  const unsigned nb = grid_for(eb.max_np, kBboxBlocks);
+  // 2048 particles and more per workgroup: the fit reads every partial
+  const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((eb.max_np + 2047) / 2048, kBboxBlocks));
   *nblocks_out = (int)nb;
   hipLaunchKernelGGL(k_bbox<T>, dim3(nb, batch), dim3(256), 0, s, eb, partial, partial_stride);
   return hipGetLastError();

@@ -43,6 +43,7 @@ template <typename T> hipError_t launch_gather(const void*, const void*, const v
                                                void*, int64_t, const Geometry*, const MeshDims&, int, hipStream_t);
 template <typename T> hipError_t launch_bin_count(const ElemBatch&, int, const Geometry*, size_t, char*, size_t,
                                                   const MeshDims&, const BinGeom&, int, hipStream_t);
+template <typename T> bool scatter_scans(const ElemBatch&, int, const BinGeom&);
 hipError_t launch_bin_scan(const Geometry*, size_t, char*, size_t, const BinGeom&, const ElemBatch&, int,
                            hipStream_t);
 template <typename T> hipError_t launch_bin_scatter(const ElemBatch&, int, const Geometry*, size_t, char*,
@@ -516,17 +517,21 @@ dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl
                          hipStream_t st, void* const* soa = nullptr) {
   int nb = 0;
   double* bbox = reinterpret_cast<double*>(sl.base + p->s_bbox);
-  if (p->fitted) DKS_TK("bbox", launch_bbox<T>(eb, batch, bbox, sl.stride / sizeof(double), &nb, st));
-  GeoArgs ga = geo_args(p, 1, nb);
-  ga.zero_off = p->s_bins;                  // the per-group tile counts
-  ga.zero_len = direct ? 0 : kXcd * (p->bg.K + 1);
-  // The order-independent deposit sums into integer node totals in R2
-  // (free until the forward y pass) and forms W from them afterwards.
+  const size_t bstride = sl.stride / sizeof(double);
+  // the per-group tile counts, and the cursors where no scan kernel writes them
+  const bool scans = scatter_scans<T>(eb, batch, w.bg);
+  const int zero_len = direct ? 0 : (scans ? 2 : 1) * kXcd * (p->bg.K + 1);
+  // The order-independent deposit and the direct one sum into integer node
+  // totals in R2 (free until the forward y pass).
   const size_t nmesh = (size_t)p->n[0] * p->n[1] * p->n[2];
   char* iacc = p->deterministic || direct ? sl.base + p->s_r2 : nullptr;
-  const size_t iacc_bytes = nmesh * (sizeof(T) == 4 || direct ? 8 : 16);
-  DKS_TK("geometry", launch_geometry_zero(bbox, sl.stride / sizeof(double), sl.geo(), sl.stride, ga, eb, batch,
-                                          iacc ? iacc : sl.base + p->s_r3, sl.stride, iacc ? iacc_bytes : p->bytes_W,
+  char* zbase = iacc ? iacc : sl.base + p->s_r3;
+  const size_t zbytes = iacc ? nmesh * (sizeof(T) == 4 || direct ? 8 : 16) : p->bytes_W;
+  if (p->fitted) DKS_TK("bbox", launch_bbox<T>(eb, batch, bbox, bstride, &nb, st));
+  GeoArgs ga = geo_args(p, 1, nb);
+  ga.zero_off = p->s_bins;
+  ga.zero_len = zero_len;
+  DKS_TK("geometry", launch_geometry_zero(bbox, bstride, sl.geo(), sl.stride, ga, eb, batch, zbase, sl.stride, zbytes,
                                           st));
   if (direct) {
     DKS_TK("deposit", launch_deposit_direct<T>(eb, batch, sl.geo(), sl.stride, iacc, sl.stride, p->md, w.bg, st));
@@ -534,7 +539,8 @@ dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl
   }
   DKS_TK("bin_count", launch_bin_count<T>(eb, batch, sl.geo(), sl.stride, sl.base, p->s_bins, p->md, w.bg,
                                           w.count_blocks, st));
-  DKS_TK("bin_scan", launch_bin_scan(sl.geo(), sl.stride, sl.base, p->s_bins, w.bg, eb, batch, st));
+  if (!scans)
+    DKS_TK("bin_scan", launch_bin_scan(sl.geo(), sl.stride, sl.base, p->s_bins, w.bg, eb, batch, st));
   DKS_TK("bin_scatter", launch_bin_scatter<T>(eb, batch, sl.geo(), sl.stride, sl.base, p->s_bins, sorted,
                                               sorted_stride, inv_off, p->md, w.bg, w.count_blocks, soa, st));
   DKS_TK("deposit", launch_deposit_binned<T>(sl.geo(), sl.stride, sl.base, p->s_bins, sorted, sorted_stride,
