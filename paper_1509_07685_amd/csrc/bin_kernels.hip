@@ -1070,7 +1070,7 @@ __device__ __forceinline__ void interp_field(Node&& node, const Cell<float, SCH>
       float rx = 0.f, ry = 0.f, rz = 0.f;
 #pragma unroll
       for (int kx = 0; kx < WD; ++kx) {
-        const float4 d = node(kz, ky, kx);
+        const float3 d = node(kz, ky, kx);
         rx += c.wx[kx] * d.x;
         ry += c.wx[kx] * d.y;
         rz += c.wx[kx] * d.z;
@@ -1183,8 +1183,17 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_binned(const Geometry
 // entries and 36 multiply-adds (trilinear weights of its cell times the
 // node differences), against 32 node values and about twice the arithmetic
 // when the differences are formed per particle.  The entries take 77 KB
-// (CIC) or 64 KB (NGP): two 1024-lane workgroups per CU.  (TSC would need
-// 91 KB, one workgroup per CU; it keeps k_gather_binned.)
+// (CIC) or 64 KB (NGP): two 1024-lane workgroups per CU.
+//
+// Bound by the random LDS reads at small meshes, by those and HBM (2.4 GB, 490
+// us at the rate of a copy) at 256^3 / 1e8.  An entry is (y, z, x of the node,
+// x of the next node), so that a CIC row of two nodes is one 16-byte and one
+// 8-byte read, no word of which goes unused: 562 us, and 17 at 64^3 / 1e6,
+// against 645 and 20 with (x, y, z, unused), and 669 and 20 with 12-byte
+// entries, which are read by 4-byte alignment.
+// TSC keeps k_gather_binned: its 91 KB leave one workgroup per CU, and staging
+// costs more for its smaller items (144x128x96 / 3e6: 90 us against 62; 91 with
+// 12-byte entries and two workgroups per CU).
 // ---------------------------------------------------------------------------
 template <int SCH> constexpr int field_edge() { return acc_edge<SCH>(); }
 template <int SCH> constexpr size_t field_lds_bytes() {
@@ -1235,7 +1244,7 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
     constexpr int NE = E * E * E, SB = 5;
     const int sy = nx2, sz = nx2 * ny2;
     for (int e0 = threadIdx.x; e0 < NE; e0 += SB * 1024) {
-      float v[SB][6];
+      float v[SB][8];
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
         const int e = min(e0 + u * 1024, NE - 1);
@@ -1248,10 +1257,14 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
         v[u][3] = c[-sy];
         v[u][4] = c[sz];
         v[u][5] = c[-sz];
+        // the next node's x difference; past the mesh's last node it is not
+        // one, and no stencil reads it (c[2] is in phi's next row)
+        v[u][6] = c[2];
+        v[u][7] = c[0];
       }
 #pragma unroll
       for (int u = 0; u < SB; ++u)
-        if (e0 + u * 1024 < NE) ef[e0 + u * 1024] = make_float4(v[u][0] - v[u][1], v[u][2] - v[u][3], v[u][4] - v[u][5], 0.f);
+        if (e0 + u * 1024 < NE) ef[e0 + u * 1024] = make_float4(v[u][2] - v[u][3], v[u][4] - v[u][5], v[u][0] - v[u][1], v[u][6] - v[u][7]);
     }
     __syncthreads();
     // Unconditional loads (past the item's end they re-read its last record;
@@ -1268,7 +1281,12 @@ __global__ __launch_bounds__(1024) void k_gather_binned_field(const Geometry* ge
         const Cell<float, SCH> c = locate<float, SCH>(p.x, p.y, p.z, g, m, bg);
         const float4* o = ef + ((c.bz - bz) * E + (c.by - by)) * E + (c.bx - bx);
         float ax = 0.f, ay = 0.f, az = 0.f;
-        interp_field<SCH>([&](int kz, int ky, int kx) { return o[(kz * E + ky) * E + kx]; }, c, ax, ay, az);
+        interp_field<SCH>(
+            [&](int kz, int ky, int kx) {
+              const float4* q = o + (kz * E + ky) * E + kx;
+              return make_float3(kx == 0 ? q->z : q[-1].w, q->x, q->y);
+            },
+            c, ax, ay, az);
         if constexpr (SOA) {
           so.ex[i] = ax * cx;
           so.ey[i] = ay * cy;
@@ -1453,7 +1471,7 @@ __global__ __launch_bounds__(kDirectThreads) void k_gather_direct(ElemBatch eb, 
       interp_field<SCH>(
           [&](int kz, int ky, int kx) {
             const T* q = o + kz * sz + ky * sy + kx;
-            return make_float4(q[1] - q[-1], q[sy] - q[-sy], q[sz] - q[-sz], 0.f);
+            return make_float3(q[1] - q[-1], q[sy] - q[-sy], q[sz] - q[-sz]);
           },
           c, ax, ay, az);
     } else {
@@ -1640,9 +1658,8 @@ hipError_t launch_gather_binned(const Geometry* geo, size_t stride, char* slot_b
   if (soa && batch != 1) return hipErrorInvalidValue;
   const SortedOut<T> so = sorted_out<T>(soa);
   if constexpr (sizeof(T) == 4) {
-    // TSC's 91 KB of node differences leave one workgroup per CU, and that
-    // gather measured slower (1851 against 1675 us at 256^3 / 1e8) than
-    // forming the differences per particle
+    // TSC forms the differences per particle: 62 us against 90 from staged
+    // ones (144x128x96 / 3e6)
     if (bg.scheme != kSchemeTSC) {
       const bool ngp = bg.scheme == kSchemeNGP;
       if (soa) {
