@@ -56,6 +56,20 @@ template <class SP> __device__ __forceinline__ int ntiles(const MeshDims& m, con
 // then covers part of a block).
 template <typename T> constexpr int kBlockCols = 128 / (2 * (int)sizeof(T));
 
+// Runs body(st) with st(p, v) a store past the caches (stream) or an ordinary
+// one: a uniform branch around a butterfly's stores.
+template <class Body> __device__ __forceinline__ void store_as(bool stream, Body&& body) {
+  if (stream)
+    body([](auto* p, const auto& v) {
+      using R = std::decay_t<decltype(v.x)>;
+      typedef R V __attribute__((ext_vector_type(2)));
+      const V w = {v.x, v.y};
+      __builtin_nontemporal_store(w, (__attribute__((address_space(1))) V*)p);
+    });
+  else
+    body([](auto* p, const auto& v) { *p = v; });
+}
+
 // ---------------------------------------------------------------------------
 // x forward: real rows of nx values (zero-padded to 2 nx) -> nx + 1 complex.
 // A length-2nx real transform is done as a length-nx complex transform of
@@ -243,7 +257,7 @@ template <typename T, class SP>
 __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_y_fwd(const typename Cplx<T>::type* __restrict__ A,
                                                         typename Cplx<T>::type* __restrict__ B,
                                                         size_t stride, MeshDims m, const FFTPlan* __restrict__ P,
-                                                        int tile0) {
+                                                        int tile0, bool stream) {
   using C = typename Cplx<T>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
@@ -260,8 +274,10 @@ __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_y_fwd(const ty
     return (SP::is_static || idx < ny) ? src[(Off)idx * (Off)cs + (Off)c] : C{0, 0};
   };
   auto out = [&](auto RC, int c, int, int base, int Ns, C* vals, int) {
+    store_as(stream, [&](auto st) {
 #pragma unroll
-    for (int r = 0; r < RC.value; ++r) dst[(Off)(base + r * Ns) * kstep + (Off)c] = vals[r];
+      for (int r = 0; r < RC.value; ++r) st(dst + ((Off)(base + r * Ns) * kstep + (Off)c), vals[r]);
+    });
   };
   run_any<T, false, false, SP, 0, true>(lds, P, in, out);
 }
@@ -1012,9 +1028,19 @@ hipError_t launch_fft_y_fwd(const void* A, void* B, size_t stride, const MeshDim
   using C = typename Cplx<T>::type;
   const int W = P.host.W, t0 = col0 / W;
   dim3 grid((col1 + W - 1) / W - t0, m.nz, batch);
+  // Stores past the caches for a B that the last-level cache (256 MB) holds
+  // only in part by the time the z pass, in another order and beside its own
+  // output, reads it.  Whole mesh solves, ordinary against these stores:
+  // FP32 128^3 (B of 38 MB) 85 and 88 us, 256x128x128 (71 MB) 144 and 140,
+  // 192^3 (123 MB) 230 and 226, 216^3 (167 MB) 409 and 402, 256^3 (285 MB) 509
+  // and 488; FP64 96x96x192 (61 MB) 121 and 122, 144^3 (101 MB) 195 and 193,
+  // 192^3 (236 MB) 419 and 402, but 256^3 (554 MB) 937 and 954.  The same
+  // stores in the other passes, or loads past the caches, gained nothing or lost.
+  const size_t bytes = (size_t)m.Ny * m.nz * m.cs * sizeof(C) * batch;
+  const bool stream = bytes >= ((size_t)64 << 20) && bytes <= ((size_t)384 << 20);
   with_plan<T, 0, false>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_y_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
-                       (const C*)A, (C*)B, stride, m, P.dev, t0);
+                       (const C*)A, (C*)B, stride, m, P.dev, t0, stream);
   }, offsets_fit32(m));
   return hipGetLastError();
 }
