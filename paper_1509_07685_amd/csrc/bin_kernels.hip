@@ -8,8 +8,10 @@
 //
 //   count    per-tile histogram (LDS-privatised, flushed with one atomic per
 //            touched tile per workgroup)
-//   scan     tile offsets, reservation cursors and the work-item list
-//            (a work item is up to kItem particles of one tile)
+//   scan     tile offsets, reservation cursors and the work items (a work
+//            item is a run of one tile's particles); the one-chunk scatter's
+//            workgroups each form it for themselves, the persistent scatter
+//            and large tile counts have a launch of their own
 //   scatter  one workgroup per chunk of 8192 (FP32) / 4096 (FP64) consecutive
 //            particles: ranks within tiles from an LDS histogram, one device
 //            atomic per touched tile to reserve the chunk's range, then the
@@ -24,13 +26,19 @@
 //   gather   per work item: stage phi of the tile plus a two-node apron
 //            (19^3 values) in LDS, form the central-difference field at the
 //            eight nodes of each particle and interpolate it with the
-//            deposit's weights; the field overwrites the particle's binned
-//            record in place
+//            deposit's weights (FP32 CIC and NGP: the differences are staged
+//            instead); the field overwrites the particle's binned record in
+//            place
 //   unsort   per scatter chunk, read each field through the inverse
 //            permutation and write the three field arrays contiguously; a
 //            chunk's records lie in one short segment per touched tile, so
 //            its scattered 16-byte reads share cache lines (scattered 4-byte
 //            writes to the original indices would cost far more)
+//
+// Solves of few particles skip the binning: k_deposit_direct adds each
+// particle's weights to 64-bit fixed-point node totals in memory, which the
+// first FFT pass reads, and k_gather_direct reads phi in place, with the
+// binned kernels' arithmetic.
 //
 // Particles outside the mesh fall in an extra tile K: they deposit nothing,
 // get E = 0 and their count is the out-of-mesh count.  The cell decision is
@@ -1686,9 +1694,10 @@ hipError_t launch_gather_binned(const Geometry* geo, size_t stride, char* slot_b
   }
   with_scheme_soa(bg.scheme, soa != nullptr, [&](auto sc, auto sa) {
     constexpr int SCH = decltype(sc)::value;
-    hipLaunchKernelGGL((k_gather_binned<T, SCH, decltype(sa)::value>), dim3(nblk, batch),
-                       dim3(kGatherThreads), 0, s, geo, stride, slot_base, bins_off, sorted_base,
-                       sorted_stride, (const T*)phi_ext, phi_stride, m, bg, so);
+    if constexpr (sizeof(T) == 8 || SCH == kSchemeTSC)
+      hipLaunchKernelGGL((k_gather_binned<T, SCH, decltype(sa)::value>), dim3(nblk, batch),
+                         dim3(kGatherThreads), 0, s, geo, stride, slot_base, bins_off, sorted_base,
+                         sorted_stride, (const T*)phi_ext, phi_stride, m, bg, so);
   });
   return hipGetLastError();
 }

@@ -321,13 +321,4 @@ struct GLBands {
   double w[6][12];   // weights
 };
 
-// Pointers to one solve's scratch (a "slot").
-struct SlotPtrs {
-  Geometry* geo;
-  double* bbox;       // kBboxBlocks * 6 partial bounds
-  void* R1;           // A, then C, then the interleaved E of the gather
-  void* R2;           // B, then D
-  void* R3;           // deposited weights, then phi with its ghost layer
-};
-
 }  // namespace dks
