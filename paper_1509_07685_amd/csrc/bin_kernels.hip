@@ -751,12 +751,12 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
 // workgroup w takes chunks w, w + G, ... (G = gridDim.x, a multiple of kXcd,
 // one workgroup per CU), and loads chunk c + G while chunk c is ranked,
 // staged and stored.  One element whose positions are 16-byte aligned; the
-// chunks are the first nfull (whole) ones.  The partial last one, if any, is
-// taken first by the workgroup next in turn (as a launch of its own it added
-// 11 us: 83 against 75 us for 1e7 particles); the tile-ordered step's kernel
-// has no registers left for that (it spilled 7, and 1e8 particles took 549
-// instead of 517 us) and leaves the partial chunk to the one-chunk kernel.
-template <typename T, int SCH, bool SOA>
+// chunks are the first nfull (whole) ones.  FOLD: the partial last one, if
+// any, is taken first by the workgroup next in turn.  As a launch of its own
+// it adds 8 us (82 against 73 us for 1e7 particles), but the loop then keeps
+// 4 registers of 128 in scratch (886 against 850 us for 1e8), 7 in the
+// tile-ordered step (549 against 517 us).
+template <typename T, int SCH, bool SOA, bool FOLD>
 __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch eb, const Geometry* geo, size_t stride,
                                                                       char* slot_base, size_t bins_off,
                                                                       char* sorted_base, size_t sorted_stride,
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter_pipe(ElemBatch 
   };
   for (int k = threadIdx.x; k <= bg.K; k += kScatterThreads) lcnt[k] = 0;
   const int64_t cp = (int64_t)nfull * CH;
-  if (!SOA && cp < n && (int)blockIdx.x == nfull % (int)gridDim.x) {          // the partial chunk (whole workgroup)
+  if (FOLD && cp < n && (int)blockIdx.x == nfull % (int)gridDim.x) {          // the partial chunk (whole workgroup)
     T xs[PER], ys[PER], zs[PER];
     load_chunk<T>(px, py, pz, cp, n, true, xs, ys, zs);
     unsigned* cursor = st.xcursor + (int)(((int64_t)b * nchunk + nfull) % kXcd) * (bg.K + 1);
@@ -1604,10 +1604,23 @@ hipError_t launch_bin_scatter(const ElemBatch& eb, int batch, const Geometry* ge
     constexpr int SCH = decltype(sc)::value;
     constexpr bool SOA = decltype(sa)::value;
     if (nfull > 0) {
-      hipLaunchKernelGGL((k_bin_scatter_pipe<T, SCH, SOA>), dim3(G, 1), dim3(kScatterThreads), lds, s, eb, geo, stride,
-                         slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, (int)nchunk, nfull, so);
-      if (SOA && (unsigned)nfull < nchunk)
-        hipLaunchKernelGGL((k_bin_scatter<T, true, true, false, SCH, true>), dim3(1), dim3(kScatterThreads), lds, s, eb,
+      const auto pipe = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(G, 1), dim3(kScatterThreads), lds, s, eb, geo, stride, slot_base, bins_off,
+                           sorted_base, sorted_stride, inv_off, m, bg, (int)nchunk, nfull, so);
+      };
+      // up to 16 chunks per workgroup (3.4e7 FP32 particles on 256 CUs) the
+      // launch saved is worth the folded kernel's scratch: 372 against 375 us
+      // for 3e7, 886 against 850 for 1e8
+      const bool part = (unsigned)nfull < nchunk;
+      if constexpr (!SOA) {
+        if (part && nfull <= 16 * G) {
+          pipe(k_bin_scatter_pipe<T, SCH, false, true>);
+          return;
+        }
+      }
+      pipe(k_bin_scatter_pipe<T, SCH, SOA, false>);
+      if (part)
+        hipLaunchKernelGGL((k_bin_scatter<T, true, true, false, SCH, SOA>), dim3(1), dim3(kScatterThreads), lds, s, eb,
                            geo, stride, slot_base, bins_off, sorted_base, sorted_stride, inv_off, m, bg, nfull,
                            (int)nchunk, so);
     } else if (stage) {
