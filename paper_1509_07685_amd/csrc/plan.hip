@@ -485,7 +485,7 @@ PartWork part_work(const dks_poisson_plan_s* p, int64_t maxn) {
   // with 3e5 particles: 8192 per item 32 us, 4096 21 us, 2048 16 us; TSC at
   // 144 x 128 x 96 with 3e6: 77, 79, 62 us).  Forming node differences costs
   // a workgroup more, and a deposit item is merged into the mesh node by
-  // node: both lose by shorter items (64^3 FP32 with 1e6: 20 -> 25 -> 28 us,
+  // node: both lose by shorter items (64^3 FP32 with 1e6: 17 -> 21 -> 23 us,
   // deposit 16 -> 23 -> 29).
   const bool staged_phi = w.bg.scheme == kSchemeTSC || p->dtype == DKS_F64;
   w.bg.gitem = staged_phi ? (int)std::min<int64_t>(w.bg.item, std::max<int64_t>(2048, maxn / 2048)) : w.bg.item;
