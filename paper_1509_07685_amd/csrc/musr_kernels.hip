@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dks_musr.h"
+#include "musr_math.h"
 
 namespace dks {
 namespace musr {
@@ -73,47 +74,22 @@ __device__ __forceinline__ double term(double d, double N) {
   }
 }
 
-// Counts and ratios N / d between these bounds take the fast terms below;
-// anything else (zero, negative, not finite, out of range) takes term().
-constexpr double kLow = 0x1p-960, kHigh = 0x1p960;
+// Counts of 0 or with a high word between these, ratios N / d likewise and
+// squares (d - N)^2 up to the higher one take the fast terms below; anything
+// else (negative, not finite, out of range) takes term().
+constexpr unsigned kLowWord = 0x03f00000u, kHighWord = 0x7bf00000u;   // of 2^-960 and 2^960
 
-// 1 / d of a normal d in (kLow, kHigh): the hardware estimate and two Newton
-// steps.
-__device__ __forceinline__ double recip(double d) {
-  double y = __builtin_amdgcn_rcp(d);
-  y = fma(fma(-d, y, 1.0), y, y);
-  return fma(fma(-d, y, 1.0), y, y);
-}
-
-// a b + c with a constant c kept in scalar registers (the compiler's two-address
-// form copies a constant into the destination before every step of a
-// polynomial: a sixth of the batch's instructions).
-__device__ __forceinline__ double fma_const(double a, double b, double c) {
-  double r;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
-  return r;
-}
-
-// log(q) of a normal q > 0: q = 2^k m with m in [sqrt(1/2), sqrt(2)), s =
-// (m - 1) / (m + 1), log m = 2 atanh(s) = 2 s (1 + z P(z)), z = s^2 <=
-// 0.02945.  P interpolates 1/3 + z/5 + z^2/7 + ... at the seven Chebyshev
-// nodes of that interval (z P off by at most 4.7e-18).
-__device__ __forceinline__ double log_normal(double q) {
-  const int hi = __double2hiint(q);
-  const int k = (hi - 0x3fe6a09e) >> 20;                  // sqrt(1/2) = 0x3fe6a09e...
-  const double m = __hiloint2double(hi - (k << 20), __double2loint(q));
-  const double s = (m - 1.0) * recip(m + 1.0);
-  const double z = s * s;
-  double p = 0.0730856419990365;
-  p = fma_const(p, z, 0.07665833338298587);
-  p = fma_const(p, z, 0.09091445389013066);
-  p = fma_const(p, z, 0.11111105556052474);
-  p = fma_const(p, z, 0.1428571431305726);
-  p = fma_const(p, z, 0.199999999999496);
-  p = fma_const(p, z, 0.3333333333333335);
-  const double s2 = s + s;
-  return fma((double)k, 0.6931471805599453, fma(s2 * z, p, s2));
-}
+struct DeviceOps {
+  static __device__ __forceinline__ double estimate(double d) { return __builtin_amdgcn_rcp(d); }
+  // a b + c with a constant c kept in scalar registers (the compiler's
+  // two-address form copies a constant into the destination before every step
+  // of a polynomial: a sixth of the batch's instructions).
+  static __device__ __forceinline__ double fma_const(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+  }
+};
 
 // grid: (time-bin blocks, detector groups, runs of `run` sets); partial:
 // [sets][gx * gy].  A thread owns one time bin t = n dt and every detector of
@@ -121,13 +97,13 @@ __device__ __forceinline__ double log_normal(double q) {
 // formed once for all sets, and per set exp(-t/tau - (sigma t)^2 / 2) and
 // cos/sin of the precession angle gamma B t once for all detectors, whose
 // counts follow by cos(w t + phi_j) = cos(w t) cos(phi_j) - sin(w t)
-// sin(phi_j) in three multiply-adds.  With the division by d turned into a
-// product, log(d / N) = -log(N (1/d)) needs no division by N either.
-// Bound by FP64 vector issue: about 840 instructions per wavefront of bins and
-// set, 42 of them per detector's logarithm and term; 133 sets of 16 x 206250
-// bins took 1.59 ms (log-likelihood) when every term divided twice and ran
-// the library logarithm, 0.62 ms now.  A single evaluation is bound by the
-// latency of its one chain per lane and by the two launches (13.4 -> 12.6 us).
+// sin(phi_j) in three multiply-adds.  Both quotients, (d - N)^2 / d and N / d
+// (log(d / N) = -log(N / d)), are products with 1 / d corrected by their exact
+// remainder, so they are rounded like divisions; a plain product would carry
+// the reciprocal's rounding, which is the same in every bin with that count.
+// Bound by FP64 vector issue: 133 sets of 16 x 206250 bins took 1.55 ms
+// (log-likelihood) when every term divided twice and ran the library
+// logarithm, 0.72 ms now.
 template <int STAT, bool DEV>
 __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void k_musr_eval(const double* __restrict__ data, long long n_bins,
                                                            double dt, Params prm, const double* __restrict__ dprm,
@@ -181,16 +157,11 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
   for (int j = 0; j < kGroup; ++j) d[j] = j < nj ? col[(size_t)j * n_bins] : 1.0;
   if constexpr (!DEV) own = damped(prm.sigma, prm.B);
   const double E = exp(a);
-  // A reciprocal's rounding error e (1/d = rd + e/d) is the same for every bin
-  // with that count, so the errors of N rd would not average out over the
-  // bins: -d e, the first order of d log(1 - e), takes them out again.
-  bool odd = false;          // some positive count out of the fast terms' range
-  double fix = 0.0;
+  bool odd = false;          // some count out of the fast terms' range
 #pragma unroll
   for (int j = 0; j < kGroup; ++j) {
-    odd = odd || (d[j] > 0.0 && !(d[j] > kLow && d[j] < kHigh));
-    rd[j] = d[j] > 0.0 ? recip(d[j]) : 1.0;
-    if (STAT == DKS_MUSR_MLE && d[j] > 0.0) fix = fma(-d[j], fma(-d[j], rd[j], 1.0), fix);
+    odd |= (d[j] != 0.0) & ((unsigned)__double2hiint(d[j]) - kLowWord > kHighWord - kLowWord);
+    rd[j] = d[j] > 0.0 ? recip<DeviceOps>(d[j]) : 0.5;         // quotient(n, 0, 1/2) = n
   }
   if constexpr (DEV) __syncthreads();
 #pragma unroll 1
@@ -207,18 +178,22 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
         return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
       }
     };
-    double acc = fix;
-    unsigned far = 0;          // largest distance of a ratio's high word from kLow's
+    double acc = 0.0;
+    // the largest high word of a quotient N / d, as a distance from the least
+    // one allowed, or of a square
+    constexpr unsigned least = STAT == DKS_MUSR_MLE ? kLowWord : 0u;
+    unsigned far = 0;
     auto one = [&](int j) {
       const double N = model(j);
       if constexpr (STAT == DKS_MUSR_CHISQ) {
-        const double r = d[j] - N;
-        acc += r * r * rd[j];
+        const double r = d[j] - N, r2 = r * r;
+        far = max(far, (unsigned)__double2hiint(r2));
+        acc += quotient(r2, d[j], rd[j]);
       } else {
-        // d <= 0 has rd = 1 and weighs its logarithm with 0
-        const double q = N * rd[j];
-        far = max(far, (unsigned)__double2hiint(q) - (unsigned)__double2hiint(kLow));
-        acc += fma(-fmax(d[j], 0.0), log_normal(q), N - d[j]);
+        // d = 0 weighs its logarithm with 0
+        const double x = quotient(N, d[j], rd[j]);
+        far = max(far, (unsigned)__double2hiint(x) - least);
+        acc += fma(-d[j], log_normal<DeviceOps>(x), N - d[j]);
       }
     };
     // four detectors at a time, their chains interleaved, then the rest
@@ -233,7 +208,7 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
           if (j < nj) one(j);
       }
     }
-    if (odd || far > (unsigned)__double2hiint(kHigh) - (unsigned)__double2hiint(kLow)) {
+    if (odd || far > kHighWord - least) {
       acc = 0.0;
 #pragma unroll 1
       for (int j = 0; j < nj; ++j) {
