@@ -22,7 +22,8 @@
  *                    for d <= 0 (log-likelihood equation; it is the Poisson
  *                    deviance, minimised by the fit).
  * Everything is FP64.  A result is deterministic: the same inputs give the
- * same bits (fixed-order reduction, no floating-point atomics).
+ * same bits (fixed-order reduction, no floating-point atomics), by either
+ * entry point and however many sets are evaluated together.
  *
  * Status codes, dtypes and streams as in dks_poisson.h.  A plan's
  * evaluations share its workspace: issue them on one stream.

@@ -5,14 +5,19 @@
 // a call brings only the parameter vector and produces one FP64 number.
 //
 // One fused kernel per call: every workgroup takes 256 consecutive time
-// bins of a group of up to 16 detectors and a run of parameter sets,
+// bins of a group of 16 (or 4) detectors and a run of parameter sets,
 // evaluates the model, accumulates the statistic in FP64, reduces it across
 // the workgroup in a fixed order and stores a partial per set; a
-// one-workgroup-per-set kernel then adds the partials in index order, so a
+// one-workgroup-per-set kernel then adds the partials in a fixed order, so a
 // result is bitwise reproducible.  (A last-workgroup-done counter in the
 // first kernel would need an agent-scope release and acquire per workgroup,
 // i.e. an L2 write-back and invalidate each, which measured slower than the
 // second launch.)
+//
+// A set's result does not depend on how many sets are evaluated with it, or
+// by which entry point: every sum is formed in one order, four detectors of a
+// bin, over the 256 lanes, the fours of a sixteen, the sixteens of a block of
+// bins, the blocks, wherever the launch's groups put the steps.
 
 #include <algorithm>
 #include <cmath>
@@ -30,16 +35,17 @@ namespace musr {
 constexpr int kMaxDet = 32;
 constexpr int kMaxSets = 1024;
 constexpr int kThreads = 256;
+constexpr int kQuad = 4;        // detectors summed in one lane
 constexpr int kGroup = 16;      // most detectors per workgroup: their counts stay in registers
-constexpr int kRun = 8;         // most parameter sets per workgroup: 36 KB of LDS, four workgroups per CU
+constexpr int kQuads = kGroup / kQuad;
+constexpr int kRun = 8;         // most parameter sets per workgroup: 38 KB of LDS, four workgroups per CU
 constexpr double kTauMu = 2.1969811;                         // muon lifetime, us
 constexpr double kGammaMu = 6.283185307179586 * 0.01355388094;   // rad / (us G)
 
-// Parameters of one evaluation, passed by value (kernel argument): sigma, B
-// and per detector N0, Nbkg, A0 N0 cos(phi), A0 N0 sin(phi).
+// Parameters of one evaluation, passed by value (kernel argument).
 struct Params {
   double sigma, B;
-  double det[4 * kMaxDet];
+  double det[kMaxDet][4];   // N0, Nbkg, A0, phi
 };
 
 // Sum over the wavefront in a fixed order (xor shuffles).
@@ -61,6 +67,21 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
     for (int i = 0; i < kThreads / 64; ++i) s += lds[i];
   __syncthreads();
   return s;
+}
+
+// The four values of q summed over the wavefront each as by wave_sum (the same
+// pairs at every step), in 7 exchanges instead of 24: each half keeps two of
+// the four values at the first step, each quarter one at the second.  Lane l
+// returns the sum of value (l & 32 ? 1 : 0) + (l & 16 ? 2 : 0).
+__device__ __forceinline__ double wave_sum4(const double (&q)[kQuads]) {
+  static_assert(kQuads == 4, "two halving steps");
+  const bool hi = threadIdx.x & 32, odd = threadIdx.x & 16;
+  const double a = (hi ? q[1] : q[0]) + __shfl_xor(hi ? q[0] : q[1], 32, 64);
+  const double b = (hi ? q[3] : q[2]) + __shfl_xor(hi ? q[2] : q[3], 32, 64);
+  double v = (odd ? b : a) + __shfl_xor(odd ? a : b, 16, 64);
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
 // The statistic's term as it is defined.
@@ -91,31 +112,33 @@ struct DeviceOps {
   }
 };
 
-// grid: (time-bin blocks, detector groups, runs of `run` sets); partial:
-// [sets][gx * gy].  A thread owns one time bin t = n dt and every detector of
-// its group for each set of its run: the counts d and their reciprocals are
-// formed once for all sets, and per set exp(-t/tau - (sigma t)^2 / 2) and
+// grid: (time-bin blocks, detector groups, runs of at most RUN sets); partial:
+// [sets][groups][blocks].  A thread owns one time bin t = n dt and every
+// detector of its group (G = kGroup, or kQuad where the blocks alone do not
+// fill the chip) for each set of its run: the counts d and their reciprocals
+// are formed once for all sets, and per set exp(-t/tau - (sigma t)^2 / 2) and
 // cos/sin of the precession angle gamma B t once for all detectors, whose
 // counts follow by cos(w t + phi_j) = cos(w t) cos(phi_j) - sin(w t)
 // sin(phi_j) in three multiply-adds.  Both quotients, (d - N)^2 / d and N / d
 // (log(d / N) = -log(N / d)), are products with 1 / d corrected by their exact
-// remainder, so they are rounded like divisions; a plain product would carry
-// the reciprocal's rounding, which is the same in every bin with that count.
+// remainder, so they are rounded like divisions.
 // Bound by FP64 vector issue: 133 sets of 16 x 206250 bins took 1.55 ms
-// (log-likelihood) when every term divided twice and ran the library
-// logarithm, 0.72 ms now.
-template <int STAT, bool DEV>
-__global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void k_musr_eval(const double* __restrict__ data, long long n_bins,
-                                                           double dt, Params prm, const double* __restrict__ dprm,
-                                                           int nparam, int n_det, int dg, int nsets, int run,
-                                                           double* __restrict__ partial) {
+// (log-likelihood; chi-square 0.56) when every term divided twice and ran the
+// library logarithm, 0.75 ms (0.30) now.  A single evaluation is bound by the
+// latency of its one chain per lane and by the two launches (12.6 -> 12.0 us).
+template <int STAT, bool DEV, int RUN, int G>
+__global__ __launch_bounds__(kThreads, RUN > 1 && STAT == DKS_MUSR_MLE ? 3 : 4) void k_musr_eval(
+    const double* __restrict__ data, long long n_bins, double dt, Params prm, const double* __restrict__ dprm,
+    int nparam, int n_det, int dg, int nsets, int run, double* __restrict__ partial) {
+  static_assert(DEV || RUN == 1, "one set by value");
+  constexpr int Q = G / kQuad;
   // per set of the run and detector of the group: N0, Nbkg, A0 N0 cos(phi), A0 N0 sin(phi)
-  __shared__ double cst[DEV ? kRun * kGroup * 4 : 1];
-  __shared__ double sums[DEV ? kRun : 1][kThreads / 64];
-  __shared__ double2 uv[DEV ? kRun : 1][DEV ? kThreads : 1];   // a lane's own entries: cos and sin parts per set
+  __shared__ double cst[RUN * G * 4];
+  __shared__ double sums[RUN][kQuads][kThreads / 64];
+  __shared__ double2 uv[RUN > 1 ? RUN : 1][RUN > 1 ? kThreads : 1];   // a lane's own entries: cos and sin parts per set
   const int tid = (int)threadIdx.x;
   const int set0 = blockIdx.z * run;
-  const int ns = DEV ? min(run, nsets - set0) : 1;
+  const int ns = RUN > 1 ? min(run, nsets - set0) : 1;
   const int j0 = blockIdx.y * dg;
   const int nj = min(dg, n_det - j0);
   const long long n = (long long)blockIdx.x * kThreads + tid;
@@ -123,117 +146,159 @@ __global__ __launch_bounds__(kThreads, DEV && STAT == DKS_MUSR_MLE ? 3 : 4) void
   const double* col = data + (size_t)j0 * n_bins + (live ? n : n_bins - 1);
   const double t = (double)n * dt;
   const double a = -t / kTauMu;
+  // (contractions written out: every instance rounds alike)
   auto damped = [&](double sigma, double B) {
-    const double EG = exp(a - 0.5 * (sigma * t) * (sigma * t));
+    const double st = sigma * t;
+    const double EG = exp(fma(-0.5 * st, st, a));
     double sw, cw;
     sincos(kGammaMu * B * t, &sw, &cw);
     return make_double2(EG * cw, -EG * sw);
   };
-  double d[kGroup], rd[kGroup];
-  double2 own;
-  if constexpr (DEV) {
-    // before the counts are loaded: their registers would be held through
-    // the sine's argument reduction, which needs many
-    for (int i = tid; i < ns * kGroup; i += kThreads) {
-      const int s = i / kGroup, j = i % kGroup;
+  auto constants = [&](int i, double N0, double Nb, double A0, double phi) {
+    double sp, cp;
+    sincos(phi, &sp, &cp);
+    double* c = cst + i * 4;
+    c[0] = N0;
+    c[1] = Nb;
+    c[2] = A0 * N0 * cp;
+    c[3] = A0 * N0 * sp;
+  };
+  double d[G], rd[G];
+  // (no load is conditional: a group's last detector is read again past its
+  // end, so the compiler can wait for the constants below without waiting for
+  // the counts)
+  auto load = [&]() {
+#pragma unroll
+    for (int j = 0; j < G; ++j) d[j] = col[(size_t)min(j, nj - 1) * n_bins];
+  };
+  // one set: the constants are requested before the counts and formed, with
+  // the lane's own factors, while those are on their way; a run's counts are
+  // loaded after its sines: their registers would be held through the argument
+  // reductions, which need many
+  if constexpr (RUN == 1) {
+    double q[4];
+    if (tid < nj) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        q[k] = DEV ? dprm[(size_t)set0 * nparam + 2 + 4 * (j0 + tid) + k] : prm.det[j0 + tid][k];
+    }
+    load();
+    if (tid < nj) constants(tid, q[0], q[1], q[2], q[3]);
+  } else {
+    for (int i = tid; i < ns * G; i += kThreads) {
+      const int s = i / G, j = i % G;
       if (j < nj) {
         const double* q = dprm + (size_t)(set0 + s) * nparam + 2 + 4 * (j0 + j);
-        double sp, cp;
-        sincos(q[3], &sp, &cp);
-        double* c = cst + i * 4;
-        c[0] = q[0];
-        c[1] = q[1];
-        c[2] = q[2] * q[0] * cp;
-        c[3] = q[2] * q[0] * sp;
+        constants(i, q[0], q[1], q[2], q[3]);
       }
     }
+  }
+  double2 own;
+  if constexpr (RUN > 1) {
 #pragma unroll 1
     for (int s = 0; s < ns; ++s) {
       const double* q = dprm + (size_t)(set0 + s) * nparam;
       uv[s][tid] = damped(q[0], q[1]);
     }
+    load();
+  } else if constexpr (DEV) {
+    const double* q = dprm + (size_t)set0 * nparam;
+    own = damped(q[0], q[1]);
+  } else {
+    own = damped(prm.sigma, prm.B);
   }
-#pragma unroll
-  for (int j = 0; j < kGroup; ++j) d[j] = j < nj ? col[(size_t)j * n_bins] : 1.0;
-  if constexpr (!DEV) own = damped(prm.sigma, prm.B);
   const double E = exp(a);
-  bool odd = false;          // some count out of the fast terms' range
+  bool odd[Q] = {};          // per four detectors: some count out of the fast terms' range
 #pragma unroll
-  for (int j = 0; j < kGroup; ++j) {
-    odd |= (d[j] != 0.0) & ((unsigned)__double2hiint(d[j]) - kLowWord > kHighWord - kLowWord);
+  for (int j = 0; j < G; ++j) {
+    odd[j / kQuad] |= (d[j] != 0.0) & ((unsigned)__double2hiint(d[j]) - kLowWord > kHighWord - kLowWord);
     rd[j] = d[j] > 0.0 ? recip<DeviceOps>(d[j]) : 0.5;         // quotient(n, 0, 1/2) = n
   }
-  if constexpr (DEV) __syncthreads();
+  __syncthreads();
 #pragma unroll 1
   for (int s = 0; s < ns; ++s) {
-    if constexpr (DEV) own = uv[s][tid];
+    if constexpr (RUN > 1) own = uv[s][tid];
     const double u = own.x, v = own.y;
-    // constants of detector j of the group: LDS, or scalar loads of the kernel argument
     auto model = [&](int j) {
-      if constexpr (DEV) {
-        const double* c = cst + (s * kGroup + j) * 4;
-        return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
-      } else {
-        const double* c = prm.det + 4 * (j0 + j);
-        return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
-      }
+      const double* c = cst + (s * G + j) * 4;
+      return fma(c[0], E, fma(c[2], u, fma(c[3], v, c[1])));
     };
-    double acc = 0.0;
-    // the largest high word of a quotient N / d, as a distance from the least
-    // one allowed, or of a square
-    constexpr unsigned least = STAT == DKS_MUSR_MLE ? kLowWord : 0u;
-    unsigned far = 0;
-    auto one = [&](int j) {
-      const double N = model(j);
-      if constexpr (STAT == DKS_MUSR_CHISQ) {
-        const double r = d[j] - N, r2 = r * r;
-        far = max(far, (unsigned)__double2hiint(r2));
-        acc += quotient(r2, d[j], rd[j]);
+    double acc[kQuads] = {0.0, 0.0, 0.0, 0.0};
+    bool slow[Q], any = !live;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      // the largest high word of a quotient N / d, as a distance from the
+      // least one allowed, or of a square
+      constexpr unsigned least = STAT == DKS_MUSR_MLE ? kLowWord : 0u;
+      unsigned far = 0;
+      auto one = [&](int j) {
+        const double N = model(j);
+        if constexpr (STAT == DKS_MUSR_CHISQ) {
+          const double r = d[j] - N, r2 = r * r;
+          far = max(far, (unsigned)__double2hiint(r2));
+          acc[q] += quotient(r2, d[j], rd[j]);
+        } else {
+          // d = 0 weighs its logarithm with 0
+          const double x = quotient(N, d[j], rd[j]);
+          far = max(far, (unsigned)__double2hiint(x) - least);
+          acc[q] += fma(-d[j], log_normal<DeviceOps>(x), N - d[j]);
+        }
+      };
+      const int jb = q * kQuad;
+      // whole fours with their chains interleaved, then the rest
+      if (jb + kQuad <= nj) {
+#pragma unroll
+        for (int j = jb; j < jb + kQuad; ++j) one(j);
       } else {
-        // d = 0 weighs its logarithm with 0
-        const double x = quotient(N, d[j], rd[j]);
-        far = max(far, (unsigned)__double2hiint(x) - least);
-        acc += fma(-d[j], log_normal<DeviceOps>(x), N - d[j]);
-      }
-    };
-    // four detectors at a time, their chains interleaved, then the rest
 #pragma unroll
-    for (int jb = 0; jb < kGroup; jb += 4) {
-      if (jb + 4 <= nj) {
-#pragma unroll
-        for (int j = jb; j < jb + 4; ++j) one(j);
-      } else {
-#pragma unroll
-        for (int j = jb; j < jb + 3; ++j)
+        for (int j = jb; j < jb + kQuad - 1; ++j)
           if (j < nj) one(j);
       }
+      slow[q] = odd[q] | (far > kHighWord - least);
+      any |= slow[q];
     }
-    if (odd || far > kHighWord - least) {
-      acc = 0.0;
+    if (any) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (live && !slow[q]) continue;
+        acc[q] = 0.0;
 #pragma unroll 1
-      for (int j = 0; j < nj; ++j) {
-        acc += term<STAT>(col[(size_t)j * n_bins], model(j));
+        for (int j = q * kQuad; live && j < min((q + 1) * kQuad, nj); ++j)
+          acc[q] += term<STAT>(col[(size_t)j * n_bins], model(j));
       }
     }
-    const double w = wave_sum(live ? acc : 0.0);
-    if ((tid & 63) == 0) sums[s][tid >> 6] = w;
+    const double w = wave_sum4(acc);
+    if ((tid & 15) == 0) sums[s][(tid >> 5 & 1) + (tid >> 4 & 1) * 2][tid >> 6] = w;
   }
   __syncthreads();
   if (tid < ns) {
     double w = 0.0;
-    for (int i = 0; i < kThreads / 64; ++i) w += sums[tid][i];
-    partial[(size_t)(set0 + tid) * gridDim.x * gridDim.y + blockIdx.y * gridDim.x + blockIdx.x] = w;
+    for (int q = 0; q * kQuad < nj; ++q) {
+      const double* p = sums[tid][q];
+      w += ((p[0] + p[1]) + p[2]) + p[3];
+    }
+    partial[((size_t)(set0 + tid) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = w;
   }
 }
 
-// One workgroup per set: the set's partials added in index order.
+// One workgroup per set: the partials of its nblk blocks of bins, each block's
+// gy groups added first (fours of detectors to sixteens, `per` of them, and
+// these in order).
 template <int STAT>
-__global__ __launch_bounds__(kThreads) void k_musr_final(const double* __restrict__ partial, int nblk,
+__global__ __launch_bounds__(kThreads) void k_musr_final(const double* __restrict__ partial, int nblk, int gy, int per,
                                                          double* __restrict__ result) {
   __shared__ double red[kThreads / 64];
-  const double* part = partial + (size_t)blockIdx.x * nblk;
+  const double* part = partial + (size_t)blockIdx.x * nblk * gy;
   double v = 0.0;
-  for (int i = (int)threadIdx.x; i < nblk; i += kThreads) v += part[i];
+  for (int i = (int)threadIdx.x; i < nblk; i += kThreads) {
+    double block = 0.0;
+    for (int g = 0; g < gy; g += per) {
+      double w = 0.0;
+      for (int u = g; u < min(g + per, gy); ++u) w += part[(size_t)u * nblk + i];
+      block += w;
+    }
+    v += block;
+  }
   const double tot = block_sum(v, red);
   if (threadIdx.x == 0) result[blockIdx.x] = STAT == DKS_MUSR_MLE ? 2.0 * tot : tot;
 }
@@ -249,7 +314,6 @@ struct dks_musr_plan_s {
   double dt;
   int max_sets;
   int bx;                 // time-bin workgroups
-  int dg, gy;             // detectors per group, groups
   size_t ws_total;
   char* ws;
   const double* data;
@@ -260,28 +324,52 @@ namespace {
 
 inline size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+int groups_of(int n_det, int dg) { return (n_det + dg - 1) / dg; }
+
+// Detectors per whole group: fours in as few groups of at most kGroup as hold
+// them, spread evenly.
+int group_size(int n_det) {
+  const int quads = groups_of(n_det, kQuad), groups = groups_of(quads, kQuads);
+  return (quads + groups - 1) / groups * kQuad;
+}
+
+// Groups of four detectors for a call of nsets sets: where a workgroup per
+// block, whole group and set would leave some of the chip's 256 CUs without
+// one (16 x 50000 bins, 196 blocks, log-likelihood: 11.2 us split; where there
+// are enough, each group's own exponentials and sines cost more than they
+// hide: 16 x 206250, 806 blocks, 16.2 us whole and 28 split).
+constexpr int kSplitFill = 256;
+bool split_groups(const dks_musr_plan_s* p, int nsets) {
+  return (long long)p->bx * groups_of(p->n_det, group_size(p->n_det)) * nsets < kSplitFill;
+}
+
+constexpr int kRunFill = 2048;
+
 template <int STAT, bool DEV>
 hipError_t launch(const dks_musr_plan_s* p, const Params& prm, const double* dprm, int nsets, double* result,
                   hipStream_t st) {
   double* partial = reinterpret_cast<double*>(p->ws);
-  // Batches: as many detectors per group as leave about four workgroups per
-  // CU (the plan's groups are those of one set), and runs of sets, which
-  // share the counts' reciprocals, as long as leave twice that.
-  int dg = p->dg, gy = p->gy, run = 1;
-  if (DEV) {
-    const long long per_group = (long long)p->bx * nsets;
-    gy = (int)std::min<long long>(gy, std::max<long long>((p->n_det + kGroup - 1) / kGroup, (1024 + per_group - 1) / per_group));
-    dg = (p->n_det + gy - 1) / gy;
-    gy = (p->n_det + dg - 1) / dg;
-    const int want = (int)std::min<long long>(kRun, std::max<long long>(1, per_group * gy / 2048));
+  const bool split = split_groups(p, nsets);
+  const int whole = group_size(p->n_det), dg = split ? kQuad : whole, gy = groups_of(p->n_det, dg);
+  // runs of sets, which share the counts' reciprocals, as long as leave eight
+  // workgroups per CU
+  int run = 1;
+  if (DEV && !split) {
+    const int want = (int)std::min<long long>(kRun, std::max<long long>(1, (long long)p->bx * gy * nsets / kRunFill));
     const int runs = (nsets + want - 1) / want;
     run = (nsets + runs - 1) / runs;
   }
-  hipLaunchKernelGGL((k_musr_eval<STAT, DEV>), dim3(p->bx, gy, (nsets + run - 1) / run), dim3(kThreads), 0, st,
-                     p->data, p->n_bins, p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, dg, nsets, run, partial);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(p->bx, gy, (nsets + run - 1) / run), dim3(kThreads), 0, st, p->data, p->n_bins,
+                       p->dt, prm, dprm, 2 + 4 * p->n_det, p->n_det, dg, nsets, run, partial);
+  };
+  constexpr int RUN = DEV ? kRun : 1;
+  if (split) go(k_musr_eval<STAT, DEV, RUN, kQuad>);
+  else go(k_musr_eval<STAT, DEV, RUN, kGroup>);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_musr_final<STAT>), dim3(nsets), dim3(kThreads), 0, st, partial, p->bx * gy, result);
+  hipLaunchKernelGGL((k_musr_final<STAT>), dim3(nsets), dim3(kThreads), 0, st, partial, p->bx, gy,
+                     split ? whole / kQuad : 1, result);
   return hipGetLastError();
 }
 
@@ -320,13 +408,11 @@ dks_status dks_musr_plan(int n_det, int64_t n_bins, double dt, int max_sets, dks
   p->dt = dt;
   p->max_sets = max_sets;
   p->bx = (int)((n_bins + kThreads - 1) / kThreads);
-  // share the per-bin transcendentals across as many detectors as a group
-  // holds while keeping at least ~512 workgroups per set in flight
-  const long long least = std::max<long long>((n_det + kGroup - 1) / kGroup, (512 + p->bx - 1) / p->bx);
-  const int groups = (int)std::min<long long>(n_det, least);
-  p->dg = (n_det + groups - 1) / groups;
-  p->gy = (n_det + p->dg - 1) / p->dg;
-  p->ws_total = al256((size_t)max_sets * p->bx * p->gy * sizeof(double));
+  // partials of the largest call, split or not
+  size_t sets_split = 0;
+  while ((int)sets_split < max_sets && split_groups(p, (int)sets_split + 1)) ++sets_split;
+  p->ws_total = al256(std::max((size_t)max_sets * groups_of(n_det, group_size(n_det)), sets_split * groups_of(n_det, kQuad)) *
+                      p->bx * sizeof(double));
   *out = p;
   return DKS_OK;
 }
@@ -368,15 +454,8 @@ dks_status dks_musr_eval(dks_musr_plan_t p, dks_musr_stat stat, const double* pa
   std::memset(&prm, 0, sizeof(prm));
   prm.sigma = params[0];
   prm.B = params[1];
-  for (int j = 0; j < p->n_det; ++j) {
-    const double* q = params + 2 + 4 * j;
-    prm.det[4 * j] = q[0];
-    prm.det[4 * j + 1] = q[1];
-    double sp, cp;
-    sincos(q[3], &sp, &cp);
-    prm.det[4 * j + 2] = q[2] * q[0] * cp;
-    prm.det[4 * j + 3] = q[2] * q[0] * sp;
-  }
+  for (int j = 0; j < p->n_det; ++j)
+    for (int q = 0; q < 4; ++q) prm.det[j][q] = params[2 + 4 * j + q];
   return run(p, stat, prm, nullptr, 1, result, static_cast<hipStream_t>(stream));
 }
 
