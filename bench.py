@@ -112,7 +112,7 @@ def measured_traffic(kernel, tile_order=False):
         sym += "_tile"          # the kernels' instances that work on the caller's arrays
     src = ("fft_kernels.hip" if sym.startswith("k_fft") else
            "particle_kernels.hip" if sym in ("k_bbox", "k_geometry_zero", "k_gradient") else "bin_kernels.hip")
-    fft = ("fft_engine.h", "fft_conv.h") if src == "fft_kernels.hip" else ()
+    fft = ("fft_engine.h", "fft_conv.h", "fft_lengths.h") if src == "fft_kernels.hip" else ()
     deps = (src, "dks_internal.h") + fft
     if any(not any(f.endswith(h) for f in doc["sources_sha256"]) for h in fft):
         return None

@@ -618,7 +618,6 @@ __global__ __launch_bounds__(kScatterThreads) void k_bin_scatter(ElemBatch eb, c
   static_assert(!STAGE || LDSHIST, "staging needs the LDS histogram");
   static_assert(!SCAN || STAGE, "the scan shares the staging's tile ownership");
   using P4 = Rec<T>;
-  using V = typename Vec16<T>::type;
   const int b = blockIdx.y;
   const dks_particle_set e = eb.at(b);
   const int64_t n = eb.n(e);

@@ -778,35 +778,7 @@ __global__ __launch_bounds__((block_threads<T, SP>())) void k_fft_x_inv(const ty
 // ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
-// Calls f with the compile-time plan equal to host plan h (tile width of 128
-// bytes, LD = W + PAD), or with DynPlan when none is or the caller rules the
-// compile-time kernels out (!allow: element offsets that may not fit 32
-// bits).  X: plans of the x rows; otherwise plans of the y and z pencils.
-// Plan creation (static_row, static_pencil) gives a length radices that only
-// the compile-time kernels know under the same conditions.
-template <typename T, int PAD, bool X, int N, class F> static bool try_plan(const FFTPlan& h, F&& f) {
-  constexpr int W = 128 / (2 * (int)sizeof(T));
-  if constexpr (X ? static_row(N) : static_pencil(N)) {
-    using SP = SPlan<N, W, W + PAD, false, RegCfg<T>::THREADS>;
-    if (plan_matches<SP>(h)) {
-      f(SP{});
-      return true;
-    }
-  }
-  return false;
-}
-template <typename T, int PAD, bool X, class F> static void with_plan(const FFTPlan& h, F&& f, bool allow = true) {
-  bool done = false;
-  if (allow) switch (h.N) {
-#define DKS_TRY(N) case N: done = try_plan<T, PAD, X, N>(h, f); break;
-    DKS_STATIC_LENGTHS(DKS_TRY)
-#undef DKS_TRY
-    default: break;
-  }
-  if (!done) f(DynPlan{});
-}
-
-static int device_cus() {
+static inline int device_cus() {
   static const int n = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
@@ -1013,13 +985,13 @@ hipError_t launch_fft_x_fwd(const void* in, size_t in_stride, bool fixed, void* 
   const bool pairs = (reinterpret_cast<uintptr_t>(in) % (2 * sizeof(T))) == 0 &&
                      (in_stride * sizeof(T)) % (2 * sizeof(T)) == 0;
   const int form = fixed ? kRowFixed : pairs ? kRowPairs : kRowReals;
-  with_plan<T, 1, true>(P.host, [&](auto sp) {
+  const bool ok = with_plan<T, 1, true>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_x_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()),
                        lds_bytes<T>(P.host) + (size_t)(m.nx + 1) * sizeof(C), s,
                        (const T*)in, in_stride, (C*)out, out_stride, m, P.dev, (const C*)post, nrows, magic_of(m.nx + 1),
                        magic_of(m.nx), form);
   });
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1038,11 +1010,11 @@ hipError_t launch_fft_y_fwd(const void* A, void* B, size_t stride, const MeshDim
   // stores in the other passes, or loads past the caches, gained nothing or lost.
   const size_t bytes = (size_t)m.Ny * m.nz * m.cs * sizeof(C) * batch;
   const bool stream = bytes >= ((size_t)64 << 20) && bytes <= ((size_t)384 << 20);
-  with_plan<T, 0, false>(P.host, [&](auto sp) {
+  const bool ok = with_plan<T, 0, false>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_y_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
                        (const C*)A, (C*)B, stride, m, P.dev, t0, stream);
   }, offsets_fit32(m));
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1054,8 +1026,9 @@ hipError_t launch_fft_z_conv(const void* B, void* Cout, size_t stride, const voi
   const int ntile = (col1 + W - 1) / W - t0;
   const int npt = (m.Ny / 2 + 1) * ntile;                 // pair-tile indices
   dim3 grid((unsigned)((npt + 7) / 8 * 16), batch);
-  bool ok = true;
-  with_plan<T, 0, false>(Pf.host, [&](auto sp) {
+  // plan creation builds the inverse plan from the same radices, reversed
+  bool inverse = true;
+  const bool ok = with_plan<T, 0, false>(Pf.host, [&](auto sp) {
     using SP = decltype(sp);
     auto launch = [&](auto spl) {
       hipLaunchKernelGGL((k_fft_z_conv<T, decltype(spl)>), grid, dim3(block_threads<T, decltype(spl)>()), lds_bytes<T>(Pf.host), s,
@@ -1063,7 +1036,7 @@ hipError_t launch_fft_z_conv(const void* B, void* Cout, size_t stride, const voi
     };
     if constexpr (SP::is_static) {
       if (!plan_matches<typename SP::Reversed>(Pi.host)) {
-        ok = false;            // plan creation builds the inverse plan from the same radices
+        inverse = false;
         return;
       }
       if constexpr (PipeOcc<T, SP>::fits) if (batch == 1) {
@@ -1078,10 +1051,11 @@ hipError_t launch_fft_z_conv(const void* B, void* Cout, size_t stride, const voi
       }
       launch(SP{});
     } else {
-      launch(DynPlan{});
+      inverse = runtime_plan(Pi.host);
+      if (inverse) launch(DynPlan{});
     }
   }, offsets_fit32(m));
-  return ok ? hipGetLastError() : hipErrorInvalidValue;
+  return ok && inverse ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1090,11 +1064,11 @@ hipError_t launch_fft_y_inv(const void* Cin, void* D, size_t stride, const MeshD
   using C = typename Cplx<T>::type;
   const int W = P.host.W, t0 = col0 / W;
   dim3 grid(m.nz + 2, (col1 + W - 1) / W - t0, batch);
-  with_plan<T, 0, false>(P.host, [&](auto sp) {
+  const bool ok = with_plan<T, 0, false>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_y_inv<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
                        (const C*)Cin, (C*)D, stride, m, P.dev, t0);
   }, offsets_fit32(m));
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -1118,12 +1092,12 @@ hipError_t launch_fft_x_inv(const void* D, size_t in_stride, void* phi_ext, size
     }
   }
   dim3 grid((nrows + P.host.W - 1) / P.host.W, batch);
-  with_plan<T, 1, true>(P.host, [&](auto sp) {
+  const bool ok = with_plan<T, 1, true>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_x_inv<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
                        (const C*)D, in_stride, (T*)phi_ext, out_stride, phi_user, m, P.dev, (const C*)post, nrows,
                        magic_of(m.nx + 2), magic_of(P.host.N));
   });
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 }  // namespace dks

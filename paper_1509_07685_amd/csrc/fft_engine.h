@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "dks_internal.h"
+#include "fft_lengths.h"
 
 namespace dks {
 
@@ -22,7 +23,7 @@ template <typename T> struct Cplx { using type = cpx<T>; };
 // complex values spread over the block's threads (512 for FP32, 256 for
 // FP64), i.e. 16 complex values per thread either way.
 template <typename T> struct RegCfg {
-  static constexpr int THREADS = sizeof(T) == 4 ? 512 : 256;
+  static constexpr int THREADS = PassLanes<T>::value;
   static constexpr int EMAX = kLdsBytes / (2 * (int)sizeof(T)) / THREADS;
   static constexpr int ARR = EMAX + 2;     // ceil(EMAX / R) * R <= EMAX + 2 for R in {2,3,4,8}
 };
@@ -315,104 +316,8 @@ __device__ __forceinline__ void run_fft(typename Cplx<T>::type* lds, const FFTPl
 }
 
 // ---------------------------------------------------------------------------
-// Compile-time plans.  For the lengths of static_radices (every 2^a 3^b from
-// 16 to 512) the kernels are instantiated with the whole plan known at
-// compile time (length, tile width, LDS stride, radix order, lanes), so
-// butterfly indexing, twiddle offsets and guards fold to constants; the
-// runtime plan above serves every other shape.  A launcher uses a
-// compile-time plan only when the host plan matches it exactly.
+// Kernels on compile-time plans (fft_lengths.h) or on the runtime plan.
 // ---------------------------------------------------------------------------
-constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
-constexpr int cmin(int a, int b) { return a < b ? a : b; }
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-
-struct DynPlan {
-  static constexpr bool is_static = false;
-};
-
-// Radix order of a length with a compile-time plan (n = 0: none, the length
-// runs on the runtime plan).  At most three passes, the two or three radices
-// near equal so that every pass keeps about the same lanes busy; the first
-// radix of an even length is even (a zero-padded forward transform then skips
-// its whole upper half), the last one too where the factors allow it.
-// Against the runtime plan, whose time went to index arithmetic, guards and
-// passes of radix 3 (the five passes of a solve): 96 x 96 x 192
-// FP64 180 -> 91 us, 8 x 48^3 FP32 in one batch 115 -> 36 us, 144 x 128 x 96
-// FP32 106 -> 56 us; raw 216 x 144 x 96 x 4 FP64, there and back, 410 -> 288 us.
-struct RadixList {
-  int n;
-  int r[3];
-};
-constexpr RadixList static_radices(int N) {
-  switch (N) {
-    case 16: return {2, {4, 4, 1}};
-    case 18: return {2, {6, 3, 1}};
-    case 24: return {2, {6, 4, 1}};
-    case 27: return {2, {9, 3, 1}};
-    case 32: return {2, {8, 4, 1}};
-    case 36: return {2, {6, 6, 1}};
-    case 48: return {2, {8, 6, 1}};
-    case 54: return {2, {6, 9, 1}};
-    case 64: return {2, {8, 8, 1}};
-    case 72: return {2, {12, 6, 1}};
-    case 81: return {2, {9, 9, 1}};
-    case 96: return {2, {8, 12, 1}};
-    case 108: return {2, {12, 9, 1}};
-    case 128: return {2, {16, 8, 1}};
-    case 144: return {2, {12, 12, 1}};
-    case 162: return {3, {6, 3, 9}};
-    case 192: return {2, {16, 12, 1}};
-    case 216: return {3, {6, 6, 6}};
-    case 243: return {3, {9, 9, 3}};
-    case 256: return {3, {8, 8, 4}};
-    case 288: return {3, {8, 6, 6}};
-    case 324: return {3, {6, 9, 6}};
-    case 384: return {3, {8, 6, 8}};
-    case 432: return {3, {6, 9, 8}};
-    case 486: return {3, {6, 9, 9}};
-    case 512: return {3, {8, 8, 8}};
-    default: return {0, {1, 1, 1}};
-  }
-}
-
-// Lengths with compile-time kernels in the convolution: x rows (pairs of
-// reals: even lengths) up to 256, y and z pencils (doubled extents) from 32,
-// where the intermediates' element offsets fit 32 bits.
-constexpr bool static_row(int N) { return N % 2 == 0 && N <= 256 && static_radices(N).n > 0; }
-constexpr bool static_pencil(int N) { return N % 2 == 0 && N >= 32 && static_radices(N).n > 0; }
-
-// The lengths above, for switches over them.
-#define DKS_STATIC_LENGTHS(F) \
-  F(16) F(18) F(24) F(27) F(32) F(36) F(48) F(54) F(64) F(72) F(81) F(96) F(108) F(128) F(144) F(162) F(192) F(216) \
-  F(243) F(256) F(288) F(324) F(384) F(432) F(486) F(512)
-
-// Compile-time plan of length N (radix order static_radices, REV reversed:
-// the inverse z transform), W pencils per tile with LDS stride LD, at most
-// CAP lanes per workgroup.  TH lanes run the tile: the widest pass's
-// butterflies in the fewest rounds that CAP allows, so a short transform does
-// not carry idle wavefronts through its barriers.
-template <int N_, int W_, int LD_, bool REV_, int CAP_>
-struct SPlan {
-  static constexpr bool is_static = true;
-  static constexpr int N = N_, W = W_, LD = LD_, logW = ilog2(W_);
-  static constexpr RadixList list = static_radices(N_);
-  static_assert(list.n > 0 && list.r[0] * list.r[1] * list.r[2] == N_, "radices of a compile-time plan");
-  static constexpr int npass = list.n;
-  static constexpr int R(int p) { return REV_ ? list.r[npass - 1 - p] : list.r[p]; }
-  static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * R(p - 1); }
-  static constexpr int tw_off(int p) { return p <= 1 ? 0 : tw_off(p - 1) + Ns(p - 1) * (R(p - 1) - 1); }
-  static constexpr int widest() {
-    int m = 0;
-    for (int p = 0; p < npass; ++p) m = N / R(p) > m ? N / R(p) : m;
-    return m * W;
-  }
-  static constexpr int rounds = (widest() + CAP_ - 1) / CAP_;
-  static constexpr int TH = ((widest() + rounds - 1) / rounds + 63) / 64 * 64;
-  // the first radix is even, so the first pass's upper half inputs are r >= R/2
-  static constexpr bool even_first = R(0) % 2 == 0;
-  using Reversed = SPlan<N_, W_, LD_, !REV_, CAP_>;
-};
-
 // Lanes per workgroup of a pass kernel.
 template <typename T, class SP> constexpr int block_threads() {
   if constexpr (SP::is_static) return SP::TH;
@@ -578,13 +483,6 @@ static inline unsigned magic_of(int d) {
 template <typename T>
 static inline size_t lds_bytes(const FFTPlan& P) {
   return (size_t)P.N * P.LD * sizeof(typename Cplx<T>::type);
-}
-
-template <class SP> static inline bool plan_matches(const FFTPlan& h) {
-  if (h.N != SP::N || h.W != SP::W || h.LD != SP::LD || h.npass != SP::npass) return false;
-  for (int p = 0; p < h.npass; ++p)
-    if (h.R[p] != SP::R(p) || h.Ns[p] != SP::Ns(p) || h.tw_off[p] != SP::tw_off(p)) return false;
-  return true;
 }
 
 }  // namespace dks

@@ -4,9 +4,10 @@
 // every 1-D plan they are launched with:
 //
 //   V1  structure: 1 <= N <= max_length; npass <= max_pass, and npass = 0
-//       only for N = 1 (a copy through the tile); every radix
-//       is 2, 3, 4, 6, 8, 9, 12 or 16 and their product is N; Ns[0] = 1 and
-//       Ns[p + 1] = Ns[p] R[p]; twiddle offsets tw_off[0] = tw_off[1] = 0 and
+//       only for N = 1 (a copy through the tile); every radix is 2, 3, 4 or
+//       8, those of the runtime plan's passes, or also 6, 9, 12 or 16 where
+//       the caller says that the plan is a compile-time one's (fixed), and
+//       their product is N; Ns[0] = 1 and Ns[p + 1] = Ns[p] R[p]; twiddle offsets tw_off[0] = tw_off[1] = 0 and
 //       tw_off[p + 1] = tw_off[p] + Ns[p] (R[p] - 1)
 //   V2  tile shape: W is a power of two, logW = log2 W, LD is W or W + 1
 //   V3  butterfly coverage: a pass of radix R gives each thread
@@ -54,10 +55,11 @@ enum PlanViolation : int {
 // csize: bytes per complex value.  tile_elems / tile_regs: V4's row length
 // and per-thread register count (tile_regs = 0: the kernel does not stage
 // its tile through registers).  extra_lds: LDS bytes the kernel uses beside
-// the tile.
+// the tile.  fixed: the plan is one that the compile-time kernels are built
+// with.
 template <class Plan>
 inline int fft_plan_violation(const Plan& P, const EngineLimits& L, size_t csize, int tile_elems, int tile_regs,
-                              size_t extra_lds) {
+                              size_t extra_lds, bool fixed = false) {
   // V1
   if (P.N < 1 || P.N > L.max_length || P.npass < 0 || P.npass > L.max_pass) return kPlanStructure;
   if ((P.npass == 0) != (P.N == 1)) return kPlanStructure;
@@ -65,7 +67,8 @@ inline int fft_plan_violation(const Plan& P, const EngineLimits& L, size_t csize
   int tw = 0;
   for (int p = 0; p < P.npass; ++p) {
     const int R = P.R[p];
-    if (R != 2 && R != 3 && R != 4 && R != 6 && R != 8 && R != 9 && R != 12 && R != 16) return kPlanStructure;
+    const bool wide = R == 6 || R == 9 || R == 12 || R == 16;
+    if (R != 2 && R != 3 && R != 4 && R != 8 && !(fixed && wide)) return kPlanStructure;
     if (P.Ns[p] != prod) return kPlanStructure;
     if (P.tw_off[p] != tw) return kPlanStructure;
     if (p > 0) tw += P.Ns[p] * (R - 1);

@@ -212,9 +212,22 @@ dks_status dks_fft_plan(int nx, int ny, int nz, int batch, dks_fft_kind kind, dk
     L.max_length = kMaxLength;
     L.max_pass = kMaxPass;
     L.lds_hw = kLdsHardware;
-    int v = fft_plan_violation(p->pl[0].dev, L, p->csize, mx, L.emax,
-                               p->half ? (size_t)(mx + 1) * p->csize : 0);
-    for (int a = 1; a < 3 && v == kPlanOk; ++a) v = fft_plan_violation(p->pl[a].dev, L, p->csize, 0, 0, 0);
+    bool fixed[3] = {false, false, false};     // the launchers' choice
+    for (int a = 0; a < 3; ++a) {
+      const auto see = [&](auto sp) { fixed[a] = decltype(sp)::is_static; };
+      const auto pick = [&](auto t) {
+        using T = decltype(t);
+        if (a == 0) with_row_plan<T>(p->pl[0].dev, see);
+        else with_col_plan<T>(p->pl[a].dev, see, fit);
+      };
+      if (dtype == DKS_F32) pick(0.0f);
+      else pick(0.0);
+    }
+    int v = fft_plan_violation(p->pl[0].dev, L, p->csize, mx, L.emax, p->half ? (size_t)(mx + 1) * p->csize : 0,
+                               fixed[0]);
+    for (int a = 1; a < 3 && v == kPlanOk; ++a) v = fft_plan_violation(p->pl[a].dev, L, p->csize, 0, 0, 0, fixed[a]);
+    // half-length rows have compile-time kernels only
+    if (p->half && !fixed[0]) v = kPlanStructure;
     if (v != kPlanOk) {
       delete p;
       return DKS_EUNSUPPORTED;

@@ -271,60 +271,17 @@ __global__ __launch_bounds__((block_threads<T, SP>())) void k_fftr_cols(const ty
   run_any<T, INV, true, SP, 0>(lds, P, rd, wr);
 }
 
-template <typename T, int N> using RowPlan =
-    SPlan<N, row_width(N, 2 * (int)sizeof(T), 128 / (2 * (int)sizeof(T))),
-          row_width(N, 2 * (int)sizeof(T), 128 / (2 * (int)sizeof(T))) + 1, false, RegCfg<T>::THREADS>;
-// Column tiles of 128 bytes per row of the array, or 256 (WIDE).
-template <typename T, int N, bool WIDE> using ColPlan =
-    SPlan<N, (WIDE ? 256 : 128) / (2 * (int)sizeof(T)), (WIDE ? 256 : 128) / (2 * (int)sizeof(T)), false,
-          RegCfg<T>::THREADS>;
-
-// Calls f with the compile-time plan equal to host plan h, or with DynPlan.
-// Plan creation gives a length the radices of static_radices exactly where
-// the compile-time kernels run it: every row, and columns whose array is
-// addressable with 32-bit element offsets.
-template <class SP, class F> static bool try_plan(const FFTPlan& h, F&& f) {
-  if (!plan_matches<SP>(h)) return false;
-  f(SP{});
-  return true;
-}
-template <typename T, class F> static void with_row_plan(const FFTPlan& h, F&& f) {
-  bool done = false;
-  switch (h.N) {
-#define DKS_TRY(N) case N: done = try_plan<RowPlan<T, N>>(h, f); break;
-    DKS_STATIC_LENGTHS(DKS_TRY)
-#undef DKS_TRY
-    default: break;
-  }
-  if (!done) f(DynPlan{});
-}
-
-template <typename T, class F> static void with_col_plan(const FFTPlan& h, F&& f, bool off32) {
-  bool done = false;
-  if (off32) switch (h.N) {
-#define DKS_TRY(N)                                                                           \
-  case N:                                                                                    \
-    if constexpr (N <= kWideMaxLength) done = try_plan<ColPlan<T, N, true>>(h, f);           \
-    if (!done) done = try_plan<ColPlan<T, N, false>>(h, f);                                  \
-    break;
-    DKS_STATIC_LENGTHS(DKS_TRY)
-#undef DKS_TRY
-    default: break;
-  }
-  if (!done) f(DynPlan{});
-}
-
 template <typename T, bool INV, int KIND>
 hipError_t launch_rows(const void* in, void* out, long long nrows, const PlanRef& P, int in_len, int out_len,
                               hipStream_t s) {
   const long long nblk = (nrows + P.host.W - 1) / P.host.W;
   if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-  with_row_plan<T>(P.host, [&](auto sp) {
+  const bool ok = with_row_plan<T>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fftr_rows<T, decltype(sp), INV, KIND>), dim3((unsigned)nblk),
                        dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s, in, out, nrows, P.dev, in_len, out_len, magic_of(in_len),
                        magic_of(out_len));
   });
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 // Real rows of even length on the half-length plan P (real_rows_half).
@@ -357,11 +314,11 @@ hipError_t launch_cols(const void* in, void* out, int ncols, size_t S, int noute
   if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
   // 32-bit offsets inside a pencil tile when the whole array is addressable with them
   const bool off32 = cols_fit32(elems);
-  with_col_plan<T>(P.host, [&](auto sp) {
+  const bool ok = with_col_plan<T>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fftr_cols<T, decltype(sp), INV>), dim3((unsigned)nblk),
                        dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s, (const C*)in, (C*)out, ncols, ntile, S, d1, s1, s2, P.dev);
   }, off32);
-  return hipGetLastError();
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 }  // namespace dks

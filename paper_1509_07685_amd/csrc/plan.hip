@@ -322,6 +322,15 @@ template <typename T> EngineLimits engine_limits() {
   return L;
 }
 
+// Whether the launchers run host plan h on a compile-time plan.
+template <int PAD, bool X> bool fixed_plan(const dks_poisson_plan_s* p, const FFTPlan& h, bool allow) {
+  bool fixed = false;
+  const auto see = [&](auto sp) { fixed = decltype(sp)::is_static; };
+  if (p->dtype == DKS_F32) with_plan<float, PAD, X>(h, see, allow);
+  else with_plan<double, PAD, X>(h, see, allow);
+  return fixed;
+}
+
 // Checks the four plans against the invariants of the pass kernels that use
 // them: x forward (rows of nx reals staged through kTileReals registers per
 // thread, nx + 1 post-twiddles in LDS beside the tile), x inverse (rows of N
@@ -331,11 +340,14 @@ int check_plans(const dks_poisson_plan_s* p) {
   const EngineLimits L = p->dtype == DKS_F32 ? engine_limits<float>() : engine_limits<double>();
   const size_t c = p->csize;
   const int nx = p->md.nx;
-  int v = fft_plan_violation(p->px.dev, L, c, nx, kTileReals, (size_t)(nx + 1) * c);
-  if (v == kPlanOk) v = fft_plan_violation(p->px.dev, L, c, p->px.dev.N, kTileReals, 0);
-  if (v == kPlanOk) v = fft_plan_violation(p->py.dev, L, c, 0, 0, 0);
-  if (v == kPlanOk) v = fft_plan_violation(p->pz.dev, L, c, 0, 0, 0);
-  if (v == kPlanOk) v = fft_plan_violation(p->pzi.dev, L, c, 0, 0, 0);
+  const bool fit = offsets_fit32(p->md);
+  const bool fx = fixed_plan<1, true>(p, p->px.dev, true), fy = fixed_plan<0, false>(p, p->py.dev, fit),
+             fz = fixed_plan<0, false>(p, p->pz.dev, fit);
+  int v = fft_plan_violation(p->px.dev, L, c, nx, kTileReals, (size_t)(nx + 1) * c, fx);
+  if (v == kPlanOk) v = fft_plan_violation(p->px.dev, L, c, p->px.dev.N, kTileReals, 0, fx);
+  if (v == kPlanOk) v = fft_plan_violation(p->py.dev, L, c, 0, 0, 0, fy);
+  if (v == kPlanOk) v = fft_plan_violation(p->pz.dev, L, c, 0, 0, 0, fz);
+  if (v == kPlanOk) v = fft_plan_violation(p->pzi.dev, L, c, 0, 0, 0, fz);
   return v;
 }
 
