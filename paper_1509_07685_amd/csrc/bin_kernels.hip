@@ -1772,22 +1772,25 @@ hipError_t launch_unsort(const ElemBatch& eb, int batch, const char* sorted_base
 
 // Where a solve deposits and gathers without binning.
 //
-// Deposit: scattered device atomics come to about 7e9 a second where many
-// particles share a node (32^3 halo bunch) and 2e10 on sparse meshes, the
-// count, scan, scatter and binned deposit to 25 us and more.  Measured, direct
-// against binned (whole step, FP32 CIC): 1e4 particles 42 against 65 us on
-// 32^3, 48 / 75 on 64^3, 91 / 130 on 128^3; 3.2e4 67 / 74, 62 / 83, 102 / 133;
-// 6.6e4 105 / 78 on 32^3.  FP64 totals hold 2^15 weights of at most 1 on their
-// scale of 2^49.
+// Deposit: scattered device atomics come to 2e10 a second, the count, scan,
+// scatter and binned deposit to 25 us and more.  Measured, direct against
+// binned (whole step, FP32 CIC, bunches of 0.15 and 0.02 of the mesh): 1e4
+// particles 38 / 54 and 38 / 71 us on 32^3, 41 / 67 and 38 / 71 on 64^3, 90 /
+// 126 and 88 / 111 on 128^3; 3.2e4 42 / 63 and 40 / 83, 50 / 72 and 42 / 86,
+// 97 / 129 and 91 / 121.  FP64 totals hold 2^15 weights of at most 1 on their
+// scale of 2^49.  FP32 totals are 8 bytes per node, to be cleared and read,
+// against 4 of the weights: 27 us at the copy rate for 2^24 nodes in all, the
+// least that is saved (deposit alone, 1e3 particles in 0.02 of the mesh: 256^3
+// 69 / 67 us, 1e4 70 / 73; 384^3 316 / 311).  A slot's node number has 32 bits.
 //
 // Gather: its reads of phi by random particles cost 1.4 (32^3) to 5.3 us
 // (128^3) per 2^16 particles, the binned gather with its unsort about 20 us up
 // to a few 1e5 particles.
 bool direct_deposit_fits(const ElemBatch& eb, int batch, bool f64, const MeshDims& m, const BinGeom& bg) {
   const int64_t w = bg.scheme == kSchemeNGP ? 1 : bg.scheme == kSchemeTSC ? 27 : 8;
-  const int64_t n = eb.max_np;
-  return n < (f64 ? 1 << 15 : 1 << 18) && n * w <= (1 << 18) && n * batch * w <= (1 << 19) &&
-         n <= 2 * (int64_t)m.nx * m.ny * m.nz;
+  const int64_t n = eb.max_np, nodes = (int64_t)m.nx * m.ny * m.nz;
+  return n < (f64 ? 1 << 15 : 1 << 18) && n * w <= (1 << 18) && n * batch * w <= (1 << 19) && n <= 2 * nodes &&
+         (f64 ? nodes < kNoNode : nodes * batch <= (1 << 24));
 }
 bool direct_gather_fits(const ElemBatch& eb, int batch) { return eb.max_np <= (1 << 18) / batch; }
 
