@@ -32,3 +32,12 @@ def kernels(n, dt, scheme, num):
 ])
 def test_small_deposits_on_large_meshes(n, dt, direct):
     assert ("bin_count" not in kernels(n, dt, "cic", 1000)) == direct
+
+
+@pytest.mark.parametrize("scheme,num,direct", [
+    ("cic", 1 << 18, True), ("cic", (1 << 18) + 1, False), ("ngp", 1 << 18, True), ("ngp", (1 << 18) + 1, False),
+    ("tsc", 1 << 16, True), ("tsc", (1 << 16) + 1, False),      # 162 reads of phi a particle
+])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_gathers_in_the_callers_order(dt, scheme, num, direct):
+    assert ("unsort" not in kernels((32, 24, 36), dt, scheme, num)) == direct
