@@ -1512,9 +1512,8 @@ __global__ __launch_bounds__(kDirectThreads) void k_gather_direct(ElemBatch eb, 
   const Geometry* g = geo_of(geo, stride, b);
   const Cell<T, SCH> c = locate<T, SCH>(((const T*)e.x)[i], ((const T*)e.y)[i], ((const T*)e.z)[i], g, m, bg);
   T ax = 0, ay = 0, az = 0;
-  if (c.key == bg.K) {           // outside: +0, whatever the coefficients' sign and value
-    ((T*)e.Ex)[i] = ((T*)e.Ey)[i] = ((T*)e.Ez)[i] = (T)0;
-  } else {
+  const bool in = c.key != bg.K;
+  if (in) {
     const int sy = m.nx + 2, sz = (m.nx + 2) * (m.ny + 2);
     // phi_ext index = node + 1 per axis
     const T* o = phi_ext + (size_t)b * phi_stride + (size_t)(c.bz + 1) * sz + ((c.by + 1) * sy + c.bx + 1);
@@ -1529,10 +1528,11 @@ __global__ __launch_bounds__(kDirectThreads) void k_gather_direct(ElemBatch eb, 
     } else {
       interp_phi<T, SCH>(o, sy, sz, c, ax, ay, az);
     }
-    ((T*)e.Ex)[i] = ax * Geo<T>::grad(g, 0);
-    ((T*)e.Ey)[i] = ay * Geo<T>::grad(g, 1);
-    ((T*)e.Ez)[i] = az * Geo<T>::grad(g, 2);
   }
+  // outside: +0, whatever the coefficients' sign and value
+  ((T*)e.Ex)[i] = ax * (in ? Geo<T>::grad(g, 0) : (T)0);
+  ((T*)e.Ey)[i] = ay * (in ? Geo<T>::grad(g, 1) : (T)0);
+  ((T*)e.Ez)[i] = az * (in ? Geo<T>::grad(g, 2) : (T)0);
 }
 
 // ---------------------------------------------------------------------------
