@@ -184,10 +184,19 @@ inline bool cols_fit32(size_t elems) { return elems < 0x7fffffffULL; }
 // run per segment raised the z pass of 512 x 512 x 256 FP32 from 3.7 to 4.8
 // TB/s (290 -> 222 us) and the 216 x 144 x 96 x 4 FP64 columns from 50 and 49
 // to 30 and 40 us.  Smaller arrays stay in the caches and want the larger
-// number of tiles (96^3 FP64: 22.7 against 25.5 us for the three passes).
+// number of tiles (96^3 FP64: 22.7 against 25.5 us for the three passes).  Over
+// a length of 192 only two of the wide tiles fit a CU's LDS, which costs more
+// than the run gains unless the narrow segments are ragged (rows that are no
+// multiple of 64 bytes) or the array is of 192 MiB and more (the last-level
+// cache holds 256).  There and back, 128 against 256 bytes: aligned 256^3 FP32
+// (128 MiB) 258 / 268 us, 256 x 256 x 128 FP64 (128) 257 / 265, 216^3 FP64 (154)
+// 333 / 340, but 192^3 x 2 FP32 (108) 216 / 212, 256 x 256 x 192 FP64 (192) 412 /
+// 409 and 256^3 x 2 FP32 (256) 562 / 551; ragged 243^3 FP32 (109) 337 / 299.
 constexpr int kWideMaxLength = 256;
-inline bool wide_columns(int N, size_t elems, size_t csize) {
-  return N <= kWideMaxLength && static_radices(N).n > 0 && cols_fit32(elems) && elems * csize >= ((size_t)64 << 20);
+inline bool wide_columns(int N, size_t elems, size_t csize, size_t row_bytes) {
+  const size_t bytes = elems * csize;
+  if (N > kWideMaxLength || static_radices(N).n == 0 || !cols_fit32(elems) || bytes < ((size_t)64 << 20)) return false;
+  return N <= 192 || row_bytes % 64 != 0 || bytes >= ((size_t)192 << 20);
 }
 
 // Real rows of even length whose half has compile-time kernels.

@@ -190,7 +190,7 @@ dks_status dks_fft_plan(int nx, int ny, int nz, int batch, dks_fft_kind kind, dk
   const size_t elems = row_len_complex(p) * (size_t)ny * nz * batch;
   const bool fit = cols_fit32(elems);
   for (int a = 1; a < 3; ++a) {
-    int W = wide_columns(ns[a], elems, c) ? 2 * wmax : wmax;
+    int W = wide_columns(ns[a], elems, c, row_len_complex(p) * c) ? 2 * wmax : wmax;
     while (W > 1 && (size_t)ns[a] * W * c > (size_t)kLdsBytes) W >>= 1;
     make_axis(p->pl[a], ns[a], W, W, fit);
   }

@@ -125,7 +125,7 @@ template <typename T> static void run(const char* name) {
     // raw columns of small, large and not 32-bit addressable arrays
     for (size_t elems : {(size_t)n * 64, (size_t)1 << 27, (size_t)1 << 31}) {
       const bool fit = cols_fit32(elems);
-      int W = wide_columns(n, elems, c) ? 2 * wmax : wmax;
+      int W = wide_columns(n, elems, c, 64) ? 2 * wmax : wmax;
       while (W > 1 && (size_t)n * W * c > (size_t)kLdsBytes) W >>= 1;
       const Plan pc = make(n, radices(n, fit), W, W);
       Count& k = fit ? cols : far_cols;
