@@ -1000,16 +1000,17 @@ hipError_t launch_fft_y_fwd(const void* A, void* B, size_t stride, const MeshDim
   using C = typename Cplx<T>::type;
   const int W = P.host.W, t0 = col0 / W;
   dim3 grid((col1 + W - 1) / W - t0, m.nz, batch);
-  // Stores past the caches for a B that the last-level cache (256 MB) holds
+  // Stores past the caches for a B that the last-level cache (256 MiB) holds
   // only in part by the time the z pass, in another order and beside its own
-  // output, reads it.  Whole mesh solves, ordinary against these stores:
-  // FP32 128^3 (B of 38 MB) 85 and 88 us, 256x128x128 (71 MB) 144 and 140,
-  // 192^3 (123 MB) 230 and 226, 216^3 (167 MB) 409 and 402, 256^3 (285 MB) 509
-  // and 488; FP64 96x96x192 (61 MB) 121 and 122, 144^3 (101 MB) 195 and 193,
-  // 192^3 (236 MB) 419 and 402, but 256^3 (554 MB) 937 and 954.  The same
-  // stores in the other passes, or loads past the caches, gained nothing or lost.
+  // output, reads it.  Mesh solves for the potential, ordinary against these
+  // stores: FP32 256x128x128 (B of 68 MiB) 111.7 and 114.8 us, 128x192x192 (81)
+  // 126.5 and 130.4, 192^3 (117) 197 and 192, 256x256x128 (136) 230 and 222, 256^3
+  // (272) 459 and 437, 256x256x288 (306) 777 and 740; FP64 128^3 (68) 101.4 and
+  // 103.5, 144^3 (96) 163 and 159, 162^3 (135) 241 and 230, 216^3 (319) 616 and 581,
+  // but 256^3 (528, with the field) 937 and 954.  The same stores in the other
+  // passes, or loads past the caches, gained nothing or lost.
   const size_t bytes = (size_t)m.Ny * m.nz * m.cs * sizeof(C) * batch;
-  const bool stream = bytes >= ((size_t)64 << 20) && bytes <= ((size_t)384 << 20);
+  const bool stream = bytes >= ((size_t)90 << 20) && bytes <= ((size_t)384 << 20);
   const bool ok = with_plan<T, 0, false>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_y_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
                        (const C*)A, (C*)B, stride, m, P.dev, t0, stream);
