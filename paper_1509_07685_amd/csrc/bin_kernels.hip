@@ -1788,18 +1788,20 @@ hipError_t launch_unsort(const ElemBatch& eb, int batch, const char* sorted_base
 // follows the stencil's reads: 32 values of phi (CIC) or 6 (NGP) and 162
 // (TSC).  Whole steps, direct against binned, bunch of 0.15 of the mesh: CIC
 // with 2.6e5 particles FP32 81 / 81 us on 64^3, 136 / 140 on 128^3, 570 / 608 on
-// 256^3, FP64 87 / 88, 175 / 178, 964 / 969; TSC FP32 with 8e4 90 / 95, 132 /
-// 140, 553 / 567 and with 1.3e5 100 / 96, 146 / 143, 585 / 574, FP64 with 4e4
-// 90 / 100, 165 / 172, 924 / 948, with 8e4 109 / 109, 180 / 182, 981 / 963 and
-// with 1.3e5 125 / 111, 205 / 187, 1048 / 973.
+// 256^3, FP64 87 / 88, 175 / 178, 964 / 969; TSC FP32 with 1.3e5 100 / 96, 146 /
+// 143, 585 / 574 and with 2e5 112 / 98, 166 / 149, 625 / 581, FP64 with 8e4 109 /
+// 109, 180 / 182, 981 / 963 and with 1.3e5 125 / 111, 205 / 187, 1048 / 973.
+// Bunches with a dense core gain to higher counts (fitted mesh over a core with
+// tails, 1e5 TSC: FP32 97 / 107 on 64^3, 141 / 149 on 128^3, FP64 112 / 123 on
+// 64^3), so the TSC lines lie at the upper end of the even ones.
 bool direct_deposit_fits(const ElemBatch& eb, int batch, bool f64, const MeshDims& m, const BinGeom& bg) {
   const int64_t w = bg.scheme == kSchemeNGP ? 1 : bg.scheme == kSchemeTSC ? 27 : 8;
   const int64_t n = eb.max_np, nodes = (int64_t)m.nx * m.ny * m.nz;
   return n < (f64 ? 1 << 15 : 1 << 18) && n * w <= (1 << 18) && n * batch * w <= (1 << 19) && n <= 2 * nodes &&
          (f64 ? nodes < kNoNode : nodes * batch <= (1 << 24));
 }
-bool direct_gather_fits(const ElemBatch& eb, int batch, const BinGeom& bg) {
-  return eb.max_np <= (bg.scheme == kSchemeTSC ? 1 << 16 : 1 << 18) / batch;
+bool direct_gather_fits(const ElemBatch& eb, int batch, bool f64, const BinGeom& bg) {
+  return eb.max_np <= (bg.scheme != kSchemeTSC ? 1 << 18 : f64 ? 3 << 15 : 1 << 17) / batch;
 }
 
 template <typename T>

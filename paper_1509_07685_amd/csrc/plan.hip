@@ -58,7 +58,7 @@ template <typename T> hipError_t launch_gather_binned(const Geometry*, size_t, c
                                                       void* const*, hipStream_t);
 template <typename T> hipError_t launch_unsort(const ElemBatch&, int, const char*, size_t, size_t, hipStream_t);
 bool direct_deposit_fits(const ElemBatch&, int, bool, const MeshDims&, const BinGeom&);
-bool direct_gather_fits(const ElemBatch&, int, const BinGeom&);
+bool direct_gather_fits(const ElemBatch&, int, bool, const BinGeom&);
 template <typename T> hipError_t launch_deposit_direct(const ElemBatch&, int, const Geometry*, size_t, void*, size_t,
                                                        const MeshDims&, const BinGeom&, hipStream_t);
 template <typename T> hipError_t launch_gather_direct(const ElemBatch&, int, const Geometry*, size_t, const void*,
@@ -576,7 +576,7 @@ dks_status solve_particles_t(const dks_poisson_plan_s* p, int batch, const Slots
   const PartWork w = part_work(p, eb.max_np);
   const bool direct = deposit_direct(p, batch, eb, sorted_out != nullptr);
   // gathered in the input order: no permutation and no unsort
-  const bool in_order = !sorted_out && (direct || direct_gather_fits(eb, batch, p->bg));
+  const bool in_order = !sorted_out && (direct || direct_gather_fits(eb, batch, p->dtype == DKS_F64, p->bg));
   const size_t inv_off = in_order ? kNoInverse : inv_offset(p, eb.max_np);
   dks_status r = deposit_stage<T>(p, batch, sl, eb, direct, sorted, sorted_stride, inv_off, w, st, sorted_out);
   if (r != DKS_OK) return r;
