@@ -1566,8 +1566,7 @@ static int compute_units() {
 
 template <typename T>
 hipError_t launch_bin_count(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, char* slot_base, size_t bins_off,
-                            const MeshDims& m, const BinGeom& bg, int nblk, hipStream_t s) {
-  (void)nblk;
+                            const MeshDims& m, const BinGeom& bg, hipStream_t s) {
   if (eb.max_np == 0) return hipSuccess;
   const int64_t nchunk = (eb.max_np + scatter_chunk<T>() - 1) / scatter_chunk<T>();
   // a multiple of kXcd, so every chunk a workgroup walks is in one XCD group
@@ -1632,8 +1631,7 @@ template <typename T> bool scatter_scans(const ElemBatch& eb, int batch, const B
 template <typename T>
 hipError_t launch_bin_scatter(const ElemBatch& eb, int batch, const Geometry* geo, size_t stride, char* slot_base, size_t bins_off,
                               char* sorted_base, size_t sorted_stride, size_t inv_off, const MeshDims& m,
-                              const BinGeom& bg, int nblk, void* const* soa, hipStream_t s) {
-  (void)nblk;
+                              const BinGeom& bg, void* const* soa, hipStream_t s) {
   if (eb.max_np == 0) return hipSuccess;
   if (soa && batch != 1) return hipErrorInvalidValue;
   const SortedOut<T> so = sorted_out<T>(soa);
@@ -1831,10 +1829,10 @@ hipError_t launch_gather_direct(const ElemBatch& eb, int batch, const Geometry* 
 
 #define DKS_INSTANTIATE(T)                                                                                         \
   template hipError_t launch_bin_count<T>(const ElemBatch&, int, const Geometry*, size_t, char*, size_t, const MeshDims&,            \
-                                          const BinGeom&, int, hipStream_t);                                       \
+                                          const BinGeom&, hipStream_t);                                            \
   template bool scatter_scans<T>(const ElemBatch&, int, const BinGeom&);                                           \
   template hipError_t launch_bin_scatter<T>(const ElemBatch&, int, const Geometry*, size_t, char*, size_t,      \
-                                            char*, size_t, size_t, const MeshDims&, const BinGeom&, int,           \
+                                            char*, size_t, size_t, const MeshDims&, const BinGeom&,                \
                                             void* const*, hipStream_t);                                            \
   template hipError_t launch_deposit_binned<T>(const Geometry*, size_t, char*, size_t, const char*, size_t, void*, \
                                                size_t, const MeshDims&, const BinGeom&, int, int, void* const*,    \

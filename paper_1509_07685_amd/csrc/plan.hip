@@ -42,13 +42,13 @@ template <typename T> hipError_t launch_gradient(const void*, void*, const Geome
 template <typename T> hipError_t launch_gather(const void*, const void*, const void*, const void*, void*, void*,
                                                void*, int64_t, const Geometry*, const MeshDims&, int, hipStream_t);
 template <typename T> hipError_t launch_bin_count(const ElemBatch&, int, const Geometry*, size_t, char*, size_t,
-                                                  const MeshDims&, const BinGeom&, int, hipStream_t);
+                                                  const MeshDims&, const BinGeom&, hipStream_t);
 template <typename T> bool scatter_scans(const ElemBatch&, int, const BinGeom&);
 hipError_t launch_bin_scan(const Geometry*, size_t, char*, size_t, const BinGeom&, const ElemBatch&, int,
                            hipStream_t);
 template <typename T> hipError_t launch_bin_scatter(const ElemBatch&, int, const Geometry*, size_t, char*,
                                                     size_t, char*, size_t, size_t, const MeshDims&, const BinGeom&,
-                                                    int, void* const*, hipStream_t);
+                                                    void* const*, hipStream_t);
 template <typename T> hipError_t launch_deposit_binned(const Geometry*, size_t, char*, size_t, const char*, size_t,
                                                        void*, size_t, const MeshDims&, const BinGeom&, int, int, void* const*,
                                                        void*, size_t, hipStream_t);
@@ -477,7 +477,6 @@ GeoArgs geo_args(const dks_poisson_plan_s* p, int mode, int nblocks) {
 // Work split of one (batched) particle solve.
 struct PartWork {
   BinGeom bg;
-  int count_blocks;   // blocks of the count and scatter kernels (same chunking)
   int item_blocks;    // blocks of the deposit kernel (loops over work items)
   int gitem_blocks;   // blocks of the gather kernel (likewise)
 };
@@ -501,7 +500,6 @@ PartWork part_work(const dks_poisson_plan_s* p, int64_t maxn) {
   // deposit 16 -> 23 -> 29).
   const bool staged_phi = w.bg.scheme == kSchemeTSC || p->dtype == DKS_F64;
   w.bg.gitem = staged_phi ? (int)std::min<int64_t>(w.bg.item, std::max<int64_t>(2048, maxn / 2048)) : w.bg.item;
-  w.count_blocks = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (maxn + 8191) / 8192));
   const int64_t items = (maxn + w.bg.item - 1) / w.bg.item + w.bg.K + 1;
   w.item_blocks = (int)std::min<int64_t>(16384, std::max<int64_t>(1, items));
   const int64_t gitems = (maxn + w.bg.gitem - 1) / w.bg.gitem + w.bg.K + 1;
@@ -550,11 +548,11 @@ dks_status deposit_stage(const dks_poisson_plan_s* p, int batch, const Slots& sl
     return DKS_OK;
   }
   DKS_TK("bin_count", launch_bin_count<T>(eb, batch, sl.geo(), sl.stride, sl.base, p->s_bins, p->md, w.bg,
-                                          w.count_blocks, st));
+                                          st));
   if (!scans)
     DKS_TK("bin_scan", launch_bin_scan(sl.geo(), sl.stride, sl.base, p->s_bins, w.bg, eb, batch, st));
   DKS_TK("bin_scatter", launch_bin_scatter<T>(eb, batch, sl.geo(), sl.stride, sl.base, p->s_bins, sorted,
-                                              sorted_stride, inv_off, p->md, w.bg, w.count_blocks, soa, st));
+                                              sorted_stride, inv_off, p->md, w.bg, soa, st));
   DKS_TK("deposit", launch_deposit_binned<T>(sl.geo(), sl.stride, sl.base, p->s_bins, sorted, sorted_stride,
                                              sl.base + p->s_r3, sl.stride / sizeof(T), p->md, w.bg, w.item_blocks,
                                              batch, soa, iacc, sl.stride / sizeof(unsigned long long), st));
