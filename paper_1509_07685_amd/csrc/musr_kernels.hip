@@ -48,31 +48,10 @@ struct Params {
   double det[kMaxDet][4];   // N0, Nbkg, A0, phi
 };
 
-// Sum over the wavefront in a fixed order (xor shuffles).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Sum over the workgroup in a fixed order: within each wavefront by xor
-// shuffles, then the four wavefront sums in order.
-__device__ __forceinline__ double block_sum(double v, double* lds) {
-  v = wave_sum(v);
-  const int w = (int)threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) lds[w] = v;
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < kThreads / 64; ++i) s += lds[i];
-  __syncthreads();
-  return s;
-}
-
-// The four values of q summed over the wavefront each as by wave_sum (the same
-// pairs at every step), in 7 exchanges instead of 24: each half keeps two of
-// the four values at the first step, each quarter one at the second.  Lane l
-// returns the sum of value (l & 32 ? 1 : 0) + (l & 16 ? 2 : 0).
+// The four values of q summed over the wavefront in a fixed order (xor
+// shuffles), in 7 exchanges instead of 24: each half keeps two of the four
+// values at the first step, each quarter one at the second.  Lane l returns
+// the sum of value (l & 32 ? 1 : 0) + (l & 16 ? 2 : 0).
 __device__ __forceinline__ double wave_sum4(const double (&q)[kQuads]) {
   static_assert(kQuads == 4, "two halving steps");
   const bool hi = threadIdx.x & 32, odd = threadIdx.x & 16;
@@ -283,13 +262,21 @@ __global__ __launch_bounds__(kThreads, RUN > 1 && STAT == DKS_MUSR_MLE ? 3 : 4) 
 
 // One workgroup per set: the partials of its nblk blocks of bins, each block's
 // gy groups added first (fours of detectors to sixteens, `per` of them, and
-// these in order).
+// these in order).  The sum over the blocks is carried in two words (each
+// addition's exact rounding error beside it), because its few last additions
+// round by far the most: the result's relative error over 160 sets of 16 x
+// 206250 bins went from 9.0e-17 (chi-square) and 8.1e-17 (log-likelihood) rms to
+// 5.7e-17 and 5.2e-17 for 0.6 us.
 template <int STAT>
 __global__ __launch_bounds__(kThreads) void k_musr_final(const double* __restrict__ partial, int nblk, int gy, int per,
                                                          double* __restrict__ result) {
-  __shared__ double red[kThreads / 64];
+  __shared__ double2 red[kThreads / 64];
   const double* part = partial + (size_t)blockIdx.x * nblk * gy;
-  double v = 0.0;
+  double2 v = make_double2(0.0, 0.0);
+  auto add = [&](double hi, double lo) {
+    const double s = v.x + hi, t = s - v.x;
+    v = make_double2(s, v.y + lo + ((v.x - (s - t)) + (hi - t)));
+  };
   for (int i = (int)threadIdx.x; i < nblk; i += kThreads) {
     double block = 0.0;
     for (int g = 0; g < gy; g += per) {
@@ -297,10 +284,19 @@ __global__ __launch_bounds__(kThreads) void k_musr_final(const double* __restric
       for (int u = g; u < min(g + per, gy); ++u) w += part[(size_t)u * nblk + i];
       block += w;
     }
-    v += block;
+    add(block, 0.0);
   }
-  const double tot = block_sum(v, red);
-  if (threadIdx.x == 0) result[blockIdx.x] = STAT == DKS_MUSR_MLE ? 2.0 * tot : tot;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) add(__shfl_xor(v.x, o, 64), __shfl_xor(v.y, o, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = red[0];
+    for (int i = 1; i < kThreads / 64; ++i) add(red[i].x, red[i].y);
+    // (an infinite or undefined sum has no error beside it)
+    const double tot = isfinite(v.x) ? v.x + v.y : v.x;
+    result[blockIdx.x] = STAT == DKS_MUSR_MLE ? 2.0 * tot : tot;
+  }
 }
 
 }  // namespace musr
