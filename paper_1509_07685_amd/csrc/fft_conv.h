@@ -996,7 +996,7 @@ hipError_t launch_fft_x_fwd(const void* in, size_t in_stride, bool fixed, void* 
 
 template <typename T>
 hipError_t launch_fft_y_fwd(const void* A, void* B, size_t stride, const MeshDims& m, const PlanRef& P, int batch,
-                            int col0, int col1, hipStream_t s) {
+                            int col0, int col1, size_t records, hipStream_t s) {
   using C = typename Cplx<T>::type;
   const int W = P.host.W, t0 = col0 / W;
   dim3 grid((col1 + W - 1) / W - t0, m.nz, batch);
@@ -1007,10 +1007,13 @@ hipError_t launch_fft_y_fwd(const void* A, void* B, size_t stride, const MeshDim
   // 126.5 and 130.4, 192^3 (117) 197 and 192, 256x256x128 (136) 230 and 222, 256^3
   // (272) 459 and 437, 256x256x288 (306) 777 and 740; FP64 128^3 (68) 101.4 and
   // 103.5, 144^3 (96) 163 and 159, 162^3 (135) 241 and 230, 216^3 (319) 616 and 581,
-  // but 256^3 (528, with the field) 937 and 954.  The same stores in the other
-  // passes, or loads past the caches, gained nothing or lost.
-  const size_t bytes = (size_t)m.Ny * m.nz * m.cs * sizeof(C) * batch;
-  const bool stream = bytes >= ((size_t)90 << 20) && bytes <= ((size_t)384 << 20);
+  // but 256^3 (528, with the field) 937 and 954.  A smaller B competes with the
+  // particle records of the step (`records` bytes), which the gather reads again:
+  // 128x128x256 FP32 (72) with 3e6 particles (34 MiB) 266 and 276, with 1e7 (114)
+  // 447 and 444, with 1e7 on anisotropic cells 463 and 454.  The same stores in
+  // the other passes, or loads past the caches, gained nothing or lost.
+  const size_t bytes = (size_t)m.Ny * m.nz * m.cs * sizeof(C) * batch, MiB = (size_t)1 << 20;
+  const bool stream = bytes <= 384 * MiB && (bytes >= 90 * MiB || (bytes >= 64 * MiB && bytes + records >= 160 * MiB));
   const bool ok = with_plan<T, 0, false>(P.host, [&](auto sp) {
     hipLaunchKernelGGL((k_fft_y_fwd<T, decltype(sp)>), grid, dim3(block_threads<T, decltype(sp)>()), lds_bytes<T>(P.host), s,
                        (const C*)A, (C*)B, stride, m, P.dev, t0, stream);

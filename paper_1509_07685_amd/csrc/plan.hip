@@ -21,7 +21,7 @@ namespace dks {
 template <typename T> hipError_t launch_fft_x_fwd(const void*, size_t, bool, void*, size_t, const MeshDims&,
                                                   const PlanRef&, const void*, int, hipStream_t);
 template <typename T> hipError_t launch_fft_y_fwd(const void*, void*, size_t, const MeshDims&, const PlanRef&, int, int,
-                                                  int, hipStream_t);
+                                                  int, size_t, hipStream_t);
 template <typename T> hipError_t launch_fft_z_conv(const void*, void*, size_t, const void*, const Geometry*,
                                                    size_t, const MeshDims&, const PlanRef&, const PlanRef&, int,
                                                    int, int, hipStream_t);
@@ -451,7 +451,8 @@ dks_status convolve(const dks_poisson_plan_s* p, const void* src, size_t in_stri
   const void* post = p->ws + p->tw_post;
   const void* G = p->ws + p->off_green;
   DKS_TK("fft_x_fwd", launch_fft_x_fwd<T>(src, in_stride, fixed, R1, cstride, m, fx, post, batch, st));
-  DKS_TK("fft_y_fwd", launch_fft_y_fwd<T>(R1, R2, cstride, m, fy, batch, 0, m.ncols, st));
+  const size_t records = (size_t)phi_user.max_np * batch * p->part_elem;      // read again by the gather
+  DKS_TK("fft_y_fwd", launch_fft_y_fwd<T>(R1, R2, cstride, m, fy, batch, 0, m.ncols, records, st));
   DKS_TK("fft_z_conv", launch_fft_z_conv<T>(R2, R1, cstride, G, sl.geo(), sl.stride, m, fz, fzi, batch, 0, m.ncols, st));
   DKS_TK("fft_y_inv", launch_fft_y_inv<T>(R1, R2, cstride, m, fy, batch, 0, m.ncols, st));
   DKS_TK("fft_x_inv", launch_fft_x_inv<T>(R2, cstride, R3, rstride, phi_user, m, fx, post, batch, st));
