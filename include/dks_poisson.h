@@ -153,7 +153,8 @@ dks_status dks_poisson_batch_scratch_bytes(dks_poisson_plan_t plan, int batch, i
  * permutation, each rounded up to 256), attached with
  * dks_poisson_set_particle_scratch (256-byte aligned; NULL with 0 bytes
  * detaches).  A solve of more particles than the attached scratch holds
- * returns DKS_EWORKSPACE.  np must be at most 2^32 - 2^20. */
+ * returns DKS_EWORKSPACE.  np must be at most 2^32 - 2^20.  (Solves of few
+ * particles go without the grouping, with the same scratch attached.) */
 dks_status dks_poisson_particle_scratch_bytes(dks_poisson_plan_t plan, int64_t np, size_t* bytes);
 dks_status dks_poisson_set_particle_scratch(dks_poisson_plan_t plan, void* scratch, size_t bytes);
 

@@ -1,9 +1,10 @@
 // Mixed-radix Stockham FFT engine shared by the convolution passes and the
 // raw transform entry points: complex helpers, radix 2 to 16 butterflies, one
-// pass over an LDS tile of W pencils ([element][pencil], pencil fastest), the
-// pass loop with runtime plans (radices 2, 3, 4 and 8), and compile-time plans
-// for the lengths of common meshes.  A transform of P passes reads its first pass from any source and
-// hands its last pass to any sink, with P - 1 LDS round trips between.
+// pass over an LDS tile of W pencils ([element][pencil], pencil fastest), and
+// the pass loops on runtime plans (radices 2, 3, 4 and 8) and on the
+// compile-time plans of common lengths.  A transform of P passes reads its
+// first pass from any source and hands its last pass to any sink, with P - 1
+// LDS round trips between.
 #ifndef DKS_FFT_ENGINE_H
 #define DKS_FFT_ENGINE_H
 

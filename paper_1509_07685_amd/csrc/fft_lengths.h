@@ -24,7 +24,7 @@ template <typename T> struct PassLanes {
 // 16 to 512) the kernels are instantiated with the whole plan known at
 // compile time (length, tile width, LDS stride, radix order, lanes), so
 // butterfly indexing, twiddle offsets and guards fold to constants; the
-// runtime plan above serves every other shape.  A launcher uses a
+// runtime plan (DynPlan) serves every other shape.  A launcher uses a
 // compile-time plan only when the host plan matches it exactly.
 // ---------------------------------------------------------------------------
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v >> 1); }
@@ -210,10 +210,10 @@ template <typename T, int N, bool WIDE> using ColPlan =
     SPlan<N, (WIDE ? 256 : 128) / (2 * (int)sizeof(T)), (WIDE ? 256 : 128) / (2 * (int)sizeof(T)), false,
           PassLanes<T>::value>;
 
-// Calls f with the compile-time plan equal to host plan h, or with DynPlan;
-// false where neither can run it.  Plan creation gives a length the radices of static_radices exactly where
-// the compile-time kernels run it: every row, and columns whose array is
-// addressable with 32-bit element offsets.
+// Call f with the compile-time plan equal to host plan h, or with DynPlan;
+// false where neither can run it.  Plan creation gives a length the radices of
+// static_radices exactly where the compile-time kernels run it: every row, and
+// columns whose array is addressable with 32-bit element offsets.
 template <class SP, class Plan, class F> bool try_raw(const Plan& h, F&& f) {
   if (!plan_matches<SP>(h)) return false;
   f(SP{});
@@ -238,8 +238,8 @@ template <typename T, class Plan, class F> bool with_col_plan(const Plan& h, F&&
   if (off32) switch (h.N) {
 #define DKS_TRY(N)                                                                           \
   case N:                                                                                    \
-    if constexpr (N <= kWideMaxLength) done = try_raw<ColPlan<T, N, true>>(h, f);           \
-    if (!done) done = try_raw<ColPlan<T, N, false>>(h, f);                                  \
+    if constexpr (N <= kWideMaxLength) done = try_raw<ColPlan<T, N, true>>(h, f);            \
+    if (!done) done = try_raw<ColPlan<T, N, false>>(h, f);                                   \
     break;
     DKS_STATIC_LENGTHS(DKS_TRY)
 #undef DKS_TRY
