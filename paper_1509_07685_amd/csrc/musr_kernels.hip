@@ -10,8 +10,8 @@
 // the workgroup in a fixed order and stores a partial per set; a
 // one-workgroup-per-set kernel then adds the partials in a fixed order, so a
 // result is bitwise reproducible.  (A last-workgroup-done counter in the
-// first kernel would need an agent-scope release and acquire per workgroup,
-// i.e. an L2 write-back and invalidate each, which measured slower than the
+// first kernel, with release and acquire fences around the partials, takes an
+// L2 write-back and invalidate per workgroup, which measured slower than the
 // second launch.)
 //
 // A set's result does not depend on how many sets are evaluated with it, or
