@@ -43,6 +43,6 @@ def test_every_length_runs_where_plan_creation_meant_it(counts, dt):
 @pytest.mark.parametrize("dt", ["f32", "f64"])
 def test_radices_without_kernels_are_refused(counts, dt):
     """Radices of a compile-time plan on another tile, or where 32-bit offsets
-    do not reach: no launcher runs them, and the checker refuses them unless
+    do not reach: no launcher runs them, and the plan check refuses them unless
     the plan is a compile-time one."""
     assert counts[dt, "planted"] == [0, 0, 1, 0]
